@@ -141,7 +141,7 @@ typedef struct {
 } emsurf_solve_info;
 
 typedef struct {
-  int32_t Lx, Ly;           /* padded FFT lengths (>= 2n-1, of the form 2^a or 3 * 2^a) */
+  int32_t Lx, Ly;           /* padded FFT lengths (>= 2n-1, products of 2, 3 and 5) */
   int64_t n_freq;           /* Lx * Ly */
   size_t bytes_that64;      /* FP64 Fourier-domain store, 0 if absent */
   size_t bytes_that32;      /* FP32 store, 0 if absent */
@@ -267,7 +267,7 @@ emsurf_status emsurf_macromodels(int32_t n_types, int32_t n_eq, int32_t n_int, c
  *   x_dev   c128 [nrhs][ny][nx][n_eq], n_eq = 4 * geom->n_patch (J unknowns first).
  *   E_dev   c128 [nrhs][Lv][Lu][2] output (E_theta, E_phi) per bin; bins with
  *           u^2 + v^2 >= 1 (no real direction) are set to zero.
- * Lu >= nx and Lv >= ny must be supported FFT lengths (2^a <= 1024 or
+ * Lu >= nx and Lv >= ny must be lengths of the form (2^a <= 1024 or
  * 3 * 2^a <= 768); larger ones sample the pattern more finely.  Workspaces of
  * nrhs * n_eq * Lu * (ny + Lv) complex values are allocated for the call,
  * which synchronises `stream` before returning. */

@@ -171,7 +171,7 @@ void project(const GreenGeomDev& g, const void* X, int Lu, int Lv, int nrhs, dou
 void check_far_args(const emsurf_geom* geom, int32_t nx, int32_t ny, int32_t nrhs, int32_t Lu, int32_t Lv) {
   EMS_CHECK_ARG(nx >= 1 && ny >= 1 && nx <= 1024 && ny <= 1024, "lattice sizes must be in [1, 1024]");
   EMS_CHECK_ARG(nrhs >= 1 && nrhs <= 64, "nrhs must be in [1, 64]");
-  EMS_CHECK_ARG(fft_length_supported(Lu) && fft_length_supported(Lv) && Lu >= nx && Lv >= ny,
+  EMS_CHECK_ARG(fft_length_basic(Lu) && fft_length_basic(Lv) && Lu >= nx && Lv >= ny,
                 "Lu, Lv must be supported FFT lengths (2^a <= 1024 or 3 * 2^a <= 768) with Lu >= nx, Lv >= ny");
   EMS_CHECK_ARG(geom != nullptr && geom->k > 0, "the far field needs a wavenumber k > 0");
 }

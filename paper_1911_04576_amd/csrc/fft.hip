@@ -10,10 +10,9 @@
 // in place, and the last stage writes global memory directly, dropping the
 // points >= n_out (the crop of the inverse transform).
 //
-// Every thread holds VPT values of one column (G threads per column); radices
-// 2, 3, 4, 8 and 16 run as register butterflies.  The arithmetic type may
-// differ from the input and output types (FP64 <-> FP32 converting loads and
-// stores for the mixed-precision solve).
+// G threads share a column; radices 2 to 24 run as register butterflies.  The
+// arithmetic type may differ from the input and output types (FP64 <-> FP32
+// converting loads and stores for the mixed-precision solve).
 #include "internal.h"
 #include "green.h"
 
@@ -54,7 +53,63 @@ __device__ constexpr double kS16[16] = {
     0.0, -0.38268343236508978178, -0.70710678118654757274, -0.92387953251128673848,
     -1.0, -0.92387953251128673848, -0.70710678118654757274, -0.38268343236508978178};
 
-// In-register DFT of length R (3, or a power of two <= 16): a[k] <- sum_n a[n] e^{sign 2 pi i n k / R}
+// cos and sin of 2*pi*j/120, rounded from extended precision: the twiddles
+// inside the composite butterflies (radices 6 to 24 divide 120)
+__device__ constexpr double kC120[120] = {
+    1.0, 0.9986295347545738, 0.9945218953682733, 0.9876883405951378, 0.9781476007338057, 0.9659258262890683,
+    0.9510565162951535, 0.9335804264972017, 0.9135454576426009, 0.8910065241883679, 0.8660254037844386,
+    0.838670567945424, 0.8090169943749475, 0.7771459614569709, 0.7431448254773942, 0.7071067811865476,
+    0.6691306063588582, 0.6293203910498375, 0.5877852522924731, 0.5446390350150271, 0.5, 0.4539904997395468,
+    0.4067366430758002, 0.35836794954530027, 0.30901699437494745, 0.25881904510252074, 0.20791169081775934,
+    0.15643446504023087, 0.10452846326765347, 0.052335956242943835, 0.0, -0.052335956242943835,
+    -0.10452846326765347, -0.15643446504023087, -0.20791169081775934, -0.25881904510252074, -0.30901699437494745,
+    -0.35836794954530027, -0.4067366430758002, -0.4539904997395468, -0.5, -0.5446390350150271, -0.5877852522924731,
+    -0.6293203910498375, -0.6691306063588582, -0.7071067811865476, -0.7431448254773942, -0.7771459614569709,
+    -0.8090169943749475, -0.838670567945424, -0.8660254037844386, -0.8910065241883679, -0.9135454576426009,
+    -0.9335804264972017, -0.9510565162951535, -0.9659258262890683, -0.9781476007338057, -0.9876883405951378,
+    -0.9945218953682733, -0.9986295347545738, -1.0, -0.9986295347545738, -0.9945218953682733, -0.9876883405951378,
+    -0.9781476007338057, -0.9659258262890683, -0.9510565162951535, -0.9335804264972017, -0.9135454576426009,
+    -0.8910065241883679, -0.8660254037844386, -0.838670567945424, -0.8090169943749475, -0.7771459614569709,
+    -0.7431448254773942, -0.7071067811865476, -0.6691306063588582, -0.6293203910498375, -0.5877852522924731,
+    -0.5446390350150271, -0.5, -0.4539904997395468, -0.4067366430758002, -0.35836794954530027, -0.30901699437494745,
+    -0.25881904510252074, -0.20791169081775934, -0.15643446504023087, -0.10452846326765347, -0.052335956242943835,
+    0.0, 0.052335956242943835, 0.10452846326765347, 0.15643446504023087, 0.20791169081775934, 0.25881904510252074,
+    0.30901699437494745, 0.35836794954530027, 0.4067366430758002, 0.4539904997395468, 0.5, 0.5446390350150271,
+    0.5877852522924731, 0.6293203910498375, 0.6691306063588582, 0.7071067811865476, 0.7431448254773942,
+    0.7771459614569709, 0.8090169943749475, 0.838670567945424, 0.8660254037844386, 0.8910065241883679,
+    0.9135454576426009, 0.9335804264972017, 0.9510565162951535, 0.9659258262890683, 0.9781476007338057,
+    0.9876883405951378, 0.9945218953682733, 0.9986295347545738};
+__device__ constexpr double kS120[120] = {
+    0.0, 0.052335956242943835, 0.10452846326765347, 0.15643446504023087, 0.20791169081775934, 0.25881904510252074,
+    0.30901699437494745, 0.35836794954530027, 0.4067366430758002, 0.4539904997395468, 0.5, 0.5446390350150271,
+    0.5877852522924731, 0.6293203910498375, 0.6691306063588582, 0.7071067811865476, 0.7431448254773942,
+    0.7771459614569709, 0.8090169943749475, 0.838670567945424, 0.8660254037844386, 0.8910065241883679,
+    0.9135454576426009, 0.9335804264972017, 0.9510565162951535, 0.9659258262890683, 0.9781476007338057,
+    0.9876883405951378, 0.9945218953682733, 0.9986295347545738, 1.0, 0.9986295347545738, 0.9945218953682733,
+    0.9876883405951378, 0.9781476007338057, 0.9659258262890683, 0.9510565162951535, 0.9335804264972017,
+    0.9135454576426009, 0.8910065241883679, 0.8660254037844386, 0.838670567945424, 0.8090169943749475,
+    0.7771459614569709, 0.7431448254773942, 0.7071067811865476, 0.6691306063588582, 0.6293203910498375,
+    0.5877852522924731, 0.5446390350150271, 0.5, 0.4539904997395468, 0.4067366430758002, 0.35836794954530027,
+    0.30901699437494745, 0.25881904510252074, 0.20791169081775934, 0.15643446504023087, 0.10452846326765347,
+    0.052335956242943835, 0.0, -0.052335956242943835, -0.10452846326765347, -0.15643446504023087,
+    -0.20791169081775934, -0.25881904510252074, -0.30901699437494745, -0.35836794954530027, -0.4067366430758002,
+    -0.4539904997395468, -0.5, -0.5446390350150271, -0.5877852522924731, -0.6293203910498375, -0.6691306063588582,
+    -0.7071067811865476, -0.7431448254773942, -0.7771459614569709, -0.8090169943749475, -0.838670567945424,
+    -0.8660254037844386, -0.8910065241883679, -0.9135454576426009, -0.9335804264972017, -0.9510565162951535,
+    -0.9659258262890683, -0.9781476007338057, -0.9876883405951378, -0.9945218953682733, -0.9986295347545738, -1.0,
+    -0.9986295347545738, -0.9945218953682733, -0.9876883405951378, -0.9781476007338057, -0.9659258262890683,
+    -0.9510565162951535, -0.9335804264972017, -0.9135454576426009, -0.8910065241883679, -0.8660254037844386,
+    -0.838670567945424, -0.8090169943749475, -0.7771459614569709, -0.7431448254773942, -0.7071067811865476,
+    -0.6691306063588582, -0.6293203910498375, -0.5877852522924731, -0.5446390350150271, -0.5, -0.4539904997395468,
+    -0.4067366430758002, -0.35836794954530027, -0.30901699437494745, -0.25881904510252074, -0.20791169081775934,
+    -0.15643446504023087, -0.10452846326765347, -0.052335956242943835};
+
+// factors R = A B of a composite butterfly, 0 for the others
+constexpr int composite_a(int R) {
+  return R == 6 ? 3 : R == 10 || R == 15 || R == 20 ? 5 : R == 12 ? 4 : R == 24 ? 8 : 0;
+}
+
+// In-register DFT of length R: a[k] <- sum_n a[n] e^{sign 2 pi i n k / R}
 template <int R, typename V>
 __device__ __forceinline__ void dft(V (&a)[R], int sign) {
   using T = typename Real<V>::T;
@@ -70,6 +125,46 @@ __device__ __forceinline__ void dft(V (&a)[R], int sign) {
     a[0] = cadd(a[0], t1);
     a[1] = cadd(t2, u);
     a[2] = csub(t2, u);
+  } else if constexpr (R == 5) {
+    // real and imaginary rows share the sums a1 +- a4 and a2 +- a3
+    const T c1 = static_cast<T>(kC120[24]), c2 = static_cast<T>(kC120[48]);
+    const T s1 = static_cast<T>(kS120[24]), s2 = static_cast<T>(kS120[48]);
+    const V t1 = cadd(a[1], a[4]), t2 = cadd(a[2], a[3]);
+    const V d1 = csub(a[1], a[4]), d2 = csub(a[2], a[3]);
+    const V m1 = V{a[0].x + c1 * t1.x + c2 * t2.x, a[0].y + c1 * t1.y + c2 * t2.y};
+    const V m2 = V{a[0].x + c2 * t1.x + c1 * t2.x, a[0].y + c2 * t1.y + c1 * t2.y};
+    const V u1 = mul_si(V{s1 * d1.x + s2 * d2.x, s1 * d1.y + s2 * d2.y}, sign);
+    const V u2 = mul_si(V{s2 * d1.x - s1 * d2.x, s2 * d1.y - s1 * d2.y}, sign);
+    a[0] = V{a[0].x + t1.x + t2.x, a[0].y + t1.y + t2.y};
+    a[1] = cadd(m1, u1);
+    a[4] = csub(m1, u1);
+    a[2] = cadd(m2, u2);
+    a[3] = csub(m2, u2);
+  } else if constexpr (composite_a(R) > 0) {
+    // n = B n1 + n2, k = k1 + A k2: B butterflies of length A, twiddles, A of length B
+    constexpr int A = composite_a(R), B = R / A;
+    V c[B][A];
+#pragma unroll
+    for (int n2 = 0; n2 < B; ++n2) {
+#pragma unroll
+      for (int n1 = 0; n1 < A; ++n1) c[n2][n1] = a[B * n1 + n2];
+      dft<A, V>(c[n2], sign);
+#pragma unroll
+      for (int k1 = 1; k1 < A; ++k1) {
+        if (n2 == 0) continue;
+        const int j = n2 * k1 % R * (120 / R);
+        c[n2][k1] = cmul(V{static_cast<T>(kC120[j]), static_cast<T>(sign < 0 ? -kS120[j] : kS120[j])}, c[n2][k1]);
+      }
+    }
+#pragma unroll
+    for (int k1 = 0; k1 < A; ++k1) {
+      V d[B];
+#pragma unroll
+      for (int n2 = 0; n2 < B; ++n2) d[n2] = c[n2][k1];
+      dft<B, V>(d, sign);
+#pragma unroll
+      for (int k2 = 0; k2 < B; ++k2) a[k1 + A * k2] = d[k2];
+    }
   } else if constexpr (R == 2) {
     V t = a[0];
     a[0] = cadd(t, a[1]);
@@ -120,13 +215,14 @@ struct PassArgs {
   double scale;
 };
 
-// Compile-time plan of a transform length L = 2^a (2..1024) or 3 * 2^a
-// (24..768): every thread holds VPT values of one column (G = L / VPT threads
-// per column, BT columns per workgroup of NT threads).  Power-of-two lengths
-// run radix-16 stages while possible, then one radix-2/4/8 stage; lengths with
-// a factor 3 run radix-8 stages, one radix-2/4 stage if needed, then radix 3.
-// WD = 2 doubles the threads and so the columns per workgroup (256-byte runs
-// per point in FP32; 64 KB of LDS at L = 256).
+// Compile-time plan of a transform length: radix of each stage, G threads per
+// column and BT columns per workgroup (NT = G BT threads).  A stage's L / R
+// butterflies go round the G threads (the last round partly idle where G does
+// not divide them).  WD = 2 doubles the threads and so the columns per
+// workgroup (256-byte runs per point in FP32; 64 KB of LDS at L = 256).
+//
+// Lengths 2^a (2..1024) and 3 * 2^a (24..768) run radix-16 or radix-8 stages
+// while possible, then what is left of the power of two, then radix 3.
 template <int L, int WD = 1> struct Shape {
   static constexpr bool R3 = L % 3 == 0;
   static constexpr int VPT = R3 ? 24 : (L >= 16 ? 16 : L);
@@ -160,15 +256,38 @@ template <int L, int WD = 1> struct Shape {
   static constexpr int NST = nst();
 };
 
+// The lengths between them, products of 2, 3 and 5: one or two stages of
+// composite radices (one LDS exchange), with 16 or 32 columns and 10 to 24
+// values per thread.
+template <int L_, int WD, int G_, int BT_, int R0, int R1, int R2> struct MixedShape {
+  static constexpr int G = G_, BT = BT_ * WD, NT = G * BT;
+  static constexpr int NST = R2 > 1 ? 3 : R1 > 1 ? 2 : 1;
+  static constexpr int radix(int s) { return s == 0 ? R0 : s == 1 ? R1 : R2; }
+  static_assert(R0 * R1 * R2 == L_, "radices multiply to the length");
+};
+// length, threads per column, columns per workgroup, radices
+#define EMS_MIXED_LENGTHS(X)                                                                             \
+  X(6, 1, 64, 6, 1, 1) X(10, 1, 64, 10, 1, 1) X(12, 1, 64, 12, 1, 1) X(20, 1, 64, 20, 1, 1)              \
+  X(36, 6, 32, 6, 6, 1) X(40, 4, 32, 10, 4, 1) X(60, 4, 32, 15, 4, 1) X(72, 6, 32, 12, 6, 1)             \
+  X(80, 4, 32, 20, 4, 1) X(100, 10, 16, 10, 10, 1) X(120, 8, 16, 15, 8, 1) X(144, 12, 16, 12, 12, 1)     \
+  X(160, 8, 16, 20, 8, 1) X(180, 12, 16, 15, 12, 1) X(200, 10, 16, 20, 10, 1) X(225, 15, 16, 15, 15, 1)  \
+  X(240, 16, 16, 16, 15, 1) X(288, 12, 16, 24, 12, 1) X(320, 16, 8, 8, 8, 5) X(360, 24, 8, 24, 15, 1)    \
+  X(400, 20, 8, 20, 20, 1) X(480, 24, 8, 24, 20, 1) X(576, 24, 8, 24, 24, 1)
+#define EMS_MIXED_SHAPE(L, G, BT, R0, R1, R2) \
+  template <int WD> struct Shape<L, WD> : MixedShape<L, WD, G, BT, R0, R1, R2> {};
+EMS_MIXED_LENGTHS(EMS_MIXED_SHAPE)
+#undef EMS_MIXED_SHAPE
+
 template <int L, int WD, int GEN, int S, int P, typename VI, typename VC, typename VO>
 __device__ __forceinline__ void run_stage(const PassArgs& a, VC* lds, const VI* __restrict__ in,
                                           VO* __restrict__ out, const VC* __restrict__ tw, bool valid, int b,
                                           int g, const GreenGen& gg, int col, int line) {
   using SH = Shape<L, WD>;
   constexpr int R = SH::radix(S);
-  constexpr int NB = SH::VPT / R;
   constexpr int LR = L / R;
   constexpr int G = SH::G;
+  constexpr int NB = (LR + G - 1) / G;
+  constexpr bool EVEN = LR % G == 0;   // every thread has NB butterflies
   constexpr int BT = SH::BT;
   constexpr bool FIRST = S == 0;
   constexpr bool LAST = S == SH::NST - 1;
@@ -190,7 +309,7 @@ __device__ __forceinline__ void run_stage(const PassArgs& a, VC* lds, const VI* 
         const int pos = i + q * LR;
         bool okx = false;
         const int dx = slot_to_offset(pos, L, gg.nx, &okx);
-        if (valid && oky && okx && pos < a.n_in)
+        if (valid && oky && okx && pos < a.n_in && (EVEN || i < LR))
           v[j][q] = cvt<VC>(green_entry(gg.rho, gg.area, gg.tan, gg.P, gg.pitch, gg.k, dx, dy, u, vv));
         else
           v[j][q] = VC{0, 0};
@@ -203,7 +322,7 @@ __device__ __forceinline__ void run_stage(const PassArgs& a, VC* lds, const VI* 
 #pragma unroll
       for (int q = 0; q < R; ++q) {
         const int pos = i + q * LR;
-        if (valid && pos < a.n_in)
+        if (valid && pos < a.n_in && (EVEN || i < LR))
           v[j][q] = cvt<VC>(in[(unsigned)(pos * a.in_pt)]);
         else
           v[j][q] = VC{0, 0};
@@ -215,7 +334,7 @@ __device__ __forceinline__ void run_stage(const PassArgs& a, VC* lds, const VI* 
     for (int j = 0; j < NB; ++j) {
       const int i = g + G * j;
 #pragma unroll
-      for (int q = 0; q < R; ++q) v[j][q] = lds[(i + q * LR) * BT + b];
+      for (int q = 0; q < R; ++q) v[j][q] = EVEN || i < LR ? lds[(i + q * LR) * BT + b] : VC{0, 0};
     }
     if constexpr (!LAST) __syncthreads();
   }
@@ -239,6 +358,7 @@ __device__ __forceinline__ void run_stage(const PassArgs& a, VC* lds, const VI* 
 #pragma unroll
   for (int j = 0; j < NB; ++j) {
     const int i = g + G * j;
+    if (!EVEN && i >= LR) continue;
     const int k = i % P;
     const int base = (i - k) * R + k;
 #pragma unroll
@@ -290,17 +410,26 @@ void launch_L(const PassArgs& a, int batch, unsigned lines, const void* in, void
                      static_cast<const VI*>(in), static_cast<VO*>(out), static_cast<const VC*>(tw), gg);
 }
 
+constexpr bool mixed_length(int L) {
+#define EMS_IS_LENGTH(LL, ...) L == LL ||
+  return EMS_MIXED_LENGTHS(EMS_IS_LENGTH) false;
+#undef EMS_IS_LENGTH
+}
+
+constexpr bool wide_length(int L) { return L == 64 || L == 128 || L == 256 || (L >= 100 && mixed_length(L)); }
+
 template <typename VI, typename VC, typename VO>
 void launch_typed(int L, const PassArgs& a, int batch, unsigned lines, const void* in, void* out, const void* tw,
                   hipStream_t s) {
   // FP32 arithmetic at power-of-two lengths 64..256 with at least 64 columns
   // takes the doubled workgroup (measured 5-7% faster at L = 256 with 192 and
-  // 768 columns); FP64 keeps 256 threads, whose LDS would double to 128 KB
+  // 768 columns), and so do the mixed lengths from 100 on, whose runs are 128
+  // bytes otherwise; FP64 keeps 256 threads, whose LDS would double to 128 KB
   constexpr bool f32 = std::is_same<VC, float2>::value;
-  const bool wide = f32 && (L == 64 || L == 128 || L == 256) && batch >= 64;
+  const bool wide = f32 && batch >= 64;
 #define EMS_FFT_CASE(LL)                                                           \
   case LL: {                                                                       \
-    if constexpr (f32 && (LL == 64 || LL == 128 || LL == 256)) {                   \
+    if constexpr (f32 && wide_length(LL)) {                                        \
       if (wide) {                                                                  \
         launch_L<LL, 2, VI, VC, VO>(a, batch, lines, in, out, tw, s);              \
         break;                                                                     \
@@ -309,6 +438,7 @@ void launch_typed(int L, const PassArgs& a, int batch, unsigned lines, const voi
     launch_L<LL, 1, VI, VC, VO>(a, batch, lines, in, out, tw, s);                  \
     break;                                                                         \
   }
+#define EMS_FFT_MIXED(LL, ...) EMS_FFT_CASE(LL)
   switch (L) {
     EMS_FFT_CASE(2)
     EMS_FFT_CASE(4)
@@ -326,8 +456,10 @@ void launch_typed(int L, const PassArgs& a, int batch, unsigned lines, const voi
     EMS_FFT_CASE(192)
     EMS_FFT_CASE(384)
     EMS_FFT_CASE(768)
+    EMS_MIXED_LENGTHS(EMS_FFT_MIXED)
     default: break;
   }
+#undef EMS_FFT_MIXED
 #undef EMS_FFT_CASE
 }
 
@@ -374,14 +506,14 @@ const void* twiddle_table(int L, Cx t) {
   return buf->p;
 }
 
-bool fft_length_supported(int L) {
+bool fft_length_basic(int L) {
   if (L >= 2 && L <= 1024 && (L & (L - 1)) == 0) return true;
   if (L % 3 != 0) return false;
   const int q = L / 3;
   return q >= 8 && q <= 256 && (q & (q - 1)) == 0;
 }
 
-int fft_length_at_least(int v) {
+int fft_length_basic_at_least(int v) {
   int best = 2;
   while (best < v) best <<= 1;
   for (int q = 8; 3 * q <= 768; q <<= 1)
@@ -389,9 +521,21 @@ int fft_length_at_least(int v) {
   return best;
 }
 
+// The padded spectrum holds Lx Ly blocks, and streaming them is most of an
+// apply, so a lattice takes the shortest length that holds it: 90 x 100
+// elements pad to 180 x 200 frequencies, where 192 x 256 took 37% more (FP32
+// structured T-apply with 4 RHS at n_eq 192: 1.10 -> 0.85 ms; FP64 A-apply of
+// 23 x 17 elements of 150 unknowns with 6 RHS, 48 x 48 -> 48 x 36: 245 -> 185 us).
+int fft_length_at_least(int v) {
+  int best = fft_length_basic_at_least(v);
+  for (int L = v; L < best; ++L)
+    if (mixed_length(L)) best = L;
+  return best;
+}
+
 namespace {
 PassArgs pass_args(const FftPass& p) {
-  EMS_CHECK_ARG(fft_length_supported(p.L), "FFT length must be 2^a in [2, 1024] or 3 * 2^a in [24, 768]");
+  EMS_CHECK_ARG(fft_length_basic(p.L) || mixed_length(p.L), "internal: no FFT kernel of this length");
   EMS_CHECK_ARG(p.n_in >= 1 && p.n_in <= p.L && p.n_out >= 1 && p.n_out <= p.L, "FFT prune/crop sizes out of range");
   EMS_CHECK_ARG(p.batch >= 1 && p.n_lines >= 1 && p.nl0 >= 1, "FFT batch/lines must be positive");
   EMS_CHECK_ARG(p.n_lines <= 65535, "FFT pass has more than 65535 lines");
@@ -454,6 +598,9 @@ void launch_fft_pass_green(const FftPass& p, const GreenGeomDev& geo, int nx, in
     EMS_FFT_GEN(192)
     EMS_FFT_GEN(384)
     EMS_FFT_GEN(768)
+#define EMS_FFT_GEN_MIXED(LL, ...) EMS_FFT_GEN(LL)
+    EMS_MIXED_LENGTHS(EMS_FFT_GEN_MIXED)
+#undef EMS_FFT_GEN_MIXED
     default: break;
   }
 #undef EMS_FFT_GEN

@@ -39,8 +39,9 @@ void validate_desc(const emsurf_plan_desc* d) {
   }
   // The pass along y of a full-width apply spans Lx Ly max_rhs n_eq complex
   // values, addressed with 32-bit offsets inside the FFT kernels: refuse such
-  // plans here rather than at their first apply.
-  const int64_t Lx = fft_length_at_least(2 * d->nx - 1), Ly = fft_length_at_least(2 * d->ny - 1);
+  // plans here rather than at their first apply.  The limit is that of the
+  // 2^a and 3 * 2^a lengths, also where the plan pads to a shorter one.
+  const int64_t Lx = fft_length_basic_at_least(2 * d->nx - 1), Ly = fft_length_basic_at_least(2 * d->ny - 1);
   const int64_t B = (int64_t)d->max_rhs * d->n_eq;
   EMS_CHECK_ARG(Lx * Ly * B + B + 1024 < (1LL << 31),
                 "padded lattice x max_rhs x n_eq exceeds the 2^31 values one FFT pass addresses; "
