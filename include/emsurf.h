@@ -243,10 +243,12 @@ emsurf_status emsurf_fill_LK_point_green(const emsurf_geom* geom, int32_t nx, in
  *              layout of emsurf_plan_create once copied to the host).
  *   Zt_dev     c128 [n_types][n_eq][n_eq] output of Z~, or NULL.
  * 1 <= n_types <= 4096, 1 <= n_eq <= 512, 0 <= n_int <= 4096.  Workspaces of
- * n_types ((n_eq + n_int)^2 + 4 n_eq^2) complex values are allocated for the
- * call.  Part of the elimination runs on a second stream that the library
- * creates once per device (default priority) and joins back into `stream`;
- * the call blocks until `stream` is done.  A singular Z_int,int or Z~ + Z_self (a zero
+ * n_types ((n_eq + n_int)^2 + 4 n_eq^2) complex values are taken for the
+ * call from memory that the library keeps (at most 4 GiB per device, freed with
+ * the process's last plan and whenever an allocation fails).  Part of the
+ * elimination runs on a second stream that the library creates once per device
+ * (default priority) and joins back into `stream`; the call blocks until
+ * `stream` is done.  A singular Z_int,int or Z~ + Z_self (a zero
  * pivot column) returns EMSURF_ERR_ARG naming the cell type, with the outputs
  * unspecified. */
 emsurf_status emsurf_macromodels(int32_t n_types, int32_t n_eq, int32_t n_int, const void* Z_dev,
@@ -269,8 +271,9 @@ emsurf_status emsurf_macromodels(int32_t n_types, int32_t n_eq, int32_t n_int, c
  *           u^2 + v^2 >= 1 (no real direction) are set to zero.
  * Lu >= nx and Lv >= ny must be lengths of the form (2^a <= 1024 or
  * 3 * 2^a <= 768); larger ones sample the pattern more finely.  Workspaces of
- * nrhs * n_eq * Lu * (ny + Lv) complex values are allocated for the call,
- * which synchronises `stream` before returning. */
+ * nrhs * n_eq * Lu * (ny + Lv) complex values are taken as in
+ * emsurf_macromodels for the call, which synchronises `stream` before
+ * returning. */
 emsurf_status emsurf_far_field(const emsurf_geom* geom, int32_t nx, int32_t ny, int32_t nrhs, int32_t Lu,
                                int32_t Lv, const void* x_dev, void* E_dev, void* stream);
 
@@ -569,7 +572,7 @@ emsurf_status emsurf_server_query(emsurf_server server, emsurf_server_stats* out
 /* device bytes a resident surface with this desc (nx, ny, n_eq, n_types) holds on
  * this server with no busy right-hand side (plan with its stream's apply
  * workspace, which its session shares, the session's batch staging and
- * reductions, one staging vector), as used for admission; 0 if invalid */
+ * reductions), as used for admission; 0 if invalid */
 size_t emsurf_server_entry_bytes(emsurf_server server, const emsurf_plan_desc* desc);
 /* device bytes each busy right-hand side adds on that surface (its slot's
  * vectors and Krylov basis); 0 if invalid */

@@ -163,7 +163,7 @@ void project(const GreenGeomDev& g, const void* X, int Lu, int Lv, int nrhs, dou
   long long grid = (total + 255) / 256;
   if (grid > 65536) grid = 65536;
   hipLaunchKernelGGL(far_field_kernel, dim3((unsigned)grid), dim3(256), 0, s, static_cast<const double2*>(X),
-                     g.rho.as<const double>(), g.area.as<const double>(), g.tan.as<const double>(), g.n_patch,
+                     g.rho, g.area, g.tan, g.n_patch,
                      g.pitch, g.k, Lu, Lv, nrhs, wsign, static_cast<double2*>(E));
   EMS_LAUNCH_CHECK();
 }
@@ -188,13 +188,16 @@ extern "C" emsurf_status emsurf_far_field(const emsurf_geom* geom, int32_t nx, i
     check_far_args(geom, nx, ny, nrhs, Lu, Lv);
     hipStream_t s = static_cast<hipStream_t>(stream);
     GreenGeomDev g;
-    upload_geom(geom, g);
+    upload_geom(geom, g, s);
     const int64_t B = (int64_t)nrhs * 4 * g.n_patch;
-    DevBuf W((size_t)ny * Lu * B * 16), X((size_t)Lv * Lu * B * 16);
-    lattice_dft(g, nx, ny, nrhs, Lu, Lv, x_dev, W.p, X.p, s);
-    project(g, X.p, Lu, Lv, nrhs, 1.0, E_dev, s);
-    // the workspaces and geometry are freed on return
+    const size_t b_w = (size_t)ny * Lu * B * 16, b_x = (size_t)Lv * Lu * B * 16;
+    Scratch ws(Scratch::round(b_w) + b_x);
+    void *W = ws.part(b_w), *X = ws.part(b_x);
+    lattice_dft(g, nx, ny, nrhs, Lu, Lv, x_dev, W, X, s);
+    project(g, X, Lu, Lv, nrhs, 1.0, E_dev, s);
     EMS_HIP(hipStreamSynchronize(s));
+    ws.idle();
+    g.idle();
     return EMSURF_OK;
   } catch (...) {
     return current_exception_status();
@@ -209,34 +212,38 @@ extern "C" emsurf_status emsurf_directivity(const emsurf_geom* geom, int32_t nx,
     check_far_args(geom, nx, ny, nrhs, Lu, Lv);
     hipStream_t s = static_cast<hipStream_t>(stream);
     GreenGeomDev g;
-    upload_geom(geom, g);
+    upload_geom(geom, g, s);
     const int64_t B = (int64_t)nrhs * 4 * g.n_patch, bins = (int64_t)Lu * Lv;
-    DevBuf W((size_t)ny * Lu * B * 16), X((size_t)Lv * Lu * B * 16);
-    DevBuf Eu((size_t)nrhs * bins * 32), El((size_t)nrhs * bins * 32);
-    lattice_dft(g, nx, ny, nrhs, Lu, Lv, x_dev, W.p, X.p, s);
-    project(g, X.p, Lu, Lv, nrhs, 1.0, Eu.p, s);
-    project(g, X.p, Lu, Lv, nrhs, -1.0, El.p, s);
     const int slices = 64;
-    DevBuf part((size_t)nrhs * slices * 8), prad((size_t)nrhs * 8);
+    const size_t b_w = (size_t)ny * Lu * B * 16, b_x = (size_t)Lv * Lu * B * 16, b_e = (size_t)nrhs * bins * 32;
+    const size_t b_part = (size_t)nrhs * slices * 8, b_prad = (size_t)nrhs * 8;
+    Scratch ws(Scratch::round(b_w) + Scratch::round(b_x) + 2 * Scratch::round(b_e) + Scratch::round(b_part) + b_prad);
+    void *W = ws.part(b_w), *X = ws.part(b_x);
+    double2 *Eu = ws.part<double2>(b_e), *El = ws.part<double2>(b_e);
+    double *part = ws.part<double>(b_part), *prad = ws.part<double>(b_prad);
+    lattice_dft(g, nx, ny, nrhs, Lu, Lv, x_dev, W, X, s);
+    project(g, X, Lu, Lv, nrhs, 1.0, Eu, s);
+    project(g, X, Lu, Lv, nrhs, -1.0, El, s);
     hipLaunchKernelGGL(power_partial_kernel, dim3(slices, (unsigned)nrhs), dim3(DIR_THREADS), 0, s,
-                       Eu.as<const double2>(), El.as<const double2>(), Lu, Lv, g.pitch, g.k, slices,
-                       part.as<double>());
+                       Eu, El, Lu, Lv, g.pitch, g.k, slices, part);
     EMS_LAUNCH_CHECK();
     std::vector<double> hp((size_t)nrhs * slices), pr(nrhs, 0.0);
-    EMS_HIP(hipMemcpyAsync(hp.data(), part.p, hp.size() * 8, hipMemcpyDeviceToHost, s));
+    EMS_HIP(hipMemcpyAsync(hp.data(), part, hp.size() * 8, hipMemcpyDeviceToHost, s));
     EMS_HIP(hipStreamSynchronize(s));
     for (int r = 0; r < nrhs; ++r) {
       for (int sl = 0; sl < slices; ++sl) pr[r] += hp[(size_t)r * slices + sl];
       EMS_CHECK_ARG(pr[r] > 0 && std::isfinite(pr[r]), "the currents radiate no power (zero or non-finite x)");
     }
-    EMS_HIP(hipMemcpyAsync(prad.p, pr.data(), (size_t)nrhs * 8, hipMemcpyHostToDevice, s));
+    EMS_HIP(hipMemcpyAsync(prad, pr.data(), (size_t)nrhs * 8, hipMemcpyHostToDevice, s));
     const long long total = (long long)nrhs * 2 * bins;
     long long grid = (total + 255) / 256;
     if (grid > 65536) grid = 65536;
-    hipLaunchKernelGGL(directivity_kernel, dim3((unsigned)grid), dim3(256), 0, s, Eu.as<const double2>(),
-                       El.as<const double2>(), Lu, Lv, nrhs, prad.as<const double>(), static_cast<double*>(D_dev));
+    hipLaunchKernelGGL(directivity_kernel, dim3((unsigned)grid), dim3(256), 0, s, Eu, El, Lu, Lv,
+                       nrhs, prad, static_cast<double*>(D_dev));
     EMS_LAUNCH_CHECK();
     EMS_HIP(hipStreamSynchronize(s));
+    ws.idle();
+    g.idle();
     if (prad_host)
       for (int r = 0; r < nrhs; ++r) prad_host[r] = pr[r];
     return EMSURF_OK;

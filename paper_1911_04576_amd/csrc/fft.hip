@@ -564,9 +564,9 @@ void launch_fft_pass_green(const FftPass& p, const GreenGeomDev& geo, int nx, in
                     c0 + p.batch <= (int64_t)n * n,
                 "internal: generating kernel pass shape");
   GreenGen gg;
-  gg.rho = geo.rho.as<const double>();
-  gg.area = geo.area.as<const double>();
-  gg.tan = geo.tan.as<const double>();
+  gg.rho = geo.rho;
+  gg.area = geo.area;
+  gg.tan = geo.tan;
   gg.P = geo.n_patch;
   gg.nx = nx;
   gg.ny = ny;

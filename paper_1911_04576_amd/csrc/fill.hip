@@ -425,8 +425,8 @@ void launch_green_padded(const GreenGeomDev& g, int nx, int ny, int Lx, int Ly, 
   const int64_t ncol = (c0 + nc - 1) / n - c0 / n + 1;
   const long long total = (long long)Ly * Lx * ncol * g.n_patch;
   EMS_CHECK_ARG(nc >= 1 && total < (1LL << 31) && c0 + nc < (1LL << 31), "internal: fill chunk exceeds 32-bit indices");
-  hipLaunchKernelGGL(green_padded_kernel, dim3(grid_for(total, 256)), dim3(256), 0, s, g.rho.as<const double>(),
-                     g.area.as<const double>(), g.tan.as<const double>(), g.n_patch, g.pitch, g.k, nx, ny, Lx, Ly,
+  hipLaunchKernelGGL(green_padded_kernel, dim3(grid_for(total, 256)), dim3(256), 0, s, g.rho,
+                     g.area, g.tan, g.n_patch, g.pitch, g.k, nx, ny, Lx, Ly,
                      (long long)c0, (long long)nc, vperm, static_cast<double2*>(K));
   EMS_LAUNCH_CHECK();
 }
@@ -435,8 +435,8 @@ void launch_lk_padded(const GreenGeomDev& g, int nx, int ny, int Lx, int Ly, int
                       hipStream_t s) {
   const long long total = (long long)Ly * Lx * nc;
   EMS_CHECK_ARG(total < (1LL << 31) && c0 + nc < (1LL << 31), "internal: fill chunk exceeds 32-bit indices");
-  hipLaunchKernelGGL(lk_padded_kernel, dim3(grid_for(total, 256)), dim3(256), 0, s, g.rho.as<const double>(),
-                     g.area.as<const double>(), g.tan.as<const double>(), g.n_patch, g.pitch, g.k, nx, ny, Lx, Ly,
+  hipLaunchKernelGGL(lk_padded_kernel, dim3(grid_for(total, 256)), dim3(256), 0, s, g.rho,
+                     g.area, g.tan, g.n_patch, g.pitch, g.k, nx, ny, Lx, Ly,
                      (long long)c0, (long long)nc, static_cast<double2*>(K));
   EMS_LAUNCH_CHECK();
 }
@@ -444,8 +444,8 @@ void launch_lk_padded(const GreenGeomDev& g, int nx, int ny, int Lx, int Ly, int
 void launch_lk_blocks(const GreenGeomDev& g, int nx, int ny, void* LK_blocks, hipStream_t s) {
   const long long nh = 2LL * g.n_patch;
   const long long total = (long long)(2 * ny - 1) * (2 * nx - 1) * 2 * nh * nh;
-  hipLaunchKernelGGL(lk_blocks_kernel, dim3(grid_for(total, 256)), dim3(256), 0, s, g.rho.as<const double>(),
-                     g.area.as<const double>(), g.tan.as<const double>(), g.n_patch, g.pitch, g.k, nx, ny,
+  hipLaunchKernelGGL(lk_blocks_kernel, dim3(grid_for(total, 256)), dim3(256), 0, s, g.rho,
+                     g.area, g.tan, g.n_patch, g.pitch, g.k, nx, ny,
                      static_cast<double2*>(LK_blocks));
   EMS_LAUNCH_CHECK();
 }
@@ -453,8 +453,8 @@ void launch_lk_blocks(const GreenGeomDev& g, int nx, int ny, void* LK_blocks, hi
 void launch_green_blocks(const GreenGeomDev& g, int nx, int ny, void* T_blocks, hipStream_t s) {
   const long long n = 4LL * g.n_patch;
   const long long total = (long long)(2 * ny - 1) * (2 * nx - 1) * n * n;
-  hipLaunchKernelGGL(green_blocks_kernel, dim3(grid_for(total, 256)), dim3(256), 0, s, g.rho.as<const double>(),
-                     g.area.as<const double>(), g.tan.as<const double>(), g.n_patch, g.pitch, g.k, nx, ny,
+  hipLaunchKernelGGL(green_blocks_kernel, dim3(grid_for(total, 256)), dim3(256), 0, s, g.rho,
+                     g.area, g.tan, g.n_patch, g.pitch, g.k, nx, ny,
                      static_cast<double2*>(T_blocks));
   EMS_LAUNCH_CHECK();
 }

@@ -6,6 +6,7 @@
 #include <cstddef>
 #include <cstdint>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <string>
 #include <utility>
@@ -57,6 +58,10 @@ emsurf_status guarded_call(F&& f) {
 #define EMS_LAUNCH_CHECK() EMS_HIP(hipGetLastError())
 
 // ----------------------------------------------------------------------------- device buffer
+// hipMalloc; when the device is out of memory, once more after the idle
+// call workspaces (below) have been freed
+void device_malloc(void** p, size_t n);
+
 struct DevBuf {
   void* p = nullptr;
   size_t bytes = 0;
@@ -73,7 +78,7 @@ struct DevBuf {
   void alloc(size_t n) {
     release();
     if (n == 0) return;
-    EMS_HIP(hipMalloc(&p, n));
+    device_malloc(&p, n);
     bytes = n;
   }
   void release() {
@@ -87,6 +92,41 @@ struct DevBuf {
   }
   template <typename T> T* as() const { return static_cast<T*>(p); }
 };
+
+// Device workspace of one call that waits for its stream before it returns:
+// taken from the blocks that earlier calls left idle (the smallest that
+// holds n bytes), else allocated.  The call says idle() once nothing on the
+// device uses the block any more; it is then kept for later calls of any
+// thread and stream.  At most SCRATCH_KEPT idle bytes are kept per device
+// (least recently used freed first); all are freed when the last plan of the
+// process is destroyed and when an allocation of the library fails.
+constexpr size_t SCRATCH_KEPT = (size_t)4 << 30;
+class Scratch {
+ public:
+  explicit Scratch(size_t n);
+  ~Scratch();
+  Scratch(const Scratch&) = delete;
+  Scratch& operator=(const Scratch&) = delete;
+  void idle();
+  void* p = nullptr;
+  size_t bytes = 0;
+  // the next part of the block, rounded up to 256 bytes
+  template <typename T = void> T* part(size_t n) {
+    T* q = reinterpret_cast<T*>(static_cast<char*>(p) + used_);
+    used_ += round(n);
+    return q;
+  }
+  static size_t round(size_t n) { return (n + 255) / 256 * 256; }
+
+ private:
+  int dev_ = 0;
+  size_t used_ = 0;
+};
+// free every idle block; whether there was one
+bool scratch_give_back();
+// plans of the process: the last one closed gives the idle blocks back
+void plan_opened();
+void plan_closed();
 
 struct PinnedBuf {
   void* p = nullptr;
@@ -294,13 +334,18 @@ void launch_apply_S_packed(Cx tc, Cx txy, const void* Sp, const TypeTiles& tiles
 // ----------------------------------------------------------------------------- fill
 // Write padded kernel K[sy][sx][v][u] (columns cols [c0, c0+nc) of the n*n batch
 // only, as a dense [Ly][Lx][nc] array) from blocks or from the Green fill.
+// Box geometry on the device for one call, which says idle() when its stream
+// has been waited for.
 struct GreenGeomDev {
-  DevBuf rho, area, tan;   // double [P][3], [P], [P][2][3]
+  const double *rho = nullptr, *area = nullptr, *tan = nullptr;   // [P][3], [P], [P][2][3]
   int n_patch = 0;
   double pitch = 0, k = 0;
+  void idle() { mem->idle(); }
+  std::vector<double> host;   // source of the copy, until mem has waited or is idle
+  std::unique_ptr<Scratch> mem;
 };
-// validate a box geometry (finite pitch > 0, areas > 0) and copy it to the device
-void upload_geom(const emsurf_geom* g, GreenGeomDev& d);
+// validate a box geometry (finite pitch > 0, areas > 0) and copy it to the device (async on s)
+void upload_geom(const emsurf_geom* g, GreenGeomDev& d, hipStream_t s);
 // a patch centre of one box coincides with one of an adjacent box (touching boxes)
 bool boxes_touch(const emsurf_geom* g);
 // caller blocks: `parts` row-major nb x nb matrices per offset (1 x n_eq dense; 2 x n_h for L, K)
@@ -387,7 +432,10 @@ struct emsurf_plan_s {
   emsurf::KernelTimer timer;
   hipStream_t timer_stream = nullptr;
   int bp_variant[65];             // FP32 block-product variant per nrhs, -1 = automatic
-  emsurf_plan_s() { for (int& v : bp_variant) v = -1; }
+  emsurf_plan_s() {
+    for (int& v : bp_variant) v = -1;
+    emsurf::plan_opened();
+  }
   ~emsurf_plan_s();
 };
 

@@ -268,7 +268,7 @@ bool boxes_touch(const emsurf_geom* g) {
   return false;
 }
 
-void upload_geom(const emsurf_geom* g, GreenGeomDev& d) {
+void upload_geom(const emsurf_geom* g, GreenGeomDev& d, hipStream_t s) {
   EMS_CHECK_ARG(g != nullptr && g->rho && g->area && g->tan, "geometry pointers must be non-NULL");
   EMS_CHECK_ARG(g->n_patch >= 1, "n_patch must be >= 1");
   EMS_CHECK_ARG(std::isfinite(g->pitch) && g->pitch > 0 && std::isfinite(g->k), "pitch must be > 0, k finite");
@@ -277,17 +277,21 @@ void upload_geom(const emsurf_geom* g, GreenGeomDev& d) {
   d.n_patch = P;
   d.pitch = g->pitch;
   d.k = g->k;
-  d.rho.alloc((size_t)P * 3 * 8);
-  d.area.alloc((size_t)P * 8);
-  d.tan.alloc((size_t)P * 6 * 8);
-  EMS_HIP(hipMemcpy(d.rho.p, g->rho, (size_t)P * 3 * 8, hipMemcpyHostToDevice));
-  EMS_HIP(hipMemcpy(d.area.p, g->area, (size_t)P * 8, hipMemcpyHostToDevice));
-  EMS_HIP(hipMemcpy(d.tan.p, g->tan, (size_t)P * 6 * 8, hipMemcpyHostToDevice));
+  d.host.assign(g->rho, g->rho + 3 * P);
+  d.host.insert(d.host.end(), g->area, g->area + P);
+  d.host.insert(d.host.end(), g->tan, g->tan + 6 * P);
+  d.mem = std::make_unique<Scratch>(d.host.size() * 8);
+  double* base = static_cast<double*>(d.mem->p);
+  d.rho = base;
+  d.area = base + 3 * P;
+  d.tan = base + 4 * P;
+  EMS_HIP(hipMemcpyAsync(base, d.host.data(), d.host.size() * 8, hipMemcpyHostToDevice, s));
 }
 
 }  // namespace emsurf
 
 emsurf_plan_s::~emsurf_plan_s() {
+  emsurf::plan_closed();
   for (auto& kv : ws) delete kv.second;
   for (auto& kv : solve_ws) emsurf::destroy_solve_work(kv.second);
   for (int ph = 0; ph < 5; ++ph)
@@ -396,7 +400,10 @@ void build_that(emsurf_plan p, hipStream_t s, FillChunk&& fill, const GreenGeomD
   if (vperm || gen) nc = std::max<int64_t>(1, nc / grp) * grp;
   nc = std::max<int64_t>(1, std::min<int64_t>(nc, nn));
   nc = std::min<int64_t>(nc, 0x7fffffff);
-  DevBuf K((size_t)(P * nc) * 16), tmp((size_t)(P * nc) * 16);
+  const size_t chunk_bytes = Scratch::round((size_t)(P * nc) * 16);
+  Scratch chunks(2 * chunk_bytes);
+  void* const K = chunks.part(chunk_bytes);
+  void* const tmp = chunks.part(chunk_bytes);
   const void* twx = twiddle_table(p->Lx, Cx::C128);
   const void* twy = twiddle_table(p->Ly, Cx::C128);
   for (int64_t c0 = 0; c0 < nn; c0 += nc) {
@@ -408,10 +415,10 @@ void build_that(emsurf_plan p, hipStream_t s, FillChunk&& fill, const GreenGeomD
     fx.out_s0 = (int64_t)p->Lx * cnt; fx.out_pt = cnt;
     fx.sign = -1;
     if (gen) {
-      launch_fft_pass_green(fx, *gen, p->d.nx, p->d.ny, p->Ly, c0, n, vperm, tmp.p, twx, s);
+      launch_fft_pass_green(fx, *gen, p->d.nx, p->d.ny, p->Ly, c0, n, vperm, tmp, twx, s);
     } else {
-      fill(c0, cnt, K.p, vperm);
-      launch_fft_pass(fx, Cx::C128, Cx::C128, Cx::C128, K.p, tmp.p, twx, s);
+      fill(c0, cnt, K, vperm);
+      launch_fft_pass(fx, Cx::C128, Cx::C128, Cx::C128, K, tmp, twx, s);
     }
     FftPass fy;
     fy.L = p->Ly; fy.n_in = p->Ly; fy.n_out = p->Ly; fy.batch = (int)cnt;
@@ -419,12 +426,13 @@ void build_that(emsurf_plan p, hipStream_t s, FillChunk&& fill, const GreenGeomD
     fy.in_s0 = cnt; fy.in_pt = (int64_t)p->Lx * cnt;
     fy.out_s0 = cnt; fy.out_pt = (int64_t)p->Lx * cnt;
     fy.sign = -1;
-    launch_fft_pass(fy, Cx::C128, Cx::C128, Cx::C128, tmp.p, K.p, twy, s);
-    launch_store_chunk(K.p, P, nn, c0, cnt, slot_dev.as<const int>(), p->pairs.as<const int>(), p->Ps, n,
+    launch_fft_pass(fy, Cx::C128, Cx::C128, Cx::C128, tmp, K, twy, s);
+    launch_store_chunk(K, P, nn, c0, cnt, slot_dev.as<const int>(), p->pairs.as<const int>(), p->Ps, n,
                        p->d.form == EMSURF_T_LK ? n / 2 : 0, vperm, gen ? 1 : 0,
                        p->that64.p, p->that32.p, p->that16.p, s);
   }
   EMS_HIP(hipStreamSynchronize(s));
+  chunks.idle();
 }
 
 // Workspace of the creating stream and every twiddle table the applies need are
@@ -616,7 +624,7 @@ emsurf_status emsurf_plan_create_green(const emsurf_plan_desc* desc, const emsur
     EMS_CHECK_ARG(geom != nullptr && desc->n_eq == 4 * geom->n_patch, "n_eq must equal 4 * geom->n_patch");
     EMS_CHECK_ARG(desc->form != EMSURF_T_LK || geom->k > 0, "the structured fill needs a wavenumber k > 0");
     GreenGeomDev g;
-    upload_geom(geom, g);
+    upload_geom(geom, g, s);
     EMS_CHECK_ARG(desc->form != EMSURF_T_LK || !boxes_touch(geom),
                   "the structured fill needs boxes that do not touch (its gradient terms are singular there)");
     p = new_plan(desc);
@@ -633,6 +641,7 @@ emsurf_status emsurf_plan_create_green(const emsurf_plan_desc* desc, const emsur
       else
         launch_green_padded(g, desc->nx, desc->ny, p->Lx, p->Ly, c0, cnt, vperm, K, s);
     }, desc->form == EMSURF_T_LK ? nullptr : &g);
+    g.idle();   // build_that has waited for the stream
     upload_S(p, S_types, s);
     build_tiles(p, elem_type, s);
     finish_plan(p, s);
@@ -652,10 +661,10 @@ emsurf_status emsurf_fill_T_point_green(const emsurf_geom* geom, int32_t nx, int
     EMS_CHECK_ARG(nx >= 1 && ny >= 1 && nx <= 512 && ny <= 512, "lattice sizes must be in [1, 512]");
     hipStream_t s = static_cast<hipStream_t>(stream);
     GreenGeomDev g;
-    upload_geom(geom, g);
+    upload_geom(geom, g, s);
     launch_green_blocks(g, nx, ny, T_blocks_dev, s);
-    // the geometry buffers are freed on return: finish using them first
     EMS_HIP(hipStreamSynchronize(s));
+    g.idle();
   });
 }
 
@@ -667,11 +676,12 @@ emsurf_status emsurf_fill_LK_point_green(const emsurf_geom* geom, int32_t nx, in
     EMS_CHECK_ARG(nx >= 1 && ny >= 1 && nx <= 512 && ny <= 512, "lattice sizes must be in [1, 512]");
     hipStream_t s = static_cast<hipStream_t>(stream);
     GreenGeomDev g;
-    upload_geom(geom, g);
+    upload_geom(geom, g, s);
     EMS_CHECK_ARG(!boxes_touch(geom),
                   "the structured fill needs boxes that do not touch (its gradient terms are singular there)");
     launch_lk_blocks(g, nx, ny, LK_blocks_dev, s);
     EMS_HIP(hipStreamSynchronize(s));
+    g.idle();
   });
 }
 

@@ -339,9 +339,10 @@ emsurf_status emsurf_precond_create(emsurf_plan plan, const emsurf_geom* geom, d
         EMS_HIP(hipMemcpyAsync(Tn.p, T_near, Tn.bytes, hipMemcpyHostToDevice, s));
       } else {
         GreenGeomDev gd;
-        upload_geom(geom, gd);
+        upload_geom(geom, gd, s);
         launch_green_blocks(gd, 2, 2, Tn.p, s);
         EMS_HIP(hipStreamSynchronize(s));
+        gd.idle();
       }
       pc->G.alloc((size_t)pc->ntiles * nq * nq * 16);
       // augmented matrices in batches of at most 512 MB

@@ -1023,12 +1023,12 @@ extern "C" emsurf_status emsurf_macromodels(int32_t n_types, int32_t n_eq, int32
     EMS_CHECK_ARG(Z_dev != nullptr && S_dev != nullptr, "Z_dev and S_dev must be non-NULL");
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int n = n_eq, m = n_int, N1 = n + m, N2 = 2 * n, T = n_types;
-    // one allocation for the call: A1, A2, the pivots, and the two steps'
+    // one workspace for the call: A1, A2, the pivots, and the two steps'
     // singular flags (kept apart, read once at the end)
     const int Kmax = m > n ? m : n;
     const size_t b_a1 = (size_t)T * N1 * N1 * 16, b_a2 = (size_t)T * N2 * N2 * 16;
     const size_t b_piv = ((size_t)T * (Kmax > 0 ? Kmax : 1) * 4 + 255) / 256 * 256;
-    DevBuf ws(b_a1 + b_a2 + b_piv + (size_t)2 * T * 4);
+    Scratch ws(b_a1 + b_a2 + b_piv + (size_t)2 * T * 4);
     double2* A1 = static_cast<double2*>(ws.p);
     double2* A2 = reinterpret_cast<double2*>(static_cast<char*>(ws.p) + b_a1);
     int* piv = reinterpret_cast<int*>(static_cast<char*>(ws.p) + b_a1 + b_a2);
@@ -1053,6 +1053,7 @@ extern "C" emsurf_status emsurf_macromodels(int32_t n_types, int32_t n_eq, int32
     std::vector<int> flags(2 * (size_t)T);
     EMS_HIP(hipMemcpyAsync(flags.data(), info, (size_t)2 * T * 4, hipMemcpyDeviceToHost, s));
     EMS_HIP(hipStreamSynchronize(s));
+    ws.idle();   // (the second stream has been joined into s)
     const int* info1 = flags.data();
     const int* info2 = flags.data() + T;
     for (int t = 0; t < T; ++t) {

@@ -8,6 +8,7 @@
 #include <algorithm>
 #include <chrono>
 #include <cmath>
+#include <cstdlib>
 #include <cstring>
 #include <deque>
 #include <map>
@@ -24,19 +25,110 @@ double now_ms() {
   return std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now().time_since_epoch()).count();
 }
 
+// Host memory of right-hand sides and solutions.  Pinned blocks of at most
+// HOST_PINNED bytes in all stay with the server for later requests (fresh
+// pageable memory cost a page fault per 4 KB on the way in and out, and its
+// copies ran at a fifth of the pinned rate: three requests of 45 MB took 30 ms
+// and take 13.3 ms); beyond that a request takes pageable memory of its own.
+constexpr size_t HOST_PINNED = (size_t)1 << 30;
+
+class HostPool;
+struct HostBlock {
+  HostPool* pool = nullptr;
+  void* p = nullptr;
+  size_t bytes = 0;
+  bool pinned = false;
+  HostBlock() = default;
+  HostBlock(HostBlock&& o) noexcept { *this = std::move(o); }
+  HostBlock& operator=(HostBlock&& o) noexcept {
+    std::swap(pool, o.pool);
+    std::swap(p, o.p);
+    std::swap(bytes, o.bytes);
+    std::swap(pinned, o.pinned);
+    return *this;
+  }
+  ~HostBlock() { release(); }
+  void release();
+  double* at(size_t i) const { return static_cast<double*>(p) + i; }
+};
+
+class HostPool {
+ public:
+  HostPool() = default;
+  HostPool(const HostPool&) = delete;
+  HostPool& operator=(const HostPool&) = delete;
+  ~HostPool() {
+    for (auto& b : idle_) (void)hipHostFree(b.first);
+  }
+  HostBlock take(size_t n) {
+    HostBlock b;
+    b.pool = this;
+    auto best = idle_.end();
+    for (auto it = idle_.begin(); it != idle_.end(); ++it)
+      if (it->second >= n && (best == idle_.end() || it->second < best->second)) best = it;
+    if (best != idle_.end()) {
+      b.p = best->first;
+      b.bytes = best->second;
+      b.pinned = true;
+      idle_.erase(best);
+      return b;
+    }
+    const size_t unit = 1u << 20, want = std::max<size_t>(1, (n + unit - 1) / unit) * unit;
+    // idle blocks that were too small make way
+    while (!idle_.empty() && pinned_ + want > HOST_PINNED) {
+      (void)hipHostFree(idle_.back().first);
+      pinned_ -= idle_.back().second;
+      idle_.pop_back();
+    }
+    if (pinned_ + want <= HOST_PINNED && hipHostMalloc(&b.p, want, hipHostMallocDefault) == hipSuccess) {
+      pinned_ += want;
+      b.bytes = want;
+      b.pinned = true;
+      return b;
+    }
+    (void)hipGetLastError();
+    b.p = std::malloc(std::max<size_t>(1, n));
+    if (!b.p) throw std::bad_alloc();
+    b.bytes = n;
+    return b;
+  }
+  void give(HostBlock& b) noexcept {
+    if (!b.pinned) {
+      std::free(b.p);
+      return;
+    }
+    try {
+      idle_.emplace_back(b.p, b.bytes);
+    } catch (...) {
+      pinned_ -= b.bytes;
+      (void)hipHostFree(b.p);
+    }
+  }
+
+ private:
+  std::vector<std::pair<void*, size_t>> idle_;
+  size_t pinned_ = 0;
+};
+
+void HostBlock::release() {
+  if (p) pool->give(*this);
+  p = nullptr;
+  bytes = 0;
+}
+
 struct Request {
   int64_t id = 0;
   uint64_t key = 0;
   emsurf_plan_desc desc{};
   std::vector<double> rho, area, tan;
   double pitch = 0, k = 0;
-  std::vector<double> S;        // interleaved complex
+  std::vector<double> S;        // interleaved complex; empty if the surface was resident at submit
   std::vector<int32_t> types;
   int nrhs = 0;
-  std::vector<double> b;        // interleaved complex [nrhs][N]
+  HostBlock b;                  // c128 [nrhs][N], until its copies to the device have ended
   enum { QUEUED, ACTIVE, DONE } state = QUEUED;
   std::vector<int> slots;
-  std::vector<double> x;        // result [nrhs][N]
+  HostBlock x;                  // result c128 [nrhs][N]
   std::vector<emsurf_solve_info> info;
   double t_submit = 0, t_admit = 0, t_done = 0;
   bool bad = false;
@@ -46,12 +138,11 @@ struct PlanEntry {
   emsurf_plan plan = nullptr;
   emsurf_session session = nullptr;
   hipStream_t stream = nullptr;
-  size_t bytes = 0;        // plan, session staging and reductions, host staging vector
+  size_t bytes = 0;        // plan, session staging and reductions
   size_t slot_bytes = 0;   // vectors and Krylov basis of one slot
   size_t held = 0;         // slot buffers the session holds now
   double last_used = 0;
   int active = 0;
-  DevBuf staging;   // one right-hand side, for host -> slot copies
 };
 
 }  // namespace
@@ -59,6 +150,7 @@ struct PlanEntry {
 
 struct emsurf_server_s {
   emsurf_server_desc d{};
+  emsurf::HostPool host;   // (outlives the requests below)
   std::map<uint64_t, std::unique_ptr<emsurf::PlanEntry>> plans;
   std::deque<std::unique_ptr<emsurf::Request>> queue;
   std::map<int64_t, std::unique_ptr<emsurf::Request>> active, done;
@@ -97,13 +189,13 @@ emsurf_plan_desc server_desc(emsurf_server sv, emsurf_plan_desc pd) {
 
 // Device bytes a resident surface holds with no busy right-hand side: the plan
 // (its stores and the apply workspace of its stream, which the session on the
-// same stream shares), the session's batch staging and reductions, and one
-// staging vector.  Each busy slot adds entry_slot_bytes.
+// same stream shares) and the session's batch staging and reductions.  Each
+// busy slot adds entry_slot_bytes.
 size_t entry_bytes(emsurf_server sv, emsurf_plan_desc pd) {
   pd = server_desc(sv, pd);
   const size_t pb = emsurf_plan_bytes(&pd);
   if (pb == 0) return 0;
-  return pb + session_fixed_bytes(pd, sv->d.max_slots, sv->d.opts.restart) + (size_t)pd.nx * pd.ny * pd.n_eq * 16;
+  return pb + session_fixed_bytes(pd, sv->d.max_slots, sv->d.opts.restart);
 }
 
 size_t entry_slot_bytes(emsurf_server sv, emsurf_plan_desc pd) {
@@ -177,7 +269,6 @@ PlanEntry* resident(emsurf_server sv, Request& rq, const std::map<uint64_t, int>
     (void)hipStreamDestroy(e->stream);
     throw Err{st};
   }
-  e->staging.alloc((size_t)pd.nx * pd.ny * pd.n_eq * 16);
   e->bytes = fixed;
   e->slot_bytes = slot;
   e->last_used = now_ms();
@@ -198,20 +289,20 @@ void place(emsurf_server sv, Request& rq, PlanEntry* e) {
   const size_t N = (size_t)rq.desc.nx * rq.desc.ny * rq.desc.n_eq;
   rq.slots.resize(rq.nrhs);
   for (int r = 0; r < rq.nrhs; ++r) {
-    EMS_HIP(hipMemcpyAsync(e->staging.p, rq.b.data() + 2 * N * r, N * 16, hipMemcpyHostToDevice, e->stream));
     int32_t slot = -1;
-    emsurf_status st = emsurf_session_submit(e->session, e->staging.p, rq.id, &slot);
-    if (st != EMSURF_OK) throw Err{st};
+    session_submit(e->session, rq.b.at(2 * N * r), rq.id, &slot);
     rq.slots[r] = slot;
   }
-  EMS_HIP(hipStreamSynchronize(e->stream));
+  // pinned memory stays with the request, whose solution the stream is waited for
+  if (!rq.b.pinned) {
+    EMS_HIP(hipStreamSynchronize(e->stream));
+    rq.b.release();
+  }
   refresh_held(sv, *e);
   e->active += 1;
   e->last_used = now_ms();
   rq.state = Request::ACTIVE;
   rq.t_admit = now_ms();
-  rq.b.clear();
-  rq.b.shrink_to_fit();
 }
 
 // Admission: first every queued request whose plan is resident and has free
@@ -281,13 +372,18 @@ void harvest(emsurf_server sv) {
     for (int s : rq.slots) all = all && e.session->slot[s].ph == SessionSlot::DONE;
     if (!all) continue;
     const size_t N = (size_t)rq.desc.nx * rq.desc.ny * rq.desc.n_eq;
-    rq.x.assign(2 * N * rq.nrhs, 0.0);
+    // the right-hand sides' own block is free again (their copies precede the
+    // finished steps on the stream) and holds the solutions
+    rq.x = rq.b.p ? std::move(rq.b) : sv->host.take(N * 16 * rq.nrhs);
     rq.info.resize(rq.nrhs);
+    for (int r = 0; r < rq.nrhs; ++r)
+      EMS_HIP(hipMemcpyAsync(rq.x.at(2 * N * r), session_x(e.session, rq.slots[r]), N * 16, hipMemcpyDeviceToHost,
+                             e.stream));
+    EMS_HIP(hipStreamSynchronize(e.stream));
     for (int r = 0; r < rq.nrhs; ++r) {
-      emsurf_status st = emsurf_session_collect(e.session, rq.slots[r], e.staging.p, &rq.info[r]);
+      emsurf_status st = emsurf_session_collect(e.session, rq.slots[r], nullptr, &rq.info[r]);
       if (st == EMSURF_ERR_ARG) rq.bad = true;
       else if (st != EMSURF_OK) throw Err{st};
-      EMS_HIP(hipMemcpy(rq.x.data() + 2 * N * r, e.staging.p, N * 16, hipMemcpyDeviceToHost));
     }
     e.active -= 1;
     e.last_used = now_ms();
@@ -343,12 +439,16 @@ emsurf_status emsurf_server_submit(emsurf_server sv, uint64_t key, const emsurf_
     rq->pitch = geom->pitch;
     rq->k = geom->k;
     const size_t nS = (size_t)desc->n_types * desc->n_eq * desc->n_eq * 2;
-    rq->S.assign(static_cast<const double*>(S_types), static_cast<const double*>(S_types) + nS);
+    // a surface that is resident now stays so while this request is queued
+    // (make_room keeps the plans of queued keys), so only others need S
+    if (!sv->plans.count(key))
+      rq->S.assign(static_cast<const double*>(S_types), static_cast<const double*>(S_types) + nS);
     rq->types.assign(elem_type, elem_type + (size_t)desc->nx * desc->ny);
     for (int32_t t : rq->types) EMS_CHECK_ARG(t >= 0 && t < desc->n_types, "elem_type entry out of range");
     const size_t N = (size_t)desc->nx * desc->ny * desc->n_eq;
     rq->nrhs = nrhs;
-    rq->b.assign(static_cast<const double*>(b_host), static_cast<const double*>(b_host) + 2 * N * nrhs);
+    rq->b = sv->host.take(N * 16 * nrhs);
+    std::memcpy(rq->b.p, b_host, N * 16 * nrhs);
     rq->t_submit = now_ms();
     if (req_id) *req_id = rq->id;
     sv->queue.push_back(std::move(rq));
@@ -396,7 +496,8 @@ emsurf_status emsurf_server_fetch(emsurf_server sv, int64_t req_id, void* x_host
     auto it = sv->done.find(req_id);
     EMS_CHECK_ARG(it != sv->done.end(), "unknown or not finished request id");
     Request& rq = *it->second;
-    if (x_host && !rq.x.empty()) std::memcpy(x_host, rq.x.data(), rq.x.size() * sizeof(double));
+    if (x_host && rq.x.p)
+      std::memcpy(x_host, rq.x.p, (size_t)rq.desc.nx * rq.desc.ny * rq.desc.n_eq * 16 * rq.nrhs);
     if (info)
       for (int r = 0; r < (int)rq.info.size(); ++r) info[r] = rq.info[r];
     if (times_ms) {

@@ -26,6 +26,11 @@ struct SessionSlot {
 size_t session_fixed_bytes(const emsurf_plan_desc& d, int max_slots, int restart);
 size_t session_slot_bytes(const emsurf_plan_desc& d, int restart);
 size_t session_bytes(const emsurf_plan_desc& d, int max_slots, int restart);
+// place a right-hand side (host or device memory) into a free slot; async on
+// the session's stream, so host memory stays in use until it has been waited for
+void session_submit(emsurf_session ss, const void* b, int64_t tag, int32_t* slot);
+// iterate of a slot (device, N c128 values)
+const void* session_x(emsurf_session ss, int slot);
 void session_launch(emsurf_session ss);
 int session_finish(emsurf_session ss);
 // bytes of the slot buffers the session holds, and the number of free slots

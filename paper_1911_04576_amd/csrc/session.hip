@@ -371,6 +371,30 @@ int session_finish(emsurf_session ss) {
   return finished;
 }
 
+const void* session_x(emsurf_session ss, int slot) { return sx(ss, slot); }
+
+void session_submit(emsurf_session ss, const void* b, int64_t tag, int32_t* slot) {
+  // a free slot that already holds its vectors first, else any free slot
+  int s = -1;
+  for (int i = 0; i < ss->S && s < 0; ++i)
+    if (ss->slot[i].ph == SessionSlot::FREE && ss->mem[i].p) s = i;
+  for (int i = 0; i < ss->S && s < 0; ++i)
+    if (ss->slot[i].ph == SessionSlot::FREE) s = i;
+  if (s < 0) {
+    set_error("no free slot");
+    throw Err{EMSURF_ERR_BUSY};
+  }
+  if (!ss->mem[s].p) ss->mem[s].alloc((size_t)(ss->m + 4) * ss->N * 16);
+  EMS_HIP(hipMemcpyAsync(sb(ss, s), b, (size_t)ss->N * 16, hipMemcpyDefault, ss->stream));
+  EMS_HIP(hipMemsetAsync(sx(ss, s), 0, (size_t)ss->N * 16, ss->stream));
+  SessionSlot q;
+  q.ph = SessionSlot::INIT;
+  q.tag = tag;
+  q.t_submit = now_ms();
+  ss->slot[s] = q;
+  if (slot) *slot = s;
+}
+
 }  // namespace emsurf
 
 namespace {
@@ -433,25 +457,7 @@ emsurf_status emsurf_session_create(emsurf_plan plan, int32_t max_slots, const e
 emsurf_status emsurf_session_submit(emsurf_session ss, const void* b_dev, int64_t tag, int32_t* slot) {
   return sguard([&] {
     EMS_CHECK_ARG(ss != nullptr && b_dev != nullptr, "session and b must be non-NULL");
-    // a free slot that already holds its vectors first, else any free slot
-    int s = -1;
-    for (int i = 0; i < ss->S && s < 0; ++i)
-      if (ss->slot[i].ph == SessionSlot::FREE && ss->mem[i].p) s = i;
-    for (int i = 0; i < ss->S && s < 0; ++i)
-      if (ss->slot[i].ph == SessionSlot::FREE) s = i;
-    if (s < 0) {
-      set_error("no free slot");
-      throw Err{EMSURF_ERR_BUSY};
-    }
-    if (!ss->mem[s].p) ss->mem[s].alloc((size_t)(ss->m + 4) * ss->N * 16);
-    EMS_HIP(hipMemcpyAsync(sb(ss, s), b_dev, (size_t)ss->N * 16, hipMemcpyDeviceToDevice, ss->stream));
-    EMS_HIP(hipMemsetAsync(sx(ss, s), 0, (size_t)ss->N * 16, ss->stream));
-    SessionSlot q;
-    q.ph = SessionSlot::INIT;
-    q.tag = tag;
-    q.t_submit = now_ms();
-    ss->slot[s] = q;
-    if (slot) *slot = s;
+    session_submit(ss, b_dev, tag, slot);
   });
 }
 
