@@ -50,10 +50,11 @@ struct emsurf_session_s {
   hipStream_t stream = nullptr;
   bool own_stream = false;
   hipEvent_t ev = nullptr;
-  emsurf::DevBuf xin, wout, partial, red, coef, items;
+  emsurf::DevBuf xin, wout, partial, coef;
   std::vector<emsurf::DevBuf> mem;   // per slot: [b | x | r | V_0 .. V_m] (N values each), or empty
-  emsurf::PinnedBuf h_red, h_coef, h_items;
-  int nblk = 0, ns = 0, rstride = 0, variant32 = 0;
+  emsurf::PinnedBuf h_red;    // a row per busy slot, written by the device
+  emsurf::PinnedBuf h_coef;
+  int rstride = 0, variant32 = 0;
   bool launched = false;
   std::vector<emsurf::SessionSlot> slot;
   std::vector<int> q_norm, q_arn;

@@ -62,11 +62,9 @@ namespace emsurf {
 size_t session_fixed_bytes(const emsurf_plan_desc& d, int max_slots, int restart) {
   const size_t N = (size_t)d.nx * d.ny * d.n_eq;
   const size_t staging = 2 * (size_t)max_slots * N * 16;   // gathered operands, apply outputs
-  const int nblk = dot_blocks((long long)N);
-  const size_t red = (size_t)max_slots * (2 * (restart + 2) + 8) * 16 * 2;
-  const size_t partial = (size_t)max_slots * nblk * (restart + 2) * 16;
+  const size_t partial = vec_partial_bytes(max_slots, restart, (long long)N);
   const size_t coef = (size_t)max_slots * restart * 16;
-  return staging + red + partial + coef + (size_t)16 * max_slots * sizeof(VecItem);
+  return staging + partial + coef;
 }
 
 size_t session_slot_bytes(const emsurf_plan_desc& d, int restart) {
@@ -120,16 +118,11 @@ void session_init(emsurf_session ss, emsurf_plan plan, int max_slots, const emsu
   ss->mem.resize(ss->S);
   ss->xin.alloc(vb * ss->S);
   ss->wout.alloc(vb * ss->S);
-  ss->nblk = dot_blocks(ss->N);
-  ss->ns = ss->m + 2;
   ss->rstride = 2 * (ss->m + 2) + 8;
-  ss->partial.alloc((size_t)ss->S * ss->nblk * ss->ns * 16);
-  ss->red.alloc((size_t)2 * ss->S * ss->rstride * 16);
-  ss->h_red.alloc(ss->red.bytes);
+  ss->partial.alloc(vec_partial_bytes(ss->S, ss->m, ss->N));
+  ss->h_red.alloc((size_t)ss->S * ss->rstride * 16);
   ss->coef.alloc((size_t)ss->S * ss->m * 16);
   ss->h_coef.alloc(ss->coef.bytes);
-  ss->items.alloc((size_t)16 * ss->S * sizeof(VecItem));
-  ss->h_items.alloc(ss->items.bytes);
   ss->slot.assign(ss->S, SessionSlot{});
   EMS_HIP(hipEventCreateWithFlags(&ss->ev, hipEventDisableTiming));
   // the FP32 product variant is fixed for the session's lifetime
@@ -139,16 +132,6 @@ void session_init(emsurf_session ss, emsurf_plan plan, int max_slots, const emsu
 }
 
 namespace {
-
-// List regions in the item buffers: launch lists 0..7, finish lists 8..15
-VecItem* hitem(emsurf_session ss, int list) { return ss->h_items.as<VecItem>() + (size_t)list * ss->S; }
-const VecItem* ditem(emsurf_session ss, int list) { return ss->items.as<VecItem>() + (size_t)list * ss->S; }
-
-void push_items(emsurf_session ss, int list, int count) {
-  if (count <= 0) return;
-  EMS_HIP(hipMemcpyAsync(const_cast<VecItem*>(ditem(ss, list)), hitem(ss, list), (size_t)count * sizeof(VecItem),
-                         hipMemcpyHostToDevice, ss->stream));
-}
 
 double2* vec(const DevBuf& buf, long long N, int s) { return buf.as<double2>() + (size_t)s * N; }
 // vectors of slot s: right-hand side, iterate, residual, Krylov basis
@@ -160,28 +143,21 @@ double2* basis(emsurf_session ss, int s, int l) { return ss->mem[s].as<double2>(
 Cx arnoldi_type(const emsurf_solve_opts& o) { return o.prec == EMSURF_FP64 ? Cx::C128 : Cx::C64; }
 Cx resid_type(const emsurf_solve_opts& o) { return o.prec == EMSURF_FP32 ? Cx::C64 : Cx::C128; }
 
-// one batched operator apply over `group` (slot, kind) entries; kind 0: residual
-// r = b - A x, kind 1: Arnoldi w = A v_j
-void batched_apply(emsurf_session ss, const std::vector<std::pair<int, int>>& group, Cx tc, int list_g, int list_s) {
+// One batched operator apply over `group` (slot, kind) entries into outputs
+// first, first + 1, .. of wout.  kind 0: A x for the residual, kind 1: A v_j.
+void batched_apply(emsurf_session ss, const std::vector<std::pair<int, int>>& group, Cx tc, int first) {
   const int nq = (int)group.size();
   if (nq == 0) return;
   const long long N = ss->N;
-  VecItem* g = hitem(ss, list_g);
-  VecItem* sc = hitem(ss, list_s);
+  std::vector<VecItem> g(nq);
   for (int q = 0; q < nq; ++q) {
     const int s = group[q].first;
-    const bool res = group[q].second == 0;
-    g[q] = VecItem{res ? (const void*)sx(ss, s) : (const void*)basis(ss, s, ss->slot[s].j), nullptr,
-                   vec(ss->xin, N, q), 1.0, 0, 0};
-    sc[q] = res ? VecItem{vec(ss->wout, N, q), sb(ss, s), sr(ss, s), 1.0, 0, 0}
-                : VecItem{vec(ss->wout, N, q), nullptr, basis(ss, s, ss->slot[s].j + 1), 1.0, 0, 0};
+    g[q].src = group[q].second == 0 ? sx(ss, s) : basis(ss, s, ss->slot[s].j);
+    g[q].dst = vec(ss->xin, N, q);
   }
-  push_items(ss, list_g, nq);
-  push_items(ss, list_s, nq);
-  launch_copy_list(ditem(ss, list_g), nq, N, ss->stream);
-  apply_A_typed(ss->plan, Cx::C128, tc, Cx::C128, nq, ss->xin.p, ss->wout.p, ss->stream,
+  launch_scaled_copies(g, N, ss->stream);
+  apply_A_typed(ss->plan, Cx::C128, tc, Cx::C128, nq, ss->xin.p, vec(ss->wout, N, first), ss->stream,
                 tc == Cx::C64 ? ss->variant32 : -1);
-  launch_copy_list(ditem(ss, list_s), nq, N, ss->stream);
 }
 
 }  // namespace
@@ -205,61 +181,46 @@ void session_launch(emsurf_session ss) {
   }
   ss->launched = !(init.empty() && g64.empty() && g32.empty());
   if (!ss->launched) return;
-  // r = b for new slots (x = 0)
-  if (!init.empty()) {
-    VecItem* it = hitem(ss, 0);
-    for (size_t i = 0; i < init.size(); ++i)
-      it[i] = VecItem{sb(ss, init[i]), nullptr, sr(ss, init[i]), 1.0, 0, 0};
-    push_items(ss, 0, (int)init.size());
-    launch_copy_list(ditem(ss, 0), (int)init.size(), N, ss->stream);
-  }
-  batched_apply(ss, g64, Cx::C128, 1, 2);
-  batched_apply(ss, g32, Cx::C64, 3, 4);
-  // residual norms: INIT and RESID slots
-  for (int s : init) ss->q_norm.push_back(s);
-  for (auto& e : g64) if (e.second == 0) ss->q_norm.push_back(e.first);
-  for (auto& e : g32) if (e.second == 0) ss->q_norm.push_back(e.first);
-  for (auto& e : g64) if (e.second == 1) ss->q_arn.push_back(e.first);
-  for (auto& e : g32) if (e.second == 1) ss->q_arn.push_back(e.first);
-  const int nn = (int)ss->q_norm.size(), na = (int)ss->q_arn.size();
-  double2* red = ss->red.as<double2>();
-  if (nn > 0) {
-    VecItem* it = hitem(ss, 5);
-    for (int i = 0; i < nn; ++i) it[i] = VecItem{nullptr, nullptr, sr(ss, ss->q_norm[i]), 1.0, 0, 0};
-    push_items(ss, 5, nn);
-    launch_dot_list(ditem(ss, 5), nn, 1, N, ss->partial.p, ss->nblk, red, ss->rstride, 0, ss->stream);
-  }
-  if (na > 0) {
-    // CGS2 per slot; rows of the reduction buffer after the norm rows
-    VecItem* it = hitem(ss, 6);
-    int nvmax = 0;
-    for (int i = 0; i < na; ++i) {
-      const int s = ss->q_arn[i];
-      const int nv = ss->slot[s].j + 1;
-      nvmax = std::max(nvmax, nv);
-      it[i] = VecItem{basis(ss, s, 0), nullptr, basis(ss, s, nv), 1.0, nv, 0};
+  batched_apply(ss, g64, Cx::C128, 0);
+  batched_apply(ss, g32, Cx::C64, (int)g64.size());
+  // rows of h_red: the norms of new right-hand sides (x = 0), the residuals,
+  // then the Arnoldi steps, read straight from the operator's outputs
+  const size_t rs = (size_t)ss->rstride;
+  double2* rows = ss->h_red.as<double2>();
+  std::vector<VecItem> news(init.size()), res, arn;
+  for (size_t i = 0; i < init.size(); ++i) news[i].src = sb(ss, init[i]);
+  ss->q_norm = init;
+  int out = 0, nvmax = 0;
+  for (auto* g : {&g64, &g32})
+    for (auto& e : *g) {
+      const int s = e.first;
+      VecItem it;
+      it.src = vec(ss->wout, N, out++);
+      if (e.second == 0) {
+        it.b = sb(ss, s);
+        it.dst = sr(ss, s);
+        res.push_back(it);
+        ss->q_norm.push_back(s);
+      } else {
+        it.nv = ss->slot[s].j + 1;
+        it.V = basis(ss, s, 0);
+        it.vstride = N;
+        it.dst = basis(ss, s, it.nv);
+        nvmax = std::max(nvmax, it.nv);
+        arn.push_back(it);
+        ss->q_arn.push_back(s);
+      }
     }
-    push_items(ss, 6, na);
-    double2* ra = red + (size_t)nn * ss->rstride;
-    const int ns = nvmax + 1;
-    const int o1 = 0, o2 = ss->m + 2, o3 = 2 * (ss->m + 2);
-    launch_dot_list(ditem(ss, 6), na, ns, N, ss->partial.p, ss->nblk, ra, ss->rstride, o1, ss->stream);
-    launch_update_list(ditem(ss, 6), na, N, ra, ss->rstride, o1, ss->stream);
-    launch_dot_list(ditem(ss, 6), na, ns, N, ss->partial.p, ss->nblk, ra, ss->rstride, o2, ss->stream);
-    launch_update_list(ditem(ss, 6), na, N, ra, ss->rstride, o2, ss->stream);
-    // final norm: items with nv = 0 on the same w
-    VecItem* it2 = hitem(ss, 7);
-    for (int i = 0; i < na; ++i) it2[i] = VecItem{nullptr, nullptr, it[i].dst, 1.0, 0, 0};
-    push_items(ss, 7, na);
-    launch_dot_list(ditem(ss, 7), na, 1, N, ss->partial.p, ss->nblk, ra, ss->rstride, o3, ss->stream);
-  }
-  EMS_HIP(hipMemcpyAsync(ss->h_red.p, ss->red.p, (size_t)(nn + na) * ss->rstride * 16, hipMemcpyDeviceToHost,
-                         ss->stream));
+  launch_norms(news, N, ss->partial.p, rows, ss->rstride, ss->stream);
+  launch_residuals(res, N, ss->partial.p, rows + news.size() * rs, ss->rstride, ss->stream);
+  // (the coefficients' places depend on the restart length alone)
+  launch_arnoldi(arn, N, nvmax, ss->partial.p, rows + (news.size() + res.size()) * rs,
+                 ArnoldiRow{0, ss->m + 2, 2 * (ss->m + 2), ss->rstride}, ss->stream);
   EMS_HIP(hipEventRecord(ss->ev, ss->stream));
 }
 
-// Wait for the step, update every slot on the host and launch the basis
-// scalings and solution updates.  Returns the number of slots that finished.
+// Wait for the step, update every slot on the host and launch the starts of
+// cycles and the solution updates.  Returns the number of slots that finished.
 int session_finish(emsurf_session ss) {
   if (!ss->launched) return 0;
   EMS_HIP(hipEventSynchronize(ss->ev));
@@ -268,9 +229,8 @@ int session_finish(emsurf_session ss) {
   const emsurf_solve_opts& o = ss->opts;
   const double2* hr = ss->h_red.as<double2>();
   const int nn = (int)ss->q_norm.size(), na = (int)ss->q_arn.size();
-  VecItem* scl = hitem(ss, 8);
-  VecItem* axp = hitem(ss, 9);
-  int nscl = 0, naxp = 0, finished = 0;
+  std::vector<VecItem> scl, axp;
+  int finished = 0;
   cd* hy = reinterpret_cast<cd*>(ss->h_coef.p);
   auto end_cycle = [&](int s) {
     SessionSlot& q = ss->slot[s];
@@ -281,8 +241,13 @@ int session_finish(emsurf_session ss) {
       for (int l = i + 1; l < k; ++l) acc -= q.H[(size_t)l * (m + 1) + i] * y[l];
       y[i] = acc / q.H[(size_t)i * (m + 1) + i];
     }
-    axp[naxp++] = VecItem{basis(ss, s, 0), reinterpret_cast<const double2*>(ss->coef.p) + (size_t)s * m,
-                          sx(ss, s), 1.0, k, 0};
+    VecItem it;
+    it.V = basis(ss, s, 0);
+    it.vstride = N;
+    it.nv = k;
+    it.b = ss->coef.as<double2>() + (size_t)s * m;
+    it.dst = sx(ss, s);
+    axp.push_back(it);
     q.cycles += 1;
     q.ph = SessionSlot::RESID;
   };
@@ -291,6 +256,7 @@ int session_finish(emsurf_session ss) {
     const int s = ss->q_norm[i];
     SessionSlot& q = ss->slot[s];
     const double beta = std::sqrt(hr[(size_t)i * ss->rstride].x);
+    const double2* start = q.ph == SessionSlot::INIT ? sb(ss, s) : sr(ss, s);
     if (q.ph == SessionSlot::INIT) {
       q.bnorm = beta;
       if (!std::isfinite(beta)) {
@@ -322,7 +288,11 @@ int session_finish(emsurf_session ss) {
     q.sn.assign(m, cd(0));
     q.g.assign(m + 1, cd(0));
     q.g[0] = beta;
-    scl[nscl++] = VecItem{sr(ss, s), nullptr, basis(ss, s, 0), 1.0 / beta, 0, 0};
+    VecItem it;
+    it.src = start;
+    it.dst = basis(ss, s, 0);
+    it.scale = 1.0 / beta;
+    scl.push_back(it);
   }
   // Arnoldi results
   const double2* ha = hr + (size_t)nn * ss->rstride;
@@ -354,19 +324,14 @@ int session_finish(emsurf_session ss) {
       q.kend = j + 1;
       end_cycle(s);
     } else {
-      scl[nscl++] = VecItem{basis(ss, s, j + 1), nullptr, basis(ss, s, j + 1), 1.0 / hn, 0, 0};
       q.j = j + 1;
     }
   }
-  if (naxp > 0) {
+  if (!axp.empty()) {
     EMS_HIP(hipMemcpyAsync(ss->coef.p, ss->h_coef.p, ss->coef.bytes, hipMemcpyHostToDevice, ss->stream));
-    push_items(ss, 9, naxp);
-    launch_axpy_list(ditem(ss, 9), naxp, N, ss->stream);
+    launch_solutions(axp, N, ss->stream);
   }
-  if (nscl > 0) {
-    push_items(ss, 8, nscl);
-    launch_copy_list(ditem(ss, 8), nscl, N, ss->stream);
-  }
+  launch_scaled_copies(scl, N, ss->stream);
   ss->launched = false;
   return finished;
 }

@@ -35,35 +35,27 @@ using cd = std::complex<double>;
 struct SolveWork {
   int nrhs = 0, m = 0;
   long long N = 0;
-  int nblk = 0, rstride = 0;
+  int rstride = 0;
   DevBuf V;        // (m+1) x nrhs x N
   DevBuf r, t;     // nrhs x N
-  DevBuf partial;  // nrhs x nblk x (m+2)
-  DevBuf red;      // nrhs x rstride
-  DevBuf scale;    // nrhs doubles
+  DevBuf partial;  // partial sums of the reductions
   DevBuf ycoef;    // nrhs x m complex
-  DevBuf mask;     // nrhs ints
   DevBuf ir_r, ir_d, ir_t;  // refinement residual, correction, operator output: nrhs x N each
   DevBuf pz, pz2;           // right preconditioning: P^-1 v and P^-1 V y, nrhs x N each
-  PinnedBuf h_red, h_scale, h_y, h_mask;
+  PinnedBuf h_red;          // nrhs x rstride, written by the device
+  PinnedBuf h_y;
   void init(int nrhs_, int m_, long long N_) {
     nrhs = nrhs_;
     m = m_;
     N = N_;
-    nblk = dot_blocks(N);
     rstride = 2 * (m + 2) + 4;
     V.reserve((size_t)(m + 1) * nrhs * N * 16);
     r.reserve((size_t)nrhs * N * 16);
     t.reserve((size_t)nrhs * N * 16);
-    partial.reserve((size_t)nrhs * nblk * (m + 2) * 16);
-    red.reserve((size_t)nrhs * rstride * 16);
-    scale.reserve((size_t)nrhs * 8);
+    partial.reserve(vec_partial_bytes(nrhs, m, N));
     ycoef.reserve((size_t)nrhs * m * 16);
-    mask.reserve((size_t)nrhs * 4);
     h_red.reserve((size_t)nrhs * rstride * 16);
-    h_scale.reserve((size_t)nrhs * 8);
     h_y.reserve((size_t)nrhs * m * 16);
-    h_mask.reserve((size_t)nrhs * 4);
   }
   double2* Vp(int l) const { return V.as<double2>() + (size_t)l * nrhs * N; }
   void init_refinement() {
@@ -76,8 +68,7 @@ struct SolveWork {
     pz2.reserve((size_t)nrhs * N * 16);
   }
   size_t bytes() const {
-    return V.bytes + r.bytes + t.bytes + partial.bytes + red.bytes + scale.bytes + ycoef.bytes + mask.bytes +
-           ir_r.bytes + ir_d.bytes + ir_t.bytes + pz.bytes + pz2.bytes;
+    return V.bytes + r.bytes + t.bytes + partial.bytes + ycoef.bytes + ir_r.bytes + ir_d.bytes + ir_t.bytes + pz.bytes + pz2.bytes;
   }
 };
 
@@ -95,14 +86,55 @@ void op_fp32(emsurf_plan p, int nrhs, const void* x, void* y, hipStream_t s) {
   apply_A_typed(p, Cx::C128, Cx::C64, Cx::C128, nrhs, x, y, s);
 }
 
-// per-RHS norms of vec ([nrhs][N]) into host array
-void norms(SolveWork& w, const void* vec, std::vector<double>& out, hipStream_t s) {
-  launch_dot(nullptr, 0, 0, vec, w.N, w.nrhs, w.partial.p, w.nblk, w.red.p, w.rstride, 0, s);
-  EMS_HIP(hipMemcpyAsync(w.h_red.p, w.red.p, (size_t)w.nrhs * w.rstride * 16, hipMemcpyDeviceToHost, s));
+// right-hand side r of a batch of vectors
+const double2* row(const void* v, const SolveWork& w, int r) { return static_cast<const double2*>(v) + (size_t)r * w.N; }
+double2* row(void* v, const SolveWork& w, int r) { return static_cast<double2*>(v) + (size_t)r * w.N; }
+
+// wait for the rows of h_red; their first values are squared norms
+std::vector<double> fetch_norms(const SolveWork& w, hipStream_t s) {
   EMS_HIP(hipStreamSynchronize(s));
-  const double2* h = w.h_red.as<double2>();
-  out.resize(w.nrhs);
-  for (int r = 0; r < w.nrhs; ++r) out[r] = std::sqrt(h[(size_t)r * w.rstride].x);
+  std::vector<double> out(w.nrhs);
+  for (int r = 0; r < w.nrhs; ++r) out[r] = std::sqrt(w.h_red.as<double2>()[(size_t)r * w.rstride].x);
+  return out;
+}
+
+// res = b - ax where on(r) (else 0); returns the norms
+template <typename On>
+std::vector<double> residual(SolveWork& w, const void* b, const void* ax, On&& on, void* res, hipStream_t s) {
+  std::vector<VecItem> it(w.nrhs);
+  for (int r = 0; r < w.nrhs; ++r) {
+    it[r].b = row(b, w, r);
+    it[r].src = row(ax, w, r);
+    it[r].dst = row(res, w, r);
+    it[r].scale = on(r) ? 1.0 : 0.0;
+  }
+  launch_residuals(it, w.N, w.partial.p, w.h_red.as<double2>(), w.rstride, s);
+  return fetch_norms(w, s);
+}
+
+// dst[r] = scale(r) src[r]
+template <typename Scale>
+void scaled_copy(SolveWork& w, const void* src, Scale&& scale, void* dst, hipStream_t s) {
+  std::vector<VecItem> it(w.nrhs);
+  for (int r = 0; r < w.nrhs; ++r) {
+    it[r].src = row(src, w, r);
+    it[r].dst = row(dst, w, r);
+    it[r].scale = scale(r);
+  }
+  launch_scaled_copies(it, w.N, s);
+}
+
+// x[r] += V y[r] over the first k basis vectors (y in ycoef)
+void add_solution(SolveWork& w, int k, void* x, hipStream_t s) {
+  std::vector<VecItem> it(w.nrhs);
+  for (int r = 0; r < w.nrhs; ++r) {
+    it[r].V = row(w.V.p, w, r);
+    it[r].vstride = (long long)w.nrhs * w.N;
+    it[r].nv = k;
+    it[r].b = w.ycoef.as<double2>() + (size_t)r * w.m;
+    it[r].dst = row(x, w, r);
+  }
+  launch_solutions(it, w.N, s);
 }
 
 void givens(cd a, cd b, double& c, cd& s) {
@@ -129,31 +161,26 @@ struct RhsState {
 // Batched GMRES on op(x) = b.  x holds the start (zeros or x0).  `confirm`
 // selects the true-residual check after a converged cycle (top-level solve).
 // pc (or NULL): right preconditioner, the Arnoldi process runs on op P^-1 and
-// a cycle ends with x += P^-1 V y.
-void gmres(emsurf_plan p, OpFn op, emsurf_precond pc, SolveWork& w, int nrhs, const double2* b, double2* x,
-           const std::vector<double>& tol, int max_iter, bool confirm, bool start_zero, std::vector<RhsState>& st,
+// a cycle ends with x += P^-1 V y.  bnorm: the norms of b, which start the
+// first cycle when x = 0.
+void gmres(emsurf_plan p, OpFn op, emsurf_precond pc, SolveWork& w, int nrhs, const double2* b,
+           const std::vector<double>& bnorm, double2* x, const std::vector<double>& tol, int max_iter, bool confirm, bool start_zero, std::vector<RhsState>& st,
            hipStream_t s) {
   const int m = w.m;
   const long long N = w.N;
   const long long vstride = (long long)nrhs * N;
   for (bool first = true;; first = false) {
     // ---- (true) residual r = b - A x for RHS still running (r = b when x = 0)
-    int* hm = w.h_mask.as<int>();
     bool any = false;
-    for (int r = 0; r < nrhs; ++r) { hm[r] = st[r].done ? 0 : 1; any = any || hm[r]; }
+    for (int r = 0; r < nrhs; ++r) any = any || !st[r].done;
     if (!any) return;
-    if (first && start_zero) {
-      double* hs0 = w.h_scale.as<double>();
-      for (int r = 0; r < nrhs; ++r) hs0[r] = hm[r] ? 1.0 : 0.0;
-      EMS_HIP(hipMemcpyAsync(w.scale.p, hs0, (size_t)nrhs * 8, hipMemcpyHostToDevice, s));
-      launch_scale(b, w.scale.p, w.r.p, N, nrhs, s);
-    } else {
-      EMS_HIP(hipMemcpyAsync(w.mask.p, hm, (size_t)nrhs * 4, hipMemcpyHostToDevice, s));
+    const void* res = b;
+    std::vector<double> beta = bnorm;
+    if (!(first && start_zero)) {
       op(p, nrhs, x, w.t.p, s);
-      launch_sub(b, w.t.p, w.mask.as<int>(), w.r.p, N, nrhs, s);
+      beta = residual(w, b, w.t.p, [&](int r) { return !st[r].done; }, w.r.p, s);
+      res = w.r.p;
     }
-    std::vector<double> beta;
-    norms(w, w.r.p, beta, s);
     for (int r = 0; r < nrhs; ++r) {
       if (st[r].done) continue;
       st[r].rel = beta[r] / st[r].bnorm;
@@ -164,7 +191,6 @@ void gmres(emsurf_plan p, OpFn op, emsurf_precond pc, SolveWork& w, int nrhs, co
     for (int r = 0; r < nrhs; ++r) any = any || !st[r].done;
     if (!any) return;
     // ---- start a cycle: v0 = r / beta
-    double* hs = w.h_scale.as<double>();
     for (int r = 0; r < nrhs; ++r) {
       RhsState& q = st[r];
       q.stopped = q.done;
@@ -175,10 +201,8 @@ void gmres(emsurf_plan p, OpFn op, emsurf_precond pc, SolveWork& w, int nrhs, co
       q.sn.assign(m, cd(0));
       q.g.assign(m + 1, cd(0));
       q.g[0] = beta[r];
-      hs[r] = q.done ? 0.0 : 1.0 / beta[r];
     }
-    EMS_HIP(hipMemcpyAsync(w.scale.p, hs, (size_t)nrhs * 8, hipMemcpyHostToDevice, s));
-    launch_scale(w.r.p, w.scale.p, w.Vp(0), N, nrhs, s);
+    scaled_copy(w, res, [&](int r) { return st[r].done ? 0.0 : 1.0 / beta[r]; }, w.Vp(0), s);
     for (int j = 0; j < m; ++j) {
       double2* wv = w.Vp(j + 1);
       if (pc) {
@@ -190,18 +214,20 @@ void gmres(emsurf_plan p, OpFn op, emsurf_precond pc, SolveWork& w, int nrhs, co
       // CGS2: red layout per RHS: [c1 (j+1)][|w0|^2][c2 (j+1)][|w1|^2][|w2|^2]
       const int nv = j + 1;
       const int o1 = 0, o2 = nv + 1, o3 = 2 * nv + 2;
-      launch_dot(w.V.p, vstride, nv, wv, N, nrhs, w.partial.p, w.nblk, w.red.p, w.rstride, o1, s);
-      launch_update(w.V.p, vstride, nv, w.red.p, w.rstride, o1, wv, N, nrhs, s);
-      launch_dot(w.V.p, vstride, nv, wv, N, nrhs, w.partial.p, w.nblk, w.red.p, w.rstride, o2, s);
-      launch_update(w.V.p, vstride, nv, w.red.p, w.rstride, o2, wv, N, nrhs, s);
-      launch_dot(nullptr, 0, 0, wv, N, nrhs, w.partial.p, w.nblk, w.red.p, w.rstride, o3, s);
-      EMS_HIP(hipMemcpyAsync(w.h_red.p, w.red.p, (size_t)w.nrhs * w.rstride * 16, hipMemcpyDeviceToHost, s));
+      std::vector<VecItem> it(nrhs);
+      for (int r = 0; r < nrhs; ++r) {
+        it[r].V = row(w.V.p, w, r);
+        it[r].vstride = vstride;
+        it[r].nv = nv;
+        it[r].src = it[r].dst = row(wv, w, r);
+      }
+      launch_arnoldi(it, N, nv, w.partial.p, w.h_red.as<double2>(), ArnoldiRow{o1, o2, o3, w.rstride}, s);
       EMS_HIP(hipStreamSynchronize(s));
       const double2* hr = w.h_red.as<double2>();
       bool all_stopped = true;
       for (int r = 0; r < nrhs; ++r) {
         RhsState& q = st[r];
-        if (q.stopped) { hs[r] = 0.0; continue; }
+        if (q.stopped) continue;
         const double2* R = hr + (size_t)r * w.rstride;
         cd* Hc = &q.H[(size_t)j * (m + 1)];
         for (int i = 0; i <= j; ++i) Hc[i] = cd(R[o1 + i].x, R[o1 + i].y) + cd(R[o2 + i].x, R[o2 + i].y);
@@ -225,15 +251,11 @@ void gmres(emsurf_plan p, OpFn op, emsurf_precond pc, SolveWork& w, int nrhs, co
           q.stopped = true;
           q.kend = j + 1;
           q.est_ok = est <= tol[r] || lucky;
-          hs[r] = 0.0;
         } else {
-          hs[r] = 1.0 / hn;
           all_stopped = false;
         }
       }
       if (all_stopped) break;
-      EMS_HIP(hipMemcpyAsync(w.scale.p, hs, (size_t)nrhs * 8, hipMemcpyHostToDevice, s));
-      launch_scale(wv, w.scale.p, wv, N, nrhs, s);
     }
     // ---- x += V y  (y from the triangular system of each RHS)
     cd* hy = reinterpret_cast<cd*>(w.h_y.p);
@@ -254,11 +276,11 @@ void gmres(emsurf_plan p, OpFn op, emsurf_precond pc, SolveWork& w, int nrhs, co
     EMS_HIP(hipMemcpyAsync(w.ycoef.p, hy, (size_t)nrhs * m * 16, hipMemcpyHostToDevice, s));
     if (pc) {
       EMS_HIP(hipMemsetAsync(w.pz.p, 0, (size_t)nrhs * N * 16, s));
-      launch_axpy_basis(w.V.p, vstride, kmax, w.ycoef.p, m, w.pz.p, N, nrhs, s);
+      add_solution(w, kmax, w.pz.p, s);
       precond_apply(pc, nrhs, w.pz.p, w.pz2.p, s);
       launch_add(x, w.pz2.p, (long long)nrhs * N, s);
     } else {
-      launch_axpy_basis(w.V.p, vstride, kmax, w.ycoef.p, m, x, N, nrhs, s);
+      add_solution(w, kmax, x, s);
     }
     if (!confirm) {
       // inner solve: accept the estimate
@@ -323,15 +345,12 @@ emsurf_status solve_impl(emsurf_plan plan, emsurf_precond pc, const emsurf_solve
     w.init(nrhs, opts->restart, N);
     if (pc) w.init_precond();
     // finiteness and norms of b
-    int* hm = w.h_mask.as<int>();
-    for (int r = 0; r < nrhs; ++r) hm[r] = 1;
-    EMS_HIP(hipMemcpyAsync(w.mask.p, hm, (size_t)nrhs * 4, hipMemcpyHostToDevice, s));
-    launch_finite(b_dev, N, nrhs, w.mask.as<int>(), s);
-    EMS_HIP(hipMemcpyAsync(hm, w.mask.p, (size_t)nrhs * 4, hipMemcpyDeviceToHost, s));
-    EMS_HIP(hipStreamSynchronize(s));
-    for (int r = 0; r < nrhs; ++r) EMS_CHECK_ARG(hm[r] == 1, "b has a non-finite entry");
-    std::vector<double> bn;
-    norms(w, b_dev, bn, s);
+    std::vector<VecItem> bi(nrhs);
+    for (int r = 0; r < nrhs; ++r) bi[r].src = row(b_dev, w, r);
+    launch_norms(bi, N, w.partial.p, w.h_red.as<double2>(), w.rstride, s);
+    const std::vector<double> bn = fetch_norms(w, s);
+    for (int r = 0; r < nrhs; ++r)
+      EMS_CHECK_ARG(w.h_red.as<double2>()[(size_t)r * w.rstride].y == 0.0, "b has a non-finite entry");
     st.assign(nrhs, RhsState{});
     if (!opts->use_x0) EMS_HIP(hipMemsetAsync(x_dev, 0, (size_t)nrhs * N * 16, s));
     for (int r = 0; r < nrhs; ++r) {
@@ -345,7 +364,7 @@ emsurf_status solve_impl(emsurf_plan plan, emsurf_precond pc, const emsurf_solve
     }
     if (opts->prec != EMSURF_FP32_IR) {
       OpFn op = opts->prec == EMSURF_FP64 ? op_fp64 : op_fp32;
-      gmres(plan, op, pc, w, nrhs, static_cast<const double2*>(b_dev), static_cast<double2*>(x_dev),
+      gmres(plan, op, pc, w, nrhs, static_cast<const double2*>(b_dev), bn, static_cast<double2*>(x_dev),
             std::vector<double>(nrhs, opts->tol), opts->max_iter, true, !opts->use_x0, st, s);
       for (int r = 0; r < nrhs; ++r) outer = std::max(outer, st[r].cycles);
     } else {
@@ -354,21 +373,12 @@ emsurf_status solve_impl(emsurf_plan plan, emsurf_precond pc, const emsurf_solve
       DevBuf &rr = w.ir_r, &d = w.ir_d, &tt = w.ir_t;
       std::vector<RhsState> inner(nrhs);
       for (outer = 0;; ++outer) {
-        for (int r = 0; r < nrhs; ++r) hm[r] = st[r].done ? 0 : 1;
-        std::vector<double> rn;
-        if (outer == 0 && !opts->use_x0) {
-          // x = 0: the residual is b itself, no operator apply needed
-          double* hs0 = w.h_scale.as<double>();
-          for (int r = 0; r < nrhs; ++r) hs0[r] = hm[r] ? 1.0 : 0.0;
-          EMS_HIP(hipMemcpyAsync(w.scale.p, hs0, (size_t)nrhs * 8, hipMemcpyHostToDevice, s));
-          launch_scale(b_dev, w.scale.p, rr.p, N, nrhs, s);
-          rn.resize(nrhs);
-          for (int r = 0; r < nrhs; ++r) rn[r] = hm[r] ? st[r].bnorm : 0.0;
-        } else {
+        std::vector<double> rn = bn;
+        const double2* res = static_cast<const double2*>(b_dev);   // x = 0: the residual is b itself
+        if (!(outer == 0 && !opts->use_x0)) {
           op_fp64(plan, nrhs, x_dev, tt.p, s);
-          EMS_HIP(hipMemcpyAsync(w.mask.p, hm, (size_t)nrhs * 4, hipMemcpyHostToDevice, s));
-          launch_sub(b_dev, tt.p, w.mask.as<int>(), rr.p, N, nrhs, s);
-          norms(w, rr.p, rn, s);
+          rn = residual(w, b_dev, tt.p, [&](int r) { return !st[r].done; }, rr.p, s);
+          res = rr.as<double2>();
         }
         bool any = false;
         for (int r = 0; r < nrhs; ++r) {
@@ -392,7 +402,7 @@ emsurf_status solve_impl(emsurf_plan plan, emsurf_precond pc, const emsurf_solve
         int budget = 0;
         for (int r = 0; r < nrhs; ++r)
           if (!st[r].done) budget = std::max(budget, opts->max_iter - st[r].iters);
-        gmres(plan, op_fp32, pc, w, nrhs, rr.as<double2>(), d.as<double2>(), itol, std::max(1, budget), false, true,
+        gmres(plan, op_fp32, pc, w, nrhs, res, rn, d.as<double2>(), itol, std::max(1, budget), false, true,
               inner, s);
         for (int r = 0; r < nrhs; ++r) st[r].iters += inner[r].iters;
         launch_add(x_dev, d.p, (long long)nrhs * N, s);

@@ -1,43 +1,58 @@
-// Launchers of the GMRES vector kernels (vecops.hip).
+// Launchers of the GMRES vector kernels (vecops.hip).  A launch works on up to
+// 64 independent vectors of N c128 values, one item each; the items travel in
+// the kernel arguments.
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <vector>
+
 namespace emsurf {
-// One item of a pointer-list launch (device memory).  Meaning per kernel:
-//   copy:   dst = scale * (b ? b - a : a)
-//   dot:    a = basis (nv vectors of length N, contiguous), dst = w
-//   update: a = basis, dst = w (w -= basis * coefficients from the reduction buffer)
-//   axpy:   a = basis, b = coefficients (nv complex), dst = x (x += basis * y)
+
+constexpr int VEC_ITEMS = 64;
+// Meaning of an item per launch:
+//   scaled copy: dst = scale src
+//   residual:    dst = scale (b - src), scale 0 or 1
+//   Arnoldi:     basis vectors V, V + vstride, .. (nv of them), the new vector
+//                w read from src and left, orthonormalised, in dst
+//   norm:        ||src||
+//   solution:    dst += sum_{l < nv} V_l y_l, y = b (device)
 struct VecItem {
-  const void* a;
-  const void* b;
-  void* dst;
-  double scale;
-  int nv;
-  int pad;
+  const double2* V = nullptr;
+  const double2* src = nullptr;
+  const double2* b = nullptr;
+  double2* dst = nullptr;
+  long long vstride = 0;
+  double scale = 1.0;
+  int nv = 0;
+  int row = 0;   // set by the Arnoldi launch
 };
-void launch_copy_list(const VecItem* items_dev, int nq, long long N, hipStream_t s);
-// red[q][off + l] = basis_l^H w (l < nv_q), red[q][off + nv_q].x = ||w||^2; ns >= max nv_q + 1
-void launch_dot_list(const VecItem* items_dev, int nq, int ns, long long N, void* partial, int nblk, void* red,
-                     int rstride, int off, hipStream_t s);
-void launch_update_list(const VecItem* items_dev, int nq, long long N, const void* red, int rstride, int off,
-                        hipStream_t s);
-void launch_axpy_list(const VecItem* items_dev, int nq, long long N, hipStream_t s);
+
+// workgroups that share one vector (their partial sums are added in order)
 int dot_blocks(long long N);
-// red[r][off + l] = V_l^H w (l < nv), red[r][off + nv].x = ||w||^2 ; partial: [nrhs][nblk][nv+1] scratch
-void launch_dot(const void* V, long long vstride, int nv, const void* w, long long N, int nrhs, void* partial,
-                int nblk, void* red, int rstride, int off, hipStream_t s);
-// w -= sum_l V_l red[r][off + l]
-void launch_update(const void* V, long long vstride, int nv, const void* red, int rstride, int off, void* w,
-                   long long N, int nrhs, hipStream_t s);
-// y[r] = x[r] * sc[r] (sc: device doubles)
-void launch_scale(const void* x, const void* sc, void* y, long long N, int nrhs, hipStream_t s);
-// x[r] += sum_{l<nv} V_l[r] y[r][l]
-void launch_axpy_basis(const void* V, long long vstride, int nv, const void* y, int ystride, void* x, long long N,
-                       int nrhs, hipStream_t s);
-// out[r] = mask[r] ? a[r] - b[r] : 0   (mask may be NULL)
-void launch_sub(const void* a, const void* b, const int* mask, void* out, long long N, int nrhs, hipStream_t s);
+// bytes of the partial sums of nq items with up to nv basis vectors
+size_t vec_partial_bytes(int nq, int nv, long long N);
+
+// Row q of a result array (host memory the device writes, or device memory;
+// rstride double2 values apart) after an Arnoldi step with nv basis vectors:
+//   [o1 + l]  first coefficients c1 = V_l^H w, [o1 + nv].x = ||w||^2
+//   [o2 + l]  second coefficients V_l^H (w - V c1)
+//   [o3].x    ||w - V (c1 + c2)||^2
+// dst receives the remainder divided by its norm, or zero where the norm is
+// at most 1e-14 ||w|| (the solver's breakdown rule).
+struct ArnoldiRow {
+  int o1, o2, o3, rstride;
+};
+void launch_arnoldi(const std::vector<VecItem>& items, long long N, int nv_max, void* partial, double2* rows,
+                    const ArnoldiRow& at, hipStream_t s);
+// rows[q rstride] = (||src||^2, number of entries of src that are not finite)
+void launch_norms(const std::vector<VecItem>& items, long long N, void* partial, double2* rows, int rstride,
+                  hipStream_t s);
+// dst = scale (b - src), rows[q rstride].x = ||dst||^2
+void launch_residuals(const std::vector<VecItem>& items, long long N, void* partial, double2* rows, int rstride,
+                      hipStream_t s);
+void launch_scaled_copies(const std::vector<VecItem>& items, long long N, hipStream_t s);
+void launch_solutions(const std::vector<VecItem>& items, long long N, hipStream_t s);
+// x += d, total values
 void launch_add(void* x, const void* d, long long total, hipStream_t s);
-// flag[r] set to 0 if b[r] has a non-finite entry (flag must be preset to 1)
-void launch_finite(const void* b, long long N, int nrhs, int* flag, hipStream_t s);
+
 }  // namespace emsurf
