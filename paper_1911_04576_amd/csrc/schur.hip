@@ -17,6 +17,8 @@
 // type) runs in the same launches, and the trailing updates spread over many
 // workgroups per matrix.  FP64 complex throughout; row-major storage, matrix
 // b at A + b N^2.
+#include <climits>
+#include <type_traits>
 #include <vector>
 
 #include <hip/hip_ext.h>
@@ -27,6 +29,7 @@ namespace emsurf {
 namespace {
 
 constexpr int PANEL = 32;
+typedef double d4v __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ double2 cmul(double2 a, double2 b) {
   return double2{a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x};
@@ -118,240 +121,243 @@ template <int CTRL> __device__ __forceinline__ double dpp_d(double v) {
   const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xF, 0xF, false);
   return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
 }
-template <int CTRL> __device__ __forceinline__ int dpp_i(int v) {
-  return __builtin_amdgcn_mov_dpp(v, CTRL, 0xF, 0xF, false);
+// Pivot key of a value |a|^2 >= 0: the upper half of the double (sign,
+// exponent, 20 bits of mantissa), ordered like it; -1 for no candidate.
+__device__ __forceinline__ int pivot_key(double v2, bool candidate) {
+  return candidate && v2 >= 0.0 ? (int)(__builtin_bit_cast(long long, v2) >> 32) : -1;   // (a NaN is none)
 }
-__device__ __forceinline__ void argmax_take(double& v, int& idx, double ov, int oi) {
-  // (bitwise operators: no short-circuit branches)
-  const bool take = (ov > v) | ((ov == v) & (oi < idx));
-  v = take ? ov : v;
-  idx = take ? oi : idx;
+__device__ __forceinline__ int max_i(int a, int b) { return a > b ? a : b; }
+// Largest v within each row of 16 lanes, in every lane: quad exchanges 1 and 2
+// and row rotations 4 and 8 by DPP.
+__device__ __forceinline__ int row_max(int v) {
+  v = max_i(v, __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, false));    // quad_perm [1,0,3,2]
+  v = max_i(v, __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, false));    // quad_perm [2,3,0,1]
+  v = max_i(v, __builtin_amdgcn_mov_dpp(v, 0x124, 0xF, 0xF, false));   // row_ror 4
+  return max_i(v, __builtin_amdgcn_mov_dpp(v, 0x128, 0xF, 0xF, false));   // row_ror 8
 }
-__device__ __forceinline__ double readlane_d(double v, int l) {
-  const long long b = __builtin_bit_cast(long long, v);
-  const int lo = __builtin_amdgcn_readlane((int)b, l);
-  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
-  return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
-}
-// The same as a DPP move that only the rows in RM take (the other rows keep
-// their value): the row broadcasts of 64-lane reductions
-template <int CTRL, int RM> __device__ __forceinline__ double bcast_dpp_d(double v) {
-  const long long b = __builtin_bit_cast(long long, v);
-  const int lo = __builtin_amdgcn_update_dpp((int)b, (int)b, CTRL, RM, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp((int)(b >> 32), (int)(b >> 32), CTRL, RM, 0xF, false);
-  return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
-}
-// (largest v, first index on ties) over the 64 lanes, as wavefront-uniform
-// values: quad exchanges 1 and 2 and row rotations 4 and 8 by DPP leave each
-// row of 16 lanes with its own result; row_bcast:15 then brings lane 15 of
-// rows 0 and 2 into rows 1 and 3, row_bcast:31 lane 31 into rows 2 and 3, so
-// that row 3 holds the result of all four, read from lane 63 (the order
-// does not matter: the rule is a maximum over (v, -index))
-__device__ __forceinline__ void wave_argmax(double& v, int& idx) {
-  argmax_take(v, idx, dpp_d<0xB1>(v), dpp_i<0xB1>(idx));   // quad_perm [1,0,3,2]
-  argmax_take(v, idx, dpp_d<0x4E>(v), dpp_i<0x4E>(idx));   // quad_perm [2,3,0,1]
-  argmax_take(v, idx, dpp_d<0x124>(v), dpp_i<0x124>(idx)); // row_ror 4
-  argmax_take(v, idx, dpp_d<0x128>(v), dpp_i<0x128>(idx)); // row_ror 8
-  argmax_take(v, idx, bcast_dpp_d<0x142, 0xA>(v), __builtin_amdgcn_update_dpp(idx, idx, 0x142, 0xA, 0xF, false));
-  argmax_take(v, idx, bcast_dpp_d<0x143, 0xC>(v), __builtin_amdgcn_update_dpp(idx, idx, 0x143, 0xC, 0xF, false));
-  v = readlane_d(v, 63);
-  idx = __builtin_amdgcn_readlane(idx, 63);
+// Largest v over the 64 lanes, wavefront-uniform: row_bcast:15 brings lane 15
+// of rows 0 and 2 into rows 1 and 3, row_bcast:31 lane 31 into rows 2 and 3,
+// so that row 3 holds the result of all four, read from lane 63.
+__device__ __forceinline__ int wave_max(int v) {
+  v = row_max(v);
+  v = max_i(v, __builtin_amdgcn_update_dpp(v, v, 0x142, 0xA, 0xF, false));
+  v = max_i(v, __builtin_amdgcn_update_dpp(v, v, 0x143, 0xC, 0xF, false));
+  return __builtin_amdgcn_readlane(v, 63);
 }
 
-// The same panel with the rows in registers, for N - k0 <= NT * RPT: NT
-// threads, thread t owning rows k0 + t, k0 + t + NT, ... (RPT of them; few
-// wavefronts keep the per-column barriers and reductions short).  The
-// panel's columns go in sub-blocks of PSB: a sub-block is staged through
-// LDS with coalesced loads and stores (rows [c0, N)), held in registers, its
-// columns are factorised there (pivot by a reduction over the thread's rows,
-// a wavefront reduction and one over the NT / 64 wavefronts in LDS, row
-// exchange through LDS), and the columns outside it then take the
-// sub-block's row swaps at once (the panel's others, the lw columns left of
-// the panel and the rw columns right of it), and the columns to its right
-// (the panel's and the rw beyond) its U rows (L11^-1 A12 by one wavefront)
-// and one rank-PSB update, so that the panel makes one pass through memory
-// per sub-block instead of one per column.  Same pivots (largest |a|^2
-// among rows [kk, K), first index on ties), same singular flags.
+// The same panel with the rows in registers, for N - k0 <= NT: one row per
+// thread.  The panel's columns go in sub-blocks of PSB: a sub-block is staged
+// through LDS with coalesced loads and stores (rows [c0, N)), held in
+// registers, its columns are factorised there, and the columns outside it
+// then take the sub-block's row swaps at once (the panel's others, the lw
+// columns left of the panel and the rw columns right of it), and the columns
+// to its right (the panel's and the rw beyond) its U rows (L11^-1 A12 by one
+// wavefront) and one rank-PSB update, so that the panel makes one pass
+// through memory per sub-block instead of one per column.  The pivot is the
+// largest |a|^2 among rows [kk, K), to 20 bits (of equal ones the row that
+// stood first when the sub-block began); same singular flags.
+//
+// One CU per matrix walks all the columns, so the panel is a serial chain, and
+// with up to 16 wavefronts on the CU what the chain waits for is the LDS and
+// the instructions that every wavefront issues per column:
+//  - A column publishes 8 bytes per wavefront (its largest key, found as a
+//    maximum with the lane by a ballot) and then the pivot row alone, for two
+//    barriers.  With every wavefront's candidate row published before a single
+//    barrier and read by every lane, the LDS took half of each column.
+//  - The key is the upper half of |a|^2, which a DPP maximum reduces in one
+//    instruction per step: a chosen pivot is within 2^-20 of the largest.
+//  - The pivot row's values sit in one lane each of a row of 16 lanes and
+//    enter the multiply-adds by DPP (row_newbcast): one LDS read per wavefront.
+//  - Rows do not move: a thread keeps its row and tracks its position.
+// Cycles of a sub-block at 864 rows (480 in brackets): its 8 columns 38100 ->
+// 16000 (22100 -> 12700), loads and stores 16400 -> 6900, swaps 3100 -> 2500,
+// update of 56 to 32 columns 66800 .. 26500 -> 74000 .. 24000.
 constexpr int PSB = 8;
-template <int NT, int RPT>
+
+// r -= m q_C, q_C held by lane C of each row of 16 lanes.  All lanes must be
+// active (volatile: not moved into a condition).  The s_nop covers the two
+// wait states between a vector write of q and its first read through DPP,
+// which the compiler does not add for inline assembly.
+template <int C> __device__ __forceinline__ void csub_mul_lane(double2& r, double2 m, double2 q) {
+  asm volatile("s_nop 1\n\t"
+      "v_fmac_f64_dpp %0, %5, %3 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, -%4, %3 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%4, %2 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, -%5, %2 row_newbcast:%6 row_mask:0xf bank_mask:0xf"
+      : "+v"(r.x), "+v"(r.y)
+      : "v"(m.x), "v"(m.y), "v"(q.x), "v"(q.y), "n"(C));
+}
+// lane C's value of each row of 16 lanes
+template <int C> __device__ __forceinline__ double lane_of_row(double v) {
+  return __builtin_amdgcn_update_dpp(0.0, v, 0x150 + C, 0xF, 0xF, true);
+}
+
+template <int NT>
 __global__ void __launch_bounds__(NT) panel_reg_kernel(double2* __restrict__ A, int N, int K, int k0, int kb, int lw,
-                                                            int rw, int* __restrict__ piv, int* __restrict__ info) {
+                                                       int rw, int* __restrict__ piv, int* __restrict__ info) {
+  constexpr int NW = NT / 64;
+  static_assert(NW <= 16, "one row of lanes merges the wavefronts' candidates");
   const int b = blockIdx.x;
   double2* M = A + (long long)b * N * N;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  __shared__ double rv[2][NT / 64];
-  __shared__ int ri[2][NT / 64];
-  __shared__ double2 cand[2][NT / 64][PSB];   // each wavefront's best candidate row
-  __shared__ double2 krow[2][PSB];                 // row col, which the pivot row displaces
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = tid & 15;
+  __shared__ int2 rec[NW];                 // each wavefront's largest pivot key and the position of its row
+  __shared__ double2 prow[16];             // the pivot row right of the column, its pivot's inverse in the column's place
   __shared__ double2 U[PSB][2 * PANEL];    // the sub-block's U rows over the columns to its right
   __shared__ int spv[PSB];                 // the sub-block's pivot rows
+  __shared__ int swX[2 * PSB], swS[2 * PSB];   // rows that its swaps move, and from where
   extern __shared__ double2 sub[];         // [N - c0][PSB]: the sub-block, rows c0 ..
-  auto rowof = [&](int q) { return k0 + tid + NT * q; };
-  int first_singular = -1;   // the same in every thread
+  // (a row's values are permuted by its index: eight lanes on the same column
+  // of eight rows then meet eight different places of the 128-byte rows)
+  auto at = [](int rr, int c) { return rr * PSB + (c ^ (rr & (PSB - 1))); };
+  if (tid < 16) prow[tid] = double2{0.0, 0.0};
+  const int row = k0 + tid;   // this thread's row
+  int first_singular = -1;    // the same in every thread
   for (int sb0 = 0; sb0 < kb; sb0 += PSB) {
     const int sbw = kb - sb0 < PSB ? kb - sb0 : PSB;
     const int c0 = k0 + sb0, rc0 = sb0 + sbw;   // rc0: first panel column to the right (panel-relative)
     // rows above c0 keep their values in this sub-block (U rows of the panel)
     // (every load of the sub-block is issued before the first is used:
-    // nsub <= RPT * NT * PSB)
+    // nsub <= NT * PSB)
     const int nsub = (N - c0) * PSB;
     {
-      double2 st[RPT * PSB];
+      double2 st[PSB];
 #pragma unroll
-      for (int j = 0; j < RPT * PSB; ++j) {
+      for (int j = 0; j < PSB; ++j) {
         const int e = tid + NT * j, c = e & (PSB - 1);
         st[j] = (e < nsub && c < sbw) ? M[(long long)(c0 + (e / PSB)) * N + k0 + sb0 + c] : double2{0.0, 0.0};
       }
 #pragma unroll
-      for (int j = 0; j < RPT * PSB; ++j) {
+      for (int j = 0; j < PSB; ++j) {
         const int e = tid + NT * j;
-        if (e < nsub) sub[e] = st[j];
+        if (e < nsub) sub[at(e / PSB, e & (PSB - 1))] = st[j];
       }
     }
     __syncthreads();
-    double2 r[RPT][PSB];
+    const bool mine = row >= c0 && row < N;
+    const int lrow = mine ? row - c0 : 0;   // (threads without a row read row c0 and never use it)
+    double2 r[PSB];
 #pragma unroll
-    for (int q = 0; q < RPT; ++q) {
-      const int rr = rowof(q);
-#pragma unroll
-      for (int c = 0; c < PSB; ++c) r[q][c] = (rr >= c0 && rr < N) ? sub[(rr - c0) * PSB + c] : double2{0.0, 0.0};
-    }
-#pragma unroll
-    for (int kk = 0; kk < PSB; ++kk) {
-      if (kk >= sbw) break;
+    for (int c = 0; c < PSB; ++c) r[c] = sub[at(lrow, c)];
+    // the row's position: where the swaps so far have put it
+    int pos = mine ? row : -1;
+    // (the columns past sbw are zero and stay so: no step looks at sbw, whose
+    // conditions would cut the step into blocks with waits of their own)
+    auto step = [&](auto kk_) {
+      constexpr int kk = decltype(kk_)::value;
       const int col = k0 + sb0 + kk;
-      // pivot: largest |a|^2 among rows [col, K), first index on ties
-      double v = -1.0;
-      int idx = tid;
-#pragma unroll
-      for (int q = 0; q < RPT; ++q) {
-        const int rr = rowof(q);
-        const double vq = (rr >= col && rr < K) ? r[q][kk].x * r[q][kk].x + r[q][kk].y * r[q][kk].y : -1.0;
-        argmax_take(v, idx, vq, rr);
+      const double v2 = r[kk].x * r[kk].x + r[kk].y * r[kk].y;
+      // (few wavefronts leave the division room beside the reduction; with
+      // many the pivot row's wavefront alone divides)
+      double rd = 0.0;
+      if constexpr (NT <= 512) {
+        rd = 1.0 / v2;
+        asm volatile("" : "+v"(rd));   // (here, not in the pivot row's block)
       }
-      wave_argmax(v, idx);
-      // one barrier per column: before it each wavefront publishes its best
-      // candidate (value, row, and the row's sub-block values), and the owner
-      // of row col publishes that row; the slots alternate with the column's
-      // parity, so the next column's writes cannot meet this column's reads
-      const int par = kk & 1;
-      if (lane == 0) {
-        rv[par][wave] = v;
-        ri[par][wave] = idx;
-      }
-      const int qc = (col - k0) / NT;
-#pragma unroll
-      for (int q = 0; q < RPT; ++q) {
-        if (rowof(q) == idx && v >= 0.0)
-#pragma unroll
-          for (int c = 0; c < PSB; ++c) cand[par][wave][c] = r[q][c];
-        if (q == qc && tid == (col - k0) % NT)
-#pragma unroll
-          for (int c = 0; c < PSB; ++c) krow[par][c] = r[q][c];
-      }
+      const int v = pivot_key(v2, pos >= col && pos < K);
+      const int wm = wave_max(v);
+      if (lane == __builtin_ctzll(__ballot(v == wm)))   // (some lane holds the maximum)
+        rec[wave] = int2{wm, pos};
       __syncthreads();
-      // the wavefronts' candidates: lane w (w < NT / 64) of every row of 16
-      // lanes takes wavefront w's, the others an empty one that never wins;
-      // four DPP steps leave every lane with the best, read as uniform values
-      double bv;
-      int p;
-      {
-        const int w = lane & 15;
-        double cv = w < NT / 64 ? rv[par][w < NT / 64 ? w : 0] : -2.0;
-        int ci = w < NT / 64 ? ri[par][w < NT / 64 ? w : 0] : 0x7fffffff;
-        argmax_take(cv, ci, dpp_d<0xB1>(cv), dpp_i<0xB1>(ci));
-        argmax_take(cv, ci, dpp_d<0x4E>(cv), dpp_i<0x4E>(ci));
-        argmax_take(cv, ci, dpp_d<0x124>(cv), dpp_i<0x124>(ci));
-        argmax_take(cv, ci, dpp_d<0x128>(cv), dpp_i<0x128>(ci));
-        bv = readlane_d(cv, 0);
-        p = __builtin_amdgcn_readlane(ci, 0);
+      // the wavefronts' records: lane w of every row of 16 lanes takes
+      // wavefront w's, the others an empty one that never wins
+      const int2 rc = rec[l16 < NW ? l16 : 0];
+      const int cv = l16 < NW ? rc.x : -2;
+      const int bv = __builtin_amdgcn_readlane(row_max(cv), 0);
+      // (a key of zero, |a| < 1e-157 throughout, has no finite inverse; -1: every value is NaN)
+      const bool singular = bv <= 0;
+      const int p = singular ? col : __builtin_amdgcn_readlane(rc.y, __builtin_ctzll(__ballot(cv == bv)));
+      if (pos == p) {
+        if constexpr (NT > 512) rd = 1.0 / v2;
+        prow[kk] = singular ? double2{0.0, 0.0} : double2{r[kk].x * rd, -r[kk].y * rd};
+#pragma unroll
+        for (int c = kk + 1; c < PSB; ++c) prow[c] = r[c];
       }
-      const int pw = ((p - k0) % NT) / 64;   // the wavefront that holds row p
-      const double2* prow = cand[par][pw];   // the pivot row over the sub-block
-      const bool singular = !(bv > 0.0);
       if (singular && first_singular < 0) first_singular = col;
       if (tid == 0) spv[kk] = p;
-      // exchange rows col and p in this sub-block (the other panel columns
-      // take the sub-block's swaps together after it: no memory operation
-      // inside the column loop, whose barrier would wait for it)
-      if (p != col) {
-#pragma unroll
-        for (int q = 0; q < RPT; ++q) {
-          if (rowof(q) == col) {
-#pragma unroll
-            for (int c = 0; c < PSB; ++c) r[q][c] = prow[c];
-          } else if (rowof(q) == p) {
-#pragma unroll
-            for (int c = 0; c < PSB; ++c) r[q][c] = krow[par][c];
-          }
-        }
-      }
+      __syncthreads();
+      const double2 q = prow[l16];
+      pos = pos == p ? col : pos == col ? p : pos;
       // multipliers and the rank-1 update inside the sub-block
-      const double2 inv = singular ? double2{0.0, 0.0} : cinv(prow[kk]);
-#pragma unroll
-      for (int q = 0; q < RPT; ++q) {
-        const int rr = rowof(q);
-        if (rr < N && rr > col) {
-          const double2 mlt = cmul(r[q][kk], inv);
-          r[q][kk] = mlt;
-#pragma unroll
-          for (int c = 0; c < PSB; ++c)
-            if (c > kk && c < sbw) r[q][c] = csub_mul(r[q][c], mlt, prow[c]);
-        }
+      const bool below = pos > col;
+      const double2 m = cmul(r[kk], double2{lane_of_row<kk>(q.x), lane_of_row<kk>(q.y)});
+      const double2 mlt{below ? m.x : 0.0, below ? m.y : 0.0};
+      r[kk].x = below ? m.x : r[kk].x;
+      r[kk].y = below ? m.y : r[kk].y;
+      if constexpr (kk < 1) csub_mul_lane<1>(r[1], mlt, q);
+      if constexpr (kk < 2) csub_mul_lane<2>(r[2], mlt, q);
+      if constexpr (kk < 3) csub_mul_lane<3>(r[3], mlt, q);
+      if constexpr (kk < 4) csub_mul_lane<4>(r[4], mlt, q);
+      if constexpr (kk < 5) csub_mul_lane<5>(r[5], mlt, q);
+      if constexpr (kk < 6) csub_mul_lane<6>(r[6], mlt, q);
+      if constexpr (kk < 7) csub_mul_lane<7>(r[7], mlt, q);
+    };
+    static_assert(PSB == 8, "steps below");
+#define EMS_STEP(k) step(std::integral_constant<int, k>{})
+    if (sbw == PSB) {
+      EMS_STEP(0); EMS_STEP(1); EMS_STEP(2); EMS_STEP(3); EMS_STEP(4); EMS_STEP(5); EMS_STEP(6); EMS_STEP(7);
+    } else {
+      EMS_STEP(0);
+      if (sbw > 1) EMS_STEP(1);
+      if (sbw > 2) EMS_STEP(2);
+      if (sbw > 3) EMS_STEP(3);
+      if (sbw > 4) EMS_STEP(4);
+      if (sbw > 5) EMS_STEP(5);
+      if (sbw > 6) EMS_STEP(6);
+    }
+#undef EMS_STEP
+    // what the sub-block's swaps do to a row outside its columns: slot x
+    // stands for row X (c0 + x / 2, or the pivot row of column x / 2), which
+    // receives what row sigma(X) held before, sigma the swaps in reverse order
+    if (tid < 2 * PSB) {
+      const int X = tid < 2 * sbw ? ((tid & 1) ? spv[tid >> 1] : c0 + (tid >> 1)) : -1;
+      int src = X;
+      for (int i = sbw - 1; i >= 0; --i) {
+        const int pi = spv[i];
+        src = src == c0 + i ? pi : src == pi ? c0 + i : src;
       }
+      swX[tid] = src != X ? X : -1;
+      swS[tid] = src;
     }
-    // the sub-block back to memory through LDS
+    // the sub-block back to memory through LDS, every row to its position
+    // (each thread read its row of sub before the first step's barriers)
+    if (mine)
 #pragma unroll
-    for (int q = 0; q < RPT; ++q) {
-      const int rr = rowof(q);
-      if (rr >= c0 && rr < N)
-#pragma unroll
-        for (int c = 0; c < PSB; ++c) sub[(rr - c0) * PSB + c] = r[q][c];
-    }
+      for (int c = 0; c < PSB; ++c) sub[at(pos - c0, c)] = r[c];
     __syncthreads();
+    {
+      double2 st[PSB];
 #pragma unroll
-    for (int j = 0; j < RPT * PSB; ++j) {
-      const int e = tid + NT * j, c = e & (PSB - 1);
-      if (e < nsub && c < sbw) M[(long long)(c0 + (e / PSB)) * N + k0 + sb0 + c] = sub[e];
+      for (int j = 0; j < PSB; ++j) {
+        const int e = tid + NT * j < nsub ? tid + NT * j : 0;
+        st[j] = sub[at(e / PSB, e & (PSB - 1))];
+      }
+#pragma unroll
+      for (int j = 0; j < PSB; ++j) {
+        const int e = tid + NT * j, c = e & (PSB - 1);
+        if (e < nsub && c < sbw) M[(long long)(c0 + (e / PSB)) * N + k0 + sb0 + c] = st[j];
+      }
     }
     // the sub-block's swaps on the other panel columns, and on the lw
     // columns left of the panel, at once: (slot x, column k0 - lw + c)
-    // writes row X (c0 + x / 2, or the pivot row of column x / 2) with the
-    // value the swap sequence brings to it, the value that row sigma(X) held
-    // before, sigma the swaps applied in reverse order
     {
-      constexpr int H = (2 * PSB * 2 * PANEL + NT - 1) / NT;
-      int Xs[H], srcs[H];
-      double2 mv[H];
-#pragma unroll
-      for (int h = 0; h < H; ++h) {
+      constexpr int H = 2 * PSB * 2 * PANEL / NT;
+      static_assert(H * NT == 2 * PSB * 2 * PANEL && H <= 2, "swap slots per thread");
+      auto take = [&](int h, int& X) {
         const int e = tid + NT * h, x = e / (2 * PANEL), c = e % (2 * PANEL);
-        Xs[h] = -1;
-        srcs[h] = -1;
-        mv[h] = double2{0.0, 0.0};
-        if (x < 2 * sbw && c < lw + kb + rw && (c < lw + sb0 || c >= lw + sb0 + sbw)) {
-          const int X = (x & 1) ? spv[x >> 1] : c0 + (x >> 1);
-          int src = X;
-          for (int i = sbw - 1; i >= 0; --i) {
-            const int pi = spv[i];
-            if (src == c0 + i)
-              src = pi;
-            else if (src == pi)
-              src = c0 + i;
-          }
-          if (src != X) {
-            Xs[h] = X;
-            srcs[h] = src;
-            mv[h] = M[(long long)src * N + k0 - lw + c];
-          }
-        }
-      }
+        const bool on = swX[x] >= 0 && c < lw + kb + rw && (c < lw + sb0 || c >= lw + sb0 + sbw);
+        X = on ? swX[x] : -1;
+        return M[(long long)(on ? swS[x] : c0) * N + k0 - (on ? lw - c : 0)];
+      };
+      auto put = [&](int h, int X, double2 v) {
+        if (X >= 0) M[(long long)X * N + k0 - lw + (tid + NT * h) % (2 * PANEL)] = v;
+      };
+      int X0, X1 = -1;
+      double2 v1{};
+      const double2 v0 = take(0, X0);
+      if constexpr (H > 1) v1 = take(1, X1);
       __syncthreads();   // every value is read before any is written
-#pragma unroll
-      for (int h = 0; h < H; ++h) {
-        const int c = (tid + NT * h) % (2 * PANEL);
-        if (Xs[h] >= 0) M[(long long)Xs[h] * N + k0 - lw + c] = mv[h];
-      }
+      put(0, X0, v0);
+      if constexpr (H > 1) put(1, X1, v1);
       if (tid < sbw) piv[(long long)b * K + c0 + tid] = spv[tid];
     }
     if (rc0 < kb + rw) {
@@ -370,7 +376,7 @@ __global__ void __launch_bounds__(NT) panel_reg_kernel(double2* __restrict__ A, 
           double2 vv = x[i];
 #pragma unroll
           for (int j = 0; j < PSB; ++j)
-            if (j < i) vv = csub_mul(vv, sub[i * PSB + j], x[j]);
+            if (j < i) vv = csub_mul(vv, sub[at(i, j)], x[j]);
           x[i] = vv;
           U[i][c] = vv;
           M[(long long)(c0 + i) * N + k0 + c] = vv;
@@ -378,36 +384,58 @@ __global__ void __launch_bounds__(NT) panel_reg_kernel(double2* __restrict__ A, 
       }
       __syncthreads();
       // rank-sbw update of the columns to the right for the rows below the
-      // sub-block: a thread keeps one column's U values in registers and
-      // walks rows rofs, rofs + rstep, ... (consecutive threads on
-      // consecutive columns of a row, the row's multipliers from LDS), with
-      // UB rows' requests in flight at once
-      constexpr int UB = NT >= 1024 ? 4 : 16;   // (fewer registers for the larger workgroup)
-      const int nrc = kb + rw - rc0, rstep = NT / nrc, nrow = N - c0 - sbw;
-      const int rofs = tid / nrc, c = rc0 + tid % nrc;
-      if (rofs < rstep) {
-        double2 u[PSB];
+      // sub-block, on the FP64 matrix cores in tiles of 16 rows x 16 columns:
+      // a wavefront keeps to one group of 16 columns, its U values (k = 4 ks +
+      // lane / 16) in registers, the next tile requested (at clamped
+      // addresses) before the current one is used (two or four at a time were
+      // slower).  Bound by this CU's traffic: 32 bytes per cycle, read and
+      // written, whether the products ran here or as vector multiply-adds.
+      const int nrow = N - c0 - sbw, ntile = (nrow + 15) / 16, ncg = (kb + rw - rc0 + 15) / 16, rstep = NW / ncg;
+      const int cg = wave % ncg, t0 = wave / ncg, lk = lane >> 4, c = rc0 + 16 * cg + l16;
+      const bool okc = c < kb + rw;
+      double nur[2], ui[2], nui[2];   // -Re U, Im U, -Im U
 #pragma unroll
-        for (int i = 0; i < PSB; ++i) u[i] = i < sbw ? U[i][c] : double2{0.0, 0.0};
-        for (int rb = rofs; rb < nrow; rb += UB * rstep) {
-          double2 vv[UB];
+      for (int ks = 0; ks < 2; ++ks) {
+        const int i = 4 * ks + lk;
+        const double2 uv = okc && i < sbw ? U[i][c] : double2{0.0, 0.0};
+        nur[ks] = -uv.x;
+        ui[ks] = uv.y;
+        nui[ks] = -uv.y;
+      }
+      double2* Mc = M + (long long)(c0 + sbw) * N + k0 + (okc ? c : rc0);
+      auto load = [&](int t, double2 (&vv)[4]) {
 #pragma unroll
-          for (int z = 0; z < UB; ++z) {
-            const int rl = rb + z * rstep;
-            vv[z] = rl < nrow ? M[(long long)(c0 + sbw + rl) * N + k0 + c] : double2{0.0, 0.0};
-          }
-          // (u[i] is zero for i >= sbw: an element's eight multipliers are
-          // read without conditions, together)
+        for (int e = 0; e < 4; ++e) {
+          const int rl = 16 * t + lk + 4 * e;
+          vv[e] = Mc[(long long)(rl < nrow ? rl : nrow - 1) * N];
+        }
+      };
+      auto update = [&](int t, double2 (&vv)[4]) {
+        const int ra = 16 * t + l16;
+        d4v re{vv[0].x, vv[1].x, vv[2].x, vv[3].x}, im{vv[0].y, vv[1].y, vv[2].y, vv[3].y};
 #pragma unroll
-          for (int z = 0; z < UB; ++z) {
-            const int rl = rb + z * rstep;
-            if (rl < nrow) {
-              double2 w = vv[z];
+        for (int ks = 0; ks < 2; ++ks) {
+          const double2 lv = sub[at(sbw + (ra < nrow ? ra : 0), 4 * ks + lk)];
+          re = __builtin_amdgcn_mfma_f64_16x16x4f64(lv.x, nur[ks], re, 0, 0, 0);
+          im = __builtin_amdgcn_mfma_f64_16x16x4f64(lv.x, nui[ks], im, 0, 0, 0);
+          re = __builtin_amdgcn_mfma_f64_16x16x4f64(lv.y, ui[ks], re, 0, 0, 0);
+          im = __builtin_amdgcn_mfma_f64_16x16x4f64(lv.y, nur[ks], im, 0, 0, 0);
+        }
 #pragma unroll
-              for (int i = 0; i < PSB; ++i) w = csub_mul(w, sub[(sbw + rl) * PSB + i], u[i]);
-              M[(long long)(c0 + sbw + rl) * N + k0 + c] = w;
-            }
-          }
+        for (int e = 0; e < 4; ++e) {
+          const int rl = 16 * t + lk + 4 * e;
+          if (okc && rl < nrow) Mc[(long long)rl * N] = double2{re[e], im[e]};
+        }
+      };
+      if (nrow > 0 && t0 < rstep) {   // (uniform in a wavefront)
+        double2 va[4], vb[4];
+        load(t0, va);
+        for (int t = t0; t < ntile; t += 2 * rstep) {
+          load(t + rstep, vb);
+          update(t, va);
+          if (t + rstep >= ntile) break;
+          load(t + 2 * rstep, va);
+          update(t + rstep, vb);
         }
       }
       __syncthreads();
@@ -564,7 +592,6 @@ constexpr int ULP = PANEL + 1;   // L rows padded: the 16 rows of a read start o
 template <int ROUNDS>
 __device__ __forceinline__ void update_tile(double2* __restrict__ M, int N, int k0, int kb, int ce, int r0, int c0,
                                             bool live, double2* __restrict__ Ls, double2* __restrict__ Us, int tid) {
-  typedef double d4v __attribute__((ext_vector_type(4)));
   const int l = tid & 63, wv = tid >> 6, wr = wv & 1, wc = wv >> 1;
   // this lane's outputs: tile (rt, ct), register e -> row (l / 16) + 4 e, column l % 16
   const int jj = l & 15, qrow = l >> 4;
@@ -689,7 +716,6 @@ __global__ void __launch_bounds__(256, 2) update_mfma_kernel(double2* __restrict
 // half, matrix-major, row tile, then column tile.
 __global__ void __launch_bounds__(512) update_persist_kernel(double2* __restrict__ A, int N, int k0, int kb, int cb,
                                                              int ce, int nrt, int nct, int T) {
-  typedef double d4v __attribute__((ext_vector_type(4)));
   __shared__ double2 Lsh[2][UT * ULP];
   __shared__ double2 Ush[2][PANEL * UT];
   const int half = threadIdx.x >> 8, tid = threadIdx.x & 255;
@@ -916,20 +942,21 @@ void eliminate(double2* A, int N, int K, int T, int* piv, int* info, hipStream_t
   int cus = 0, dev = 0;
   EMS_HIP(hipGetDevice(&dev));
   EMS_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-  // far columns: a persistent grid that leaves 2 T CUs free, the panels'
-  // and as many again for the near columns' kernels that run beside it
-  const int persist_grid = (T <= 64 && cus - 2 * T >= 64) ? cus - 2 * T : 0;
+  // far columns: a persistent grid that leaves T + 16 CUs free, the panels'
+  // and some for the near columns' kernels that run beside it (2 T: 1.5%
+  // slower at 32 types, where the far update bounds the first blocks)
+  const int persist_grid = (T <= 64 && cus - T - 16 >= 64) ? cus - T - 16 : 0;
   auto panel = [&](int k0, int kb, int lw, int rw, hipEvent_t stop) {
     const int rows = N - k0;
     const uint32_t shm = (uint32_t)((size_t)rows * PSB * sizeof(double2));
     // (the sub-block staging holds rows * PSB values in LDS; one row per
-    // thread: 512 threads up to 512 rows, 1024 beyond, where the larger
-    // workgroup beat 768 threads and 512 with two rows each)
+    // thread: 512 threads up to 512 rows (256 up to 256 rows took as long:
+    // shorter columns, longer updates), 1024 beyond)
     if (rows <= 512)
-      hipExtLaunchKernelGGL((panel_reg_kernel<512, 1>), dim3((unsigned)T), dim3(512), shm, s, nullptr, stop, 0u, A, N,
+      hipExtLaunchKernelGGL((panel_reg_kernel<512>), dim3((unsigned)T), dim3(512), shm, s, nullptr, stop, 0u, A, N,
                             K, k0, kb, lw, rw, piv, info);
     else if (rows <= 1024)
-      hipExtLaunchKernelGGL((panel_reg_kernel<1024, 1>), dim3((unsigned)T), dim3(1024), shm, s, nullptr, stop, 0u, A, N,
+      hipExtLaunchKernelGGL((panel_reg_kernel<1024>), dim3((unsigned)T), dim3(1024), shm, s, nullptr, stop, 0u, A, N,
                             K, k0, kb, lw, rw, piv, info);
     else   // (lw == rw == 0 here: blocks of one panel)
       hipExtLaunchKernelGGL(panel_kernel, dim3((unsigned)T), dim3(512), 0u, s, nullptr, stop, 0u, A, N, K, k0, kb, piv, info);
