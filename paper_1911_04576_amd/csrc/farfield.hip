@@ -8,139 +8,200 @@
 // (common factor -jk e^{-jkr}/(4 pi r) dropped).  At the direction cosines of
 // the bins of an Lu x Lv lattice DFT, k pitch u = 2 pi p' / Lu (p' the signed
 // bin), the sum over elements is the zero-padded 2-D DFT with kernel
-// e^{+j 2 pi (p ix / Lu + q iy / Lv)} of the lattice data: two Stockham
-// passes of sign +1 (the passes of the coupling apply), then one projection
-// per bin over the patches of a box.
+// e^{+j 2 pi (p ix / Lu + q iy / Lv)} of the lattice data: a Stockham pass of
+// sign +1 along x (the pass of the coupling apply), then one kernel that runs
+// the pass along y in LDS and projects its points onto the directions.
 #include <cmath>
 #include <vector>
 
-#include "internal.h"
+#include "fft_device.h"
 
 namespace emsurf {
 namespace {
 
-__device__ __forceinline__ double2 cmul(double2 a, double2 b) {
-  return double2{a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x};
-}
+struct PatternArgs {
+  const double2* W;      // [iy][p][r][u], transformed along x
+  const double* rho;
+  const double* area;
+  const double* tan;
+  const double2* tw;     // twiddles of the y transform
+  int P, Lu, ny, nrhs;
+  double pitch, k;
+  double2* E;            // [r][q][p][2] (E_theta, E_phi), upper half space; or NULL
+  double* U;             // [r][half space][q][p] radiation intensity; or NULL
+  double* part;          // [r][p] power of the bins (., p), with U
+};
 
-// One thread per (bin q, bin p, right-hand side r).  X[q][p][r][u] holds the
-// lattice DFT of the unknowns; E[r][q][p][2] receives (E_theta, E_phi), zero
-// outside the visible region u^2 + v^2 < 1.  wsign = +1 for the upper half
-// space (w = cos(theta) >= 0), -1 for the lower one.
-__global__ void far_field_kernel(const double2* __restrict__ X, const double* __restrict__ rho,
-                                 const double* __restrict__ area, const double* __restrict__ tan, int P, double pitch,
-                                 double k, int Lu, int Lv, int nrhs, double wsign, double2* __restrict__ E) {
-  const long long total = (long long)Lv * Lu * nrhs;
-  const int n = 4 * P;
-  for (long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x; t < total;
-       t += (long long)gridDim.x * blockDim.x) {
-    const int r = (int)(t % nrhs);
-    const long long bin = t / nrhs;
-    const int p = (int)(bin % Lu), q = (int)(bin / Lu);
-    const int ps = p < (Lu + 1) / 2 ? p : p - Lu;
-    const int qs = q < (Lv + 1) / 2 ? q : q - Lv;
-    const double u = 2.0 * 3.14159265358979323846 * ps / (Lu * k * pitch);
-    const double v = 2.0 * 3.14159265358979323846 * qs / (Lv * k * pitch);
-    double2* out = E + (((long long)r * Lv + q) * Lu + p) * 2;
-    const double s2 = u * u + v * v;
-    if (!(s2 < 1.0)) {
-      out[0] = double2{0.0, 0.0};
-      out[1] = double2{0.0, 0.0};
-      continue;
-    }
-    const double w = wsign * sqrt(1.0 - s2), st = sqrt(s2);
-    const double cp = st > 0.0 ? u / st : 1.0, sp = st > 0.0 ? v / st : 0.0;
-    const double th[3] = {w * cp, w * sp, -st};
-    const double ph[3] = {-sp, cp, 0.0};
-    const double2* xb = X + (bin * nrhs + r) * n;
-    double2 N[3] = {{0, 0}, {0, 0}, {0, 0}}, L[3] = {{0, 0}, {0, 0}, {0, 0}};
-    for (int i = 0; i < P; ++i) {
-      double sn, cs;
-      sincos(k * (u * rho[3 * i] + v * rho[3 * i + 1] + w * rho[3 * i + 2]), &sn, &cs);
-      const double2 ph_i{area[i] * cs, area[i] * sn};
-      const double2 j0 = cmul(ph_i, xb[2 * i]), j1 = cmul(ph_i, xb[2 * i + 1]);
-      const double2 m0 = cmul(ph_i, xb[2 * P + 2 * i]), m1 = cmul(ph_i, xb[2 * P + 2 * i + 1]);
-      const double* t0 = tan + 6 * i;
-      const double* t1 = t0 + 3;
+// One workgroup per (x bin p, right-hand side r), which owns the bins (q, p)
+// of all q.  It takes BT / 4 patches at a time: their 2 J and 2 M columns are
+// transformed along y in LDS (Lv points), then every thread adds the patches to
+// its bins, both half spaces at once.  A spectrum written by a y pass and read
+// by a projection of each half space is 403 MB at 64 x 57 elements, n_eq 192,
+// 2 RHS and 256 x 256 bins: 330 of 375 us per call, now 97 of 138 us (bound
+// by the FP64 sums of two workgroups per CU, whose spectra fill the LDS).  With a patch's phase split
+// into e^{jkux} (per workgroup), e^{jkvy} and e^{jkwz} (kept while the next
+// patch has the same y or z) the sums need few sincos:
+//   S = (t . (cp, sp, 0) J, t_z st J, t . phi^ J) summed over the tangents,
+//   R the same of M,
+//   E_theta += e^{jk..} (+-w S0 - S1 + R2),  E_phi += e^{jk..} (S2 -+ w R0 + R1)
+// with theta^ = (+-w cp, +-w sp, -st) above and below.  Bins outside the
+// visible region u^2 + v^2 < 1 are zero.
+template <int L>
+__global__ void __launch_bounds__((Shape<L, 1>::NT)) pattern_kernel(PatternArgs a) {
+  using SH = Shape<L, 1>;
+  constexpr int BT = SH::BT, NT = SH::NT, NBIN = (L + NT - 1) / NT, PC = BT / 4;
+  static_assert(BT % 4 == 0, "whole patches");
+  __shared__ double2 lds[L * BT];
+  __shared__ double2 phx[PC];
+  __shared__ double red[NT];
+  const int t = threadIdx.x, p = blockIdx.x, r = blockIdx.y, n = 4 * a.P;
+  const double pi = 3.14159265358979323846;
+  const int ps = p < (a.Lu + 1) / 2 ? p : p - a.Lu;
+  const double u = 2.0 * pi * ps / (a.Lu * a.k * a.pitch);
+  struct Bin {
+    double v, w, cp, sp, st;
+    double2 py, pz;               // e^{jkvy}, e^{jkwz}
+    double2 et[2], ep[2];         // above, below
+    bool vis;
+  } bin[NBIN];
 #pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        N[c].x += j0.x * t0[c] + j1.x * t1[c];
-        N[c].y += j0.y * t0[c] + j1.y * t1[c];
-        L[c].x += m0.x * t0[c] + m1.x * t1[c];
-        L[c].y += m0.y * t0[c] + m1.y * t1[c];
+  for (int j = 0; j < NBIN; ++j) {
+    const int q = t + NT * j, qs = q < (L + 1) / 2 ? q : q - L;
+    Bin& B = bin[j];
+    B.v = 2.0 * pi * qs / (L * a.k * a.pitch);
+    const double s2 = u * u + B.v * B.v;
+    B.vis = q < L && s2 < 1.0;
+    B.w = B.vis ? sqrt(1.0 - s2) : 1.0;
+    B.st = sqrt(s2);
+    B.cp = B.st > 0.0 ? u / B.st : 1.0;
+    B.sp = B.st > 0.0 ? B.v / B.st : 0.0;
+    B.py = B.pz = double2{1.0, 0.0};
+    B.et[0] = B.et[1] = B.ep[0] = B.ep[1] = double2{0.0, 0.0};
+  }
+  if (u * u < 1.0) {   // (the whole workgroup)
+    PassArgs f{};
+    f.n_in = a.ny;
+    f.n_out = L;
+    f.in_pt = a.Lu * a.nrhs * n;
+    f.sign = +1;
+    f.scale = 1.0;
+    const double2* Wl = a.W + ((long long)p * a.nrhs + r) * n;
+    double y0 = 0.0, z0 = 0.0;   // of the phases kept in bin (e^0 = 1)
+    const int b = t % BT, g = t / BT;
+    for (int pb = 0; pb < a.P; pb += PC) {
+      // column b: J of patch pb + b / 2 (b < BT / 2), then M
+      const int h = b < BT / 2 ? 0 : 1, cl = 2 * pb + b - h * (BT / 2);
+      run_stage<L, 1, 0, 0, 1, double2, double2, double2, true>(f, lds, Wl + h * 2 * a.P + cl, nullptr, a.tw,
+                                                                cl < 2 * a.P, b, g, GreenGen{}, 0, 0);
+      if (t < PC && pb + t < a.P) {
+        double sn, cs;
+        sincos(a.k * u * a.rho[3 * (pb + t)], &sn, &cs);
+        phx[t] = double2{a.area[pb + t] * cs, a.area[pb + t] * sn};
+      }
+      __syncthreads();
+      const int np = a.P - pb < PC ? a.P - pb : PC;
+      for (int i = 0; i < np; ++i) {
+        const double* rho = a.rho + 3 * (pb + i);
+        const double* t0 = a.tan + 6 * (pb + i);
+        const double y = rho[1], z = rho[2];
+        const bool ny = y != y0, nz = z != z0;
+        y0 = y;
+        z0 = z;
+#pragma unroll
+        for (int j = 0; j < NBIN; ++j) {
+          Bin& B = bin[j];
+          const int q = t + NT * j < L ? t + NT * j : 0;
+          if (ny) sincos(a.k * B.v * y, &B.py.y, &B.py.x);
+          if (nz) sincos(a.k * B.w * z, &B.pz.y, &B.pz.x);
+          const double2 pxy = cmul(phx[i], B.py);
+          const double2 up = cmul(pxy, B.pz), dn = cmul(pxy, double2{B.pz.x, -B.pz.y});
+          double2 S[2][3];
+#pragma unroll
+          for (int m = 0; m < 2; ++m) {
+            const double2 x0 = lds[lds_column<L, 1>(q, m * (BT / 2) + 2 * i)];
+            const double2 x1 = lds[lds_column<L, 1>(q, m * (BT / 2) + 2 * i + 1)];
+            const double e0 = t0[0] * B.cp + t0[1] * B.sp, e1 = t0[3] * B.cp + t0[4] * B.sp;
+            const double g0 = t0[2] * B.st, g1 = t0[5] * B.st;
+            const double f0 = t0[1] * B.cp - t0[0] * B.sp, f1 = t0[4] * B.cp - t0[3] * B.sp;
+            S[m][0] = double2{B.w * (e0 * x0.x + e1 * x1.x), B.w * (e0 * x0.y + e1 * x1.y)};
+            S[m][1] = double2{g0 * x0.x + g1 * x1.x, g0 * x0.y + g1 * x1.y};
+            S[m][2] = double2{f0 * x0.x + f1 * x1.x, f0 * x0.y + f1 * x1.y};
+          }
+          // theta: w S0 - S1 + R2 above, -w S0 - S1 + R2 below; phi: S2 - w R0 + R1 above, S2 + w R0 + R1 below
+          const double2 ct{S[1][2].x - S[0][1].x, S[1][2].y - S[0][1].y};
+          const double2 cf{S[0][2].x + S[1][1].x, S[0][2].y + S[1][1].y};
+          const double2 e[4] = {cmul(up, cadd(ct, S[0][0])), cmul(dn, csub(ct, S[0][0])),
+                                cmul(up, csub(cf, S[1][0])), cmul(dn, cadd(cf, S[1][0]))};
+          B.et[0] = cadd(B.et[0], e[0]);
+          B.et[1] = cadd(B.et[1], e[1]);
+          B.ep[0] = cadd(B.ep[0], e[2]);
+          B.ep[1] = cadd(B.ep[1], e[3]);
+        }
+      }
+      __syncthreads();   // every column is read before the next ones arrive
+    }
+  }
+  const double du = 2.0 * pi / (a.Lu * a.k * a.pitch), dv = 2.0 * pi / (L * a.k * a.pitch);
+  double power = 0.0;
+#pragma unroll
+  for (int j = 0; j < NBIN; ++j) {
+    const Bin& B = bin[j];
+    const int q = t + NT * j;
+    if (q >= L) continue;
+    if (a.E) {
+      double2* out = a.E + (((long long)r * L + q) * a.Lu + p) * 2;
+      out[0] = B.vis ? B.et[0] : double2{0.0, 0.0};
+      out[1] = B.vis ? B.ep[0] : double2{0.0, 0.0};
+    }
+    if (a.U) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const double U = B.vis ? B.et[h].x * B.et[h].x + B.et[h].y * B.et[h].y + B.ep[h].x * B.ep[h].x +
+                                     B.ep[h].y * B.ep[h].y
+                               : 0.0;
+        a.U[(((long long)r * 2 + h) * L + q) * a.Lu + p] = U;
+        power += U * du * dv / B.w;
       }
     }
-    double2 et{0, 0}, ep{0, 0};
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      et.x += N[c].x * th[c] + L[c].x * ph[c];
-      et.y += N[c].y * th[c] + L[c].y * ph[c];
-      ep.x += N[c].x * ph[c] - L[c].x * th[c];
-      ep.y += N[c].y * ph[c] - L[c].y * th[c];
-    }
-    out[0] = et;
-    out[1] = ep;
   }
-}
-
-// Radiation intensity U = |E_theta|^2 + |E_phi|^2 weighted by the solid angle
-// of its bin, du dv / |w|, summed per right-hand side over both half spaces:
-// one workgroup per (right-hand side, slice of bins), a fixed-order tree in
-// LDS, partial sums written per workgroup (the host adds them in order).
-constexpr int DIR_THREADS = 256;
-__global__ void __launch_bounds__(DIR_THREADS) power_partial_kernel(const double2* __restrict__ Eu,
-                                                                    const double2* __restrict__ El, int Lu, int Lv,
-                                                                    double pitch, double k, int slices,
-                                                                    double* __restrict__ partial) {
-  __shared__ double red[DIR_THREADS];
-  const int r = blockIdx.y, sl = blockIdx.x;
-  const long long bins = (long long)Lu * Lv;
-  const long long per = (bins + slices - 1) / slices;
-  const long long b0 = sl * per, b1 = b0 + per < bins ? b0 + per : bins;
-  const double pi = 3.14159265358979323846;
-  const double dudv = (2.0 * pi / (Lu * k * pitch)) * (2.0 * pi / (Lv * k * pitch));
-  double acc = 0.0;
-  for (long long b = b0 + threadIdx.x; b < b1; b += DIR_THREADS) {
-    const int p = (int)(b % Lu), q = (int)(b / Lu);
-    const int ps = p < (Lu + 1) / 2 ? p : p - Lu;
-    const int qs = q < (Lv + 1) / 2 ? q : q - Lv;
-    const double u = 2.0 * pi * ps / (Lu * k * pitch), v = 2.0 * pi * qs / (Lv * k * pitch);
-    const double s2 = u * u + v * v;
-    if (!(s2 < 1.0)) continue;
-    const double2* eu = Eu + ((long long)r * bins + b) * 2;
-    const double2* el = El + ((long long)r * bins + b) * 2;
-    const double U = eu[0].x * eu[0].x + eu[0].y * eu[0].y + eu[1].x * eu[1].x + eu[1].y * eu[1].y +
-                     el[0].x * el[0].x + el[0].y * el[0].y + el[1].x * el[1].x + el[1].y * el[1].y;
-    acc += U * dudv / sqrt(1.0 - s2);
-  }
-  red[threadIdx.x] = acc;
+  if (!a.U) return;
+  red[t] = power;
   __syncthreads();
-  for (int h = DIR_THREADS / 2; h > 0; h >>= 1) {
-    if (threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) partial[(long long)r * slices + sl] = red[0];
-}
-
-// D[r][h][q][p] = 4 pi U / P_rad[r] (zero outside the visible region)
-__global__ void directivity_kernel(const double2* __restrict__ Eu, const double2* __restrict__ El, int Lu, int Lv,
-                                   int nrhs, const double* __restrict__ prad, double* __restrict__ D) {
-  const long long bins = (long long)Lu * Lv, total = (long long)nrhs * 2 * bins;
-  for (long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x; t < total;
-       t += (long long)gridDim.x * blockDim.x) {
-    const long long b = t % bins;
-    const int h = (int)((t / bins) % 2), r = (int)(t / (2 * bins));
-    const double2* e = (h == 0 ? Eu : El) + ((long long)r * bins + b) * 2;
-    const double U = e[0].x * e[0].x + e[0].y * e[0].y + e[1].x * e[1].x + e[1].y * e[1].y;
-    D[t] = 4.0 * 3.14159265358979323846 * U / prad[r];
+  if (t < 64) {   // (fixed order: lane t adds its share, then a tree)
+    double s = 0.0;
+    for (int i = t; i < NT; i += 64) s += red[i];
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
+    if (t == 0) a.part[(long long)r * a.Lu + p] = s;
   }
 }
 
-// Lattice DFT of the unknowns (sign +1) into X[q][p][r][u]; W is the
-// half-transformed workspace
-void lattice_dft(const GreenGeomDev& g, int nx, int ny, int nrhs, int Lu, int Lv, const void* x_dev, void* W, void* X,
-                 hipStream_t s) {
-  const int n = 4 * g.n_patch;
+// D[r][h][q][p] holds the radiation intensity U and receives 4 pi U / P_rad[r],
+// P_rad[r] the sum of the Lu partial powers (every workgroup adds them in the
+// same order; the first of a right-hand side reports the sum)
+constexpr int DIR_THREADS = 256;
+__global__ void __launch_bounds__(DIR_THREADS) directivity_kernel(const double* __restrict__ part, int Lu,
+                                                                  long long per_rhs, double* __restrict__ D,
+                                                                  double* __restrict__ prad) {
+  __shared__ double sum;
+  const int r = blockIdx.y, t = threadIdx.x;
+  if (t < 64) {
+    double s = 0.0;
+    for (int i = t; i < Lu; i += 64) s += part[(long long)r * Lu + i];
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
+    if (t == 0) sum = s;
+  }
+  __syncthreads();
+  const double P = sum;
+  if (blockIdx.x == 0 && t == 0) prad[r] = P;
+  double* d = D + r * per_rhs;
+  for (long long i = blockIdx.x * (long long)DIR_THREADS + t; i < per_rhs; i += (long long)gridDim.x * DIR_THREADS)
+    d[i] = 4.0 * 3.14159265358979323846 * d[i] / P;
+}
+
+// x pass of the lattice DFT of the unknowns (sign +1) into W[iy][p][r][u]
+void lattice_dft_x(int n, int nx, int ny, int nrhs, int Lu, const void* x_dev, void* W, hipStream_t s) {
   const int64_t B = (int64_t)nrhs * n, M = (int64_t)nx * ny;
   FftPass fx;
   fx.L = Lu; fx.n_in = nx; fx.n_out = Lu; fx.batch = n;
@@ -149,23 +210,54 @@ void lattice_dft(const GreenGeomDev& g, int nx, int ny, int nrhs, int Lu, int Lv
   fx.out_s1 = n; fx.out_s0 = (int64_t)Lu * B; fx.out_pt = B;
   fx.sign = +1;
   launch_fft_pass(fx, Cx::C128, Cx::C128, Cx::C128, x_dev, W, twiddle_table(Lu, Cx::C128), s);
-  FftPass fy;
-  fy.L = Lv; fy.n_in = ny; fy.n_out = Lv; fy.batch = (int)B;
-  fy.n_lines = Lu; fy.nl0 = Lu;
-  fy.in_s0 = B; fy.in_pt = (int64_t)Lu * B;
-  fy.out_s0 = B; fy.out_pt = (int64_t)Lu * B;
-  fy.sign = +1;
-  launch_fft_pass(fy, Cx::C128, Cx::C128, Cx::C128, W, X, twiddle_table(Lv, Cx::C128), s);
 }
 
-void project(const GreenGeomDev& g, const void* X, int Lu, int Lv, int nrhs, double wsign, void* E, hipStream_t s) {
-  const long long total = (long long)Lv * Lu * nrhs;
-  long long grid = (total + 255) / 256;
-  if (grid > 65536) grid = 65536;
-  hipLaunchKernelGGL(far_field_kernel, dim3((unsigned)grid), dim3(256), 0, s, static_cast<const double2*>(X),
-                     g.rho, g.area, g.tan, g.n_patch,
-                     g.pitch, g.k, Lu, Lv, nrhs, wsign, static_cast<double2*>(E));
+void launch_pattern(int Lv, const PatternArgs& a, hipStream_t s) {
+  // the y transform addresses its input with 32-bit offsets
+  const int64_t B = (int64_t)a.nrhs * 4 * a.P;
+  EMS_CHECK_ARG(Lv * a.Lu * B + B + 1024 < (1LL << 31), "FFT line span exceeds 32-bit offsets");
+  const dim3 grid((unsigned)a.Lu, (unsigned)a.nrhs);
+  switch (Lv) {
+#define EMS_PATTERN(LL)                                                                                 \
+  case LL:                                                                                              \
+    hipLaunchKernelGGL((pattern_kernel<LL>), grid, dim3((unsigned)Shape<LL, 1>::NT), 0, s, a);          \
+    break;
+    EMS_PATTERN(2)
+    EMS_PATTERN(4)
+    EMS_PATTERN(8)
+    EMS_PATTERN(16)
+    EMS_PATTERN(32)
+    EMS_PATTERN(64)
+    EMS_PATTERN(128)
+    EMS_PATTERN(256)
+    EMS_PATTERN(512)
+    EMS_PATTERN(1024)
+    EMS_PATTERN(24)
+    EMS_PATTERN(48)
+    EMS_PATTERN(96)
+    EMS_PATTERN(192)
+    EMS_PATTERN(384)
+    EMS_PATTERN(768)
+#undef EMS_PATTERN
+    default: break;
+  }
   EMS_LAUNCH_CHECK();
+}
+
+PatternArgs pattern_args(const GreenGeomDev& g, int ny, int nrhs, int Lu, int Lv, const void* W) {
+  PatternArgs a{};
+  a.W = static_cast<const double2*>(W);
+  a.rho = g.rho;
+  a.area = g.area;
+  a.tan = g.tan;
+  a.tw = static_cast<const double2*>(twiddle_table(Lv, Cx::C128));
+  a.P = g.n_patch;
+  a.Lu = Lu;
+  a.ny = ny;
+  a.nrhs = nrhs;
+  a.pitch = g.pitch;
+  a.k = g.k;
+  return a;
 }
 
 void check_far_args(const emsurf_geom* geom, int32_t nx, int32_t ny, int32_t nrhs, int32_t Lu, int32_t Lv) {
@@ -189,12 +281,12 @@ extern "C" emsurf_status emsurf_far_field(const emsurf_geom* geom, int32_t nx, i
     hipStream_t s = static_cast<hipStream_t>(stream);
     GreenGeomDev g;
     upload_geom(geom, g, s);
-    const int64_t B = (int64_t)nrhs * 4 * g.n_patch;
-    const size_t b_w = (size_t)ny * Lu * B * 16, b_x = (size_t)Lv * Lu * B * 16;
-    Scratch ws(Scratch::round(b_w) + b_x);
-    void *W = ws.part(b_w), *X = ws.part(b_x);
-    lattice_dft(g, nx, ny, nrhs, Lu, Lv, x_dev, W, X, s);
-    project(g, X, Lu, Lv, nrhs, 1.0, E_dev, s);
+    const int n = 4 * g.n_patch;
+    Scratch ws((size_t)ny * Lu * nrhs * n * 16);
+    lattice_dft_x(n, nx, ny, nrhs, Lu, x_dev, ws.p, s);
+    PatternArgs a = pattern_args(g, ny, nrhs, Lu, Lv, ws.p);
+    a.E = static_cast<double2*>(E_dev);
+    launch_pattern(Lv, a, s);
     EMS_HIP(hipStreamSynchronize(s));
     ws.idle();
     g.idle();
@@ -213,37 +305,28 @@ extern "C" emsurf_status emsurf_directivity(const emsurf_geom* geom, int32_t nx,
     hipStream_t s = static_cast<hipStream_t>(stream);
     GreenGeomDev g;
     upload_geom(geom, g, s);
-    const int64_t B = (int64_t)nrhs * 4 * g.n_patch, bins = (int64_t)Lu * Lv;
-    const int slices = 64;
-    const size_t b_w = (size_t)ny * Lu * B * 16, b_x = (size_t)Lv * Lu * B * 16, b_e = (size_t)nrhs * bins * 32;
-    const size_t b_part = (size_t)nrhs * slices * 8, b_prad = (size_t)nrhs * 8;
-    Scratch ws(Scratch::round(b_w) + Scratch::round(b_x) + 2 * Scratch::round(b_e) + Scratch::round(b_part) + b_prad);
-    void *W = ws.part(b_w), *X = ws.part(b_x);
-    double2 *Eu = ws.part<double2>(b_e), *El = ws.part<double2>(b_e);
+    const int n = 4 * g.n_patch;
+    const size_t b_w = (size_t)ny * Lu * nrhs * n * 16, b_part = (size_t)nrhs * Lu * 8, b_prad = (size_t)nrhs * 8;
+    Scratch ws(Scratch::round(b_w) + Scratch::round(b_part) + b_prad);
+    void* W = ws.part(b_w);
     double *part = ws.part<double>(b_part), *prad = ws.part<double>(b_prad);
-    lattice_dft(g, nx, ny, nrhs, Lu, Lv, x_dev, W, X, s);
-    project(g, X, Lu, Lv, nrhs, 1.0, Eu, s);
-    project(g, X, Lu, Lv, nrhs, -1.0, El, s);
-    hipLaunchKernelGGL(power_partial_kernel, dim3(slices, (unsigned)nrhs), dim3(DIR_THREADS), 0, s,
-                       Eu, El, Lu, Lv, g.pitch, g.k, slices, part);
+    lattice_dft_x(n, nx, ny, nrhs, Lu, x_dev, W, s);
+    PatternArgs a = pattern_args(g, ny, nrhs, Lu, Lv, W);
+    a.U = static_cast<double*>(D_dev);
+    a.part = part;
+    launch_pattern(Lv, a, s);
+    const long long per_rhs = (long long)2 * Lu * Lv;
+    const long long blocks = (per_rhs + 4 * DIR_THREADS - 1) / (4 * DIR_THREADS);
+    hipLaunchKernelGGL(directivity_kernel, dim3((unsigned)(blocks < 4096 ? blocks : 4096), (unsigned)nrhs),
+                       dim3(DIR_THREADS), 0, s, part, Lu, per_rhs, static_cast<double*>(D_dev), prad);
     EMS_LAUNCH_CHECK();
-    std::vector<double> hp((size_t)nrhs * slices), pr(nrhs, 0.0);
-    EMS_HIP(hipMemcpyAsync(hp.data(), part, hp.size() * 8, hipMemcpyDeviceToHost, s));
-    EMS_HIP(hipStreamSynchronize(s));
-    for (int r = 0; r < nrhs; ++r) {
-      for (int sl = 0; sl < slices; ++sl) pr[r] += hp[(size_t)r * slices + sl];
-      EMS_CHECK_ARG(pr[r] > 0 && std::isfinite(pr[r]), "the currents radiate no power (zero or non-finite x)");
-    }
-    EMS_HIP(hipMemcpyAsync(prad, pr.data(), (size_t)nrhs * 8, hipMemcpyHostToDevice, s));
-    const long long total = (long long)nrhs * 2 * bins;
-    long long grid = (total + 255) / 256;
-    if (grid > 65536) grid = 65536;
-    hipLaunchKernelGGL(directivity_kernel, dim3((unsigned)grid), dim3(256), 0, s, Eu, El, Lu, Lv,
-                       nrhs, prad, static_cast<double*>(D_dev));
-    EMS_LAUNCH_CHECK();
+    std::vector<double> pr(nrhs, 0.0);
+    EMS_HIP(hipMemcpyAsync(pr.data(), prad, b_prad, hipMemcpyDeviceToHost, s));
     EMS_HIP(hipStreamSynchronize(s));
     ws.idle();
     g.idle();
+    for (int r = 0; r < nrhs; ++r)
+      EMS_CHECK_ARG(pr[r] > 0 && std::isfinite(pr[r]), "the currents radiate no power (zero or non-finite x)");
     if (prad_host)
       for (int r = 0; r < nrhs; ++r) prad_host[r] = pr[r];
     return EMSURF_OK;

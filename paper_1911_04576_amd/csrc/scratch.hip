@@ -1,7 +1,7 @@
 // Device memory of one library call.  hipMalloc is cheap, but hipFree waits
 // for the device and, once a process has freed some GB, took 25 ms per GB here
 // (up to 200 ms for 8 GB): a directivity call at 64 x 57 elements, 0.4 ms of
-// kernels, took 16 to 18 ms with its 0.5 GB freed at the end, and takes 0.37 ms
+// kernels, took 16 to 18 ms with its 0.5 GB freed at the end, and took 0.37 ms
 // with the block kept; macromodels of 32 types of 288 + 576 unknowns 4.31 and
 // 3.94 ms.
 #include <algorithm>
