@@ -15,6 +15,8 @@
 // right-hand-side counts may be processed in several passes.  The FP32
 // many-right-hand-side form on the matrix cores is in blockprod_mfma.hip;
 // launch_block_product_variant below chooses between them.
+#include <type_traits>
+
 #include "internal.h"
 
 namespace emsurf {
@@ -98,7 +100,9 @@ __device__ __forceinline__ void store_run(double2* __restrict__ dst, const doubl
 // previous U are multiplied.  LDS holds the spectral columns as xs[v][NR] for
 // v < npad = n rounded up to U (rows past n zero) and afterwards stages the
 // outputs as [r][u] for contiguous stores.
-template <typename V, int NR, int U>
+// KS: groups of wavefronts that share the rows and split the columns, their
+// sums added through LDS (few frequencies, see gemv_split).
+template <typename V, int NR, int U, int KS>
 __global__ void __launch_bounds__(512) block_gemv_kernel(const V* __restrict__ That, const V* __restrict__ xh, V* __restrict__ yh, int n,
                                                          int nrhs, int r0, int nr) {
   using T = typename Real<V>::T;
@@ -106,7 +110,11 @@ __global__ void __launch_bounds__(512) block_gemv_kernel(const V* __restrict__ T
   V* xs = reinterpret_cast<V*>(smem_raw);  // [npad][NR], later [nr][n]
   const long long k = blockIdx.x;
   const int npad = (n + U - 1) / U * U;
-  const int u = threadIdx.x;
+  const int lanes = blockDim.x / KS, part = KS > 1 ? threadIdx.x / lanes : 0, u = threadIdx.x - part * lanes;
+  // this group's columns, in whole stages (vend <= npad); a share is a multiple
+  // of 8 whatever U, which follows NR: the sums must not
+  const int per = KS > 1 ? (n + 8 * KS - 1) / (8 * KS) * 8 : npad;
+  const int vbeg = part * per < npad ? part * per : npad, vend = vbeg + per < npad ? vbeg + per : npad;
   const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
       (void*)(That + k * (long long)n * n), (short)0, n * n * (int)sizeof(V), 0x00020000);
   // lanes past the last row stream row n - 1 and store nothing
@@ -114,7 +122,7 @@ __global__ void __launch_bounds__(512) block_gemv_kernel(const V* __restrict__ T
   const int col_bytes = n * (int)sizeof(V);
   // the first columns are requested before the spectral columns are staged
   V acur[U], anxt[U];
-  gemv_fetch<V, U>(acur, rs, voff, 0, n, col_bytes);
+  gemv_fetch<V, U>(acur, rs, voff, vbeg, n, col_bytes);
   const V* xk = xh + k * (long long)nrhs * n + (long long)r0 * n;
   for (int i = threadIdx.x; i < NR * npad; i += blockDim.x) {
     const int r = i / npad, v = i - r * npad;
@@ -125,16 +133,35 @@ __global__ void __launch_bounds__(512) block_gemv_kernel(const V* __restrict__ T
 #pragma unroll
   for (int r = 0; r < NR; ++r) { ar[r] = 0; ai[r] = 0; }
   // two register stages used alternately (no copies between them)
-  for (int v0 = 0; v0 < npad; v0 += 2 * U) {
+  for (int v0 = vbeg; v0 < vend; v0 += 2 * U) {
     gemv_fetch<V, U>(anxt, rs, voff, v0 + U, n, col_bytes);
     __builtin_amdgcn_sched_barrier(0);
     gemv_stage_mac<V, NR, U>(acur, xs + v0 * NR, ar, ai);
     gemv_fetch<V, U>(acur, rs, voff, v0 + 2 * U, n, col_bytes);
     __builtin_amdgcn_sched_barrier(0);
-    if (v0 + U < npad) gemv_stage_mac<V, NR, U>(anxt, xs + (v0 + U) * NR, ar, ai);
+    if (v0 + U < vend) gemv_stage_mac<V, NR, U>(anxt, xs + (v0 + U) * NR, ar, ai);
   }
   __syncthreads();
-  if (u < n) {
+  if constexpr (KS > 1) {
+    // the groups' sums, a right-hand side at a time: [part][u] after the
+    // outputs' place
+    V* sums = xs + NR * npad;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      if (u < n) sums[part * n + u] = V{ar[r], ai[r]};
+      __syncthreads();
+      if (part == 0 && u < n && r < nr) {
+        V t = sums[u];
+#pragma unroll
+        for (int q = 1; q < KS; ++q) {
+          t.x += sums[q * n + u].x;
+          t.y += sums[q * n + u].y;
+        }
+        xs[r * n + u] = t;
+      }
+      __syncthreads();
+    }
+  } else if (u < n) {
 #pragma unroll
     for (int r = 0; r < NR; ++r)
       if (r < nr) xs[r * n + u] = V{ar[r], ai[r]};
@@ -149,6 +176,13 @@ template <typename V, int NR> constexpr int gemv_stage() {
   return sizeof(V) == 8 ? (NR <= 8 ? 8 : 4) : (NR <= 4 ? 4 : 2);
 }
 
+// Groups that split a block's columns, by the plan alone (a column's sum must
+// not depend on the other right-hand sides).  With fewer workgroups than two
+// per CU a block's stream is latency: 64 frequencies of 96 unknowns in FP64 took
+// 5.8 us with one group, 4.8 us with four.
+constexpr int64_t SPLIT_FREQ = 512;
+inline int gemv_split(int n, int64_t P) { return P > SPLIT_FREQ ? 1 : n <= 128 ? 4 : n <= 256 ? 2 : 1; }
+
 template <typename V, int NR>
 void launch_nr(const void* That, const void* xh, void* yh, int n, int nrhs, int r0, int nr, int64_t P,
                hipStream_t s) {
@@ -156,8 +190,17 @@ void launch_nr(const void* That, const void* xh, void* yh, int n, int nrhs, int 
   const int threads = ((n + 63) / 64) * 64;
   const int npad = (n + U - 1) / U * U;
   const size_t shm = (size_t)npad * NR * sizeof(V);
-  hipLaunchKernelGGL((block_gemv_kernel<V, NR, U>), dim3((unsigned)P), dim3(threads), shm, s,
-                     static_cast<const V*>(That), static_cast<const V*>(xh), static_cast<V*>(yh), n, nrhs, r0, nr);
+  auto launch = [&](auto ks) {
+    constexpr int KS = decltype(ks)::value;
+    hipLaunchKernelGGL((block_gemv_kernel<V, NR, U, KS>), dim3((unsigned)P), dim3(threads * KS),
+                       shm + (KS > 1 ? (size_t)KS * n * sizeof(V) : 0), s, static_cast<const V*>(That),
+                       static_cast<const V*>(xh), static_cast<V*>(yh), n, nrhs, r0, nr);
+  };
+  switch (gemv_split(n, P)) {
+    case 4: launch(std::integral_constant<int, 4>{}); break;
+    case 2: launch(std::integral_constant<int, 2>{}); break;
+    default: launch(std::integral_constant<int, 1>{}); break;
+  }
 }
 
 template <typename V>

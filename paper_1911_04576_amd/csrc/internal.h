@@ -177,6 +177,14 @@ int fft_length_at_least(int v);
 // Launch a pass. tin/tcomp/tout select element types of input, arithmetic and output.
 void launch_fft_pass(const FftPass& p, Cx tin, Cx tcomp, Cx tout, const void* in, void* out,
                      const void* twiddles, hipStream_t s);
+// Both axes at once for lattices whose padded lengths fit (a rule on the
+// lattice alone): forward (sign -1) x[r][iy][ix][u] -> X[ky][kx][r][u], inverse
+// (+1) Y[ky][kx][r][u] -> y[r][iy][ix][u], scaled by 1 / (Lx Ly).
+struct SmallDft {
+  int nx, ny, Lx, Ly, n, nrhs, sign;
+};
+bool small_dft_fits(int Lx, int Ly);
+void launch_small_dft(const SmallDft& d, Cx tin, Cx tout, const void* in, void* out, hipStream_t s);
 struct GreenGeomDev;
 // x pass of the kernel transform (FP64) whose inputs are the point-sampled
 // coupling entries of columns [c0, c0 + p.batch), generated in the first stage

@@ -179,6 +179,8 @@ void apply_T_bufs(emsurf_plan p, Cx tin, Cx tc, Cx tout, int nrhs, const void* x
     if (timed) ::emsurf::timer_begin(pp, phase, ss, end_out);
   };
 
+  // small lattices transform both axes in one launch (timed as phases 0 and 4)
+  const bool small = small_dft_fits(Lx, Ly);
   // forward along x: lines (r, iy); x[r][iy][ix][u] -> W[iy][kx][r][u]
   FftPass fx;
   fx.L = Lx; fx.n_in = Nx; fx.n_out = Lx; fx.batch = n;
@@ -187,7 +189,10 @@ void apply_T_bufs(emsurf_plan p, Cx tin, Cx tc, Cx tout, int nrhs, const void* x
   fx.out_s1 = n; fx.out_s0 = (int64_t)Lx * B; fx.out_pt = B;
   fx.sign = -1;
   timer_begin(p, 0, s, &e);
-  launch_fft_pass(fx, tin, tc, tc, x, w.W, twx, s);
+  if (small)
+    launch_small_dft(SmallDft{Nx, Ny, Lx, Ly, n, nrhs, -1}, tin, tc, x, w.X, s);
+  else
+    launch_fft_pass(fx, tin, tc, tc, x, w.W, twx, s);
   timer_end(e, s);
 
   // forward along y: lines kx; W[iy][kx][b] -> X[ky][kx][b]
@@ -198,7 +203,7 @@ void apply_T_bufs(emsurf_plan p, Cx tin, Cx tc, Cx tout, int nrhs, const void* x
   fy.out_s0 = B; fy.out_pt = (int64_t)Lx * B;
   fy.sign = -1;
   timer_begin(p, 1, s, &e);
-  launch_fft_pass(fy, tc, tc, tc, w.W, w.X, twy, s);
+  if (!small) launch_fft_pass(fy, tc, tc, tc, w.W, w.X, twy, s);
   timer_end(e, s);
 
   // Fourier-domain block products
@@ -224,7 +229,7 @@ void apply_T_bufs(emsurf_plan p, Cx tin, Cx tc, Cx tout, int nrhs, const void* x
   FftPass iy = fy;
   iy.n_in = Ly; iy.n_out = Ny; iy.sign = +1;
   timer_begin(p, 3, s, &e);
-  launch_fft_pass(iy, tc, tc, tc, w.Y, w.W, twy, s);
+  if (!small) launch_fft_pass(iy, tc, tc, tc, w.Y, w.W, twy, s);
   timer_end(e, s);
 
   // inverse along x, keep ix < Nx, scale 1/(Lx Ly)
@@ -236,7 +241,10 @@ void apply_T_bufs(emsurf_plan p, Cx tin, Cx tc, Cx tout, int nrhs, const void* x
   ix.sign = +1;
   ix.scale = 1.0 / ((double)Lx * (double)Ly);
   timer_begin(p, 4, s, &e);
-  launch_fft_pass(ix, tc, tc, tout, w.W, y, twx, s);
+  if (small)
+    launch_small_dft(SmallDft{Nx, Ny, Lx, Ly, n, nrhs, +1}, tc, tout, w.Y, y, s);
+  else
+    launch_fft_pass(ix, tc, tc, tout, w.W, y, twx, s);
   timer_end(e, s);
 }
 
