@@ -324,8 +324,10 @@ __host__ __device__ inline int64_t bf16_offset(int n, int u, int v, int p) {
 // ----------------------------------------------------------------------------- S apply
 struct TypeTiles {
   DevBuf elem_sorted;   // int32 [M] elements sorted by type
-  DevBuf tiles;         // int32 [n_tiles][3] = (type, start in elem_sorted, count)
+  DevBuf tiles;         // int32 [n_tiles][3] = (type, start in elem_sorted, count), then [n_groups][3]
   int n_tiles = 0;
+  int n_groups = 0, group_max = 0;   // larger runs of one type, for the matrix-core apply
+  std::vector<int> group_count;
 };
 // y[r][m] = (axpy ? x_axpy[r][m] - : ) S_{type(m)} t[r][m]
 // types: S store type; t type; x_axpy and y types (FP64 or FP32 per ty/tx).

@@ -327,21 +327,31 @@ void build_tiles(emsurf_plan p, const int32_t* elem_type, hipStream_t s) {
     order[m] = m;
   }
   std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return elem_type[a] < elem_type[b]; });
-  const int TC = 32;
   std::vector<int> tiles;
-  int i = 0;
-  while (i < M) {
-    const int t = elem_type[order[i]];
-    int j = i;
-    while (j < M && elem_type[order[j]] == t) ++j;
-    for (int a = i; a < j; a += TC) {
-      tiles.push_back(t);
-      tiles.push_back(a);
-      tiles.push_back(std::min(TC, j - a));
+  // runs of at most top elements of one type: (type, start, count)
+  auto runs = [&](int top, int* longest) {
+    int count = 0;
+    *longest = 0;
+    for (int i = 0, j; i < M; i = j) {
+      const int t = elem_type[order[i]];
+      for (j = i; j < M && j - i < top && elem_type[order[j]] == t;) ++j;
+      tiles.insert(tiles.end(), {t, i, j - i});
+      *longest = std::max(*longest, j - i);
+      ++count;
     }
-    i = j;
+    return count;
+  };
+  int longest;
+  p->tiles.n_tiles = runs(32, &longest);
+  // groups of the matrix-core apply: the longest of 256, 128, 64, 32 elements
+  // whose groups are at least half full in all (its grid counts full groups)
+  for (int top = 256;; top /= 2) {
+    const size_t at = tiles.size();
+    p->tiles.n_groups = runs(top, &p->tiles.group_max);
+    if (top == 32 || (int64_t)p->tiles.n_groups * p->tiles.group_max <= 2 * (int64_t)M) break;
+    tiles.resize(at);
   }
-  p->tiles.n_tiles = (int)(tiles.size() / 3);
+  for (int g = 0; g < p->tiles.n_groups; ++g) p->tiles.group_count.push_back(tiles[3 * (size_t)(p->tiles.n_tiles + g) + 2]);
   p->tiles.elem_sorted.alloc(order.size() * sizeof(int));
   p->tiles.tiles.alloc(tiles.size() * sizeof(int));
   EMS_HIP(hipMemcpyAsync(p->tiles.elem_sorted.p, order.data(), order.size() * sizeof(int), hipMemcpyHostToDevice, s));

@@ -157,9 +157,10 @@ template <> struct SM<double> {
 };
 
 constexpr int SA_THREADS = 256;
-constexpr int SA_UT = 8;      // row tiles of 8 per workgroup (64 rows)
-// columns per workgroup: two wavefronts across, CTW column tiles of 16 each
-template <int CTW> constexpr int sa_cols() { return 32 * CTW; }
+// Workgroup tile: two wavefronts across the columns (one column tile of 16
+// each) by two across the rows (RT row tiles of 8 each, interleaved)
+constexpr int SA_COLS = 32;
+template <int RT> constexpr int sa_rows() { return 16 * RT; }
 
 __host__ __device__ inline int s_row_tiles(int n) { return (n + 7) / 8; }
 __host__ __device__ inline int s_k_tiles(int n) { return (n + 15) / 16; }
@@ -192,200 +193,208 @@ __global__ void pack_S_kernel(const double2* __restrict__ S, T* __restrict__ out
   }
 }
 
-// Work items w = (type tile * nub + row block) * ncb + column block, in type
-// order.  Workgroups go to the 8 XCDs in turn (workgroup b to XCD b % 8), so
-// XCD x takes the contiguous items [x per, (x + 1) per): the workgroups an
-// XCD holds at a time share a few macromodel slices in its L2.  Wavefront
-// (wc, wu) = (w % 2, w / 2) takes column tiles CTW wc .. CTW wc + CTW - 1 and
-// row tiles 4 wu .. 4 wu + 3 of the item.
-template <typename T, typename VX, int CTW>
-__global__ void __launch_bounds__(SA_THREADS, sizeof(T) == 8 ? 3 : 2) apply_S_mfma_kernel(
-    const T* __restrict__ Sp, const int* __restrict__ elem_sorted, const int* __restrict__ tiles, int n, int M,
-    int nrhs, int ncb, int nub, int items, int per, const typename SM<T>::V2* __restrict__ t,
+// first item of each XCD
+struct XcdItems { int first[9]; };
+
+// Work items w = (group * ncb + column block) * nub + row block; a group is up
+// to 256 elements of one type and its columns are its (right-hand side,
+// element) pairs, so that a type has few part-empty column blocks.  Workgroups
+// go to the 8 XCDs in turn (workgroup b to XCD b % 8) and XCD x takes the
+// items from first[x]: those that an XCD holds at a time share macromodels in
+// its L2.  Wavefront (wc, wu) = (w % 2, w / 2) takes column tile wc and row
+// tiles wu, wu + 2, .. of the item.
+//
+// Bound by the matrix cores with many columns, by latency with few.  So a
+// column's vector offset is looked up once into LDS (not divided out by every
+// thread), loads carry no conditions, operands leave LDS a chunk ahead of
+// their products, and a small tile fills the chip early: 32 x 32 outputs are
+// as fast as 64 x 64 even where there is work for both.  y = S t, 64 rows x 64
+// columns (FP64 32) before: 4 x 4 elements, n_eq 96, 1 right-hand side, FP32
+// 11.9 -> 5.8 us, FP64 12.9 -> 9.0; 48 x 40, n_eq 96, 12: 40 -> 26, 64 -> 50;
+// 61 x 61, n_eq 288, 12: 332 -> 301 (98 TFLOP/s), 650 -> 596.
+template <typename T, typename VX, int RT>
+__global__ void __launch_bounds__(SA_THREADS, 3) apply_S_mfma_kernel(
+    const T* __restrict__ Sp, const int* __restrict__ elem_sorted, const int* __restrict__ groups, int n, int M,
+    int nrhs, int ncb, int nub, XcdItems span, const typename SM<T>::V2* __restrict__ t,
     const VX* __restrict__ x_axpy, VX* __restrict__ y) {
   using V2 = typename SM<T>::V2;
   using C = typename SM<T>::C;
   using Acc = typename SM<T>::Acc;
   using R = typename Real<VX>::T;
   constexpr int CH = 16 / (int)sizeof(T), NCH = 8 / CH;
-  constexpr int NCOL = sa_cols<CTW>(), NAC = (NCOL + 63) / 64;   // columns staged per thread
-  constexpr int NBC = SA_UT * 512 / CH / SA_THREADS;   // macromodel chunks staged per thread
+  constexpr int NCOL = SA_COLS, ROWS = sa_rows<RT>(), UT = 2 * RT;
+  constexpr int VPT = 2, TPC = 16 / VPT;               // values of a column staged per thread, threads per column
+  constexpr int NBC = UT * 512 / CH / SA_THREADS;      // macromodel chunks staged per thread
   // a k-tile of the vectors in A-lane order and of the packed macromodels;
   // two buffers: the next k-tile is staged while the current one is used.
   // At the end the same memory holds the output tile, rows of YROW values
-  // (64 rows u x (re, im) and padding: the rows start 16 banks apart)
-  // (FP64 keeps one macromodel buffer: 48 KB of LDS, three workgroups per CU,
+  // (the rows u x (re, im) and padding)
+  // (FP64 with RT = 3 keeps one macromodel buffer, three workgroups per CU,
   // for a second barrier per k-tile)
-  constexpr int NB = sizeof(T) == 8 ? 1 : 2;
-  constexpr int AS = 2 * CTW * 512, BS = SA_UT * 512;
-  constexpr int YROW = sizeof(T) == 4 ? 132 : 144;
+  constexpr int NB = sizeof(T) == 8 && RT > 2 ? 1 : 2;
+  constexpr int AS = 2 * 512, BS = UT * 512;
+  constexpr int YROW = 2 * ROWS + (sizeof(T) == 4 ? 4 : 16);
   constexpr int LDS_T = 2 * AS + NB * BS > NCOL * YROW ? 2 * AS + NB * BS : NCOL * YROW;
   __shared__ __align__(16) T lds[LDS_T];
+  __shared__ long long cbase[NCOL];   // vector offset of each column, -1 past the last
   auto As = [&](int bf) { return lds + bf * AS; };
   auto Bs = [&](int bf) { return lds + 2 * AS + (NB == 2 ? bf : 0) * BS; };
-  const int w = (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
-  if (w >= items) return;   // the whole workgroup: no barrier reached
-  const int cb = w % ncb, tub = w / ncb, tile = tub / nub, ub = tub - tile * nub;
-  const int type = tiles[3 * tile], start = tiles[3 * tile + 1], count = tiles[3 * tile + 2];
+  const int w = span.first[blockIdx.x % 8] + (int)(blockIdx.x / 8);
+  if (w >= span.first[blockIdx.x % 8 + 1]) return;   // the whole workgroup: no barrier reached
+  const int ub = w % nub, gcb = w / nub, grp = gcb / ncb, cb = gcb - grp * ncb;
+  const int type = groups[3 * grp], start = groups[3 * grp + 1], count = groups[3 * grp + 2];
   const int ncols = nrhs * count, col0 = cb * NCOL;
   if (col0 >= ncols) return;   // the whole workgroup: no barrier reached
   const int nut = s_row_tiles(n), nvt = s_k_tiles(n);
-  const int ut0 = ub * SA_UT;
+  const int ut0 = ub * UT;
   const T* St = Sp + (long long)type * nut * nvt * 512;
-  const int tid = threadIdx.x, l = tid & 63, wv = tid >> 6, wc = wv & 1, wu = wv >> 1;
-  // A staging: columns ac + 64 g of the block, source indices 4 aq .. 4 aq + 3 of the k-tile
-  const int ac = tid >> 2, aq = tid & 3;
-  // Element indices of the block's columns: the input columns of this
-  // thread's A staging (NAC) and the output chunks' columns (NXC), loaded
-  // at a clamped index without conditions and all before the first is used
-  // (the compiler barrier keeps them from sinking into the conditional
-  // blocks that use them, where each would cost a wait of its own)
-  constexpr int XC = 16 / (2 * (int)sizeof(R)), CPC = 64 / XC, NXC = NCOL * CPC / SA_THREADS;
-  int el_a[NAC], el_x[NXC];
-#pragma unroll
-  for (int g = 0; g < NAC; ++g) {
-    const int acol = col0 + ac + 64 * g;
-    const bool ok = ac + 64 * g < NCOL && acol < ncols;
-    el_a[g] = elem_sorted[start + (ok ? acol % count : 0)];
-  }
-#pragma unroll
-  for (int k = 0; k < NXC; ++k) {
-    const int col = col0 + (tid + SA_THREADS * k) / CPC;
-    el_x[k] = elem_sorted[start + (col < ncols ? col % count : 0)];
-  }
-  asm volatile("" ::: "memory");
-  const V2* tcol[NAC];
-#pragma unroll
-  for (int g = 0; g < NAC; ++g) {
-    const int acol = col0 + ac + 64 * g;
-    const bool ok = ac + 64 * g < NCOL && acol < ncols;
-    tcol[g] = ok ? t + ((long long)(acol / count) * M + el_a[g]) * n : nullptr;
-  }
-  V2 an[NAC][4];
-  auto load_a = [&](int vt) {
-#pragma unroll
-    for (int g = 0; g < NAC; ++g)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int v = vt * 16 + 4 * aq + i;
-        an[g][i] = (tcol[g] != nullptr && v < n) ? tcol[g][v] : V2{0, 0};
-      }
-  };
-  // the workgroup's SA_UT row tiles of the packed macromodels (zero past n)
+  const int tid = threadIdx.x, l = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), wc = wv & 1, wu = wv >> 1;
+  // macromodel chunks of this thread (a row tile past the last repeats it; nothing stores its rows)
   C bn[NBC];
-  auto load_b = [&](int vt) {
+  unsigned boff[NBC];   // bytes from the type's macromodel (at most 16 MB)
 #pragma unroll
-    for (int j = 0; j < NBC; ++j) {
-      const int ci = tid + SA_THREADS * j, bu = ci / (512 / CH), wi = ci - bu * (512 / CH);
-      bn[j] = ut0 + bu < nut ? *reinterpret_cast<const C*>(St + ((long long)(ut0 + bu) * nvt + vt) * 512 + wi * CH)
-                             : C{};
+  for (int j = 0; j < NBC; ++j) {
+    const int ci = tid + SA_THREADS * j, bu = ci / (512 / CH), wi = ci - bu * (512 / CH);
+    boff[j] = (unsigned)(min(ut0 + bu, nut - 1) * nvt * 512 + wi * CH) * (unsigned)sizeof(T);
+  }
+  auto load_b = [&](int vt) {
+    const char* base = reinterpret_cast<const char*>(St + vt * 512);
+#pragma unroll
+    for (int j = 0; j < NBC; ++j) bn[j] = *reinterpret_cast<const C*>(base + boff[j]);
+  };
+  load_b(0);
+  if (tid < NCOL) {
+    const int col = col0 + tid, r = col / count;
+    cbase[tid] = col < ncols ? ((long long)r * M + elem_sorted[start + col - r * count]) * n : -1;
+  }
+  __syncthreads();
+  // A staging: column ac, source indices VPT aq .. VPT aq + VPT - 1 of the k-tile (columns past the last repeat it)
+  const int ac = tid / TPC, aq = tid % TPC;
+  const V2* tcol = t + cbase[min(ac, ncols - 1 - col0)];
+  V2 an[VPT];
+  auto load_a = [&](int vt) {
+    const int v = vt * 16 + VPT * aq;
+    if (vt * 16 + 16 <= n) {
+      // 16 bytes a load, at the alignment of a complex value
+      typedef T CU __attribute__((ext_vector_type(CH), aligned(2 * sizeof(T))));
+#pragma unroll
+      for (int i = 0; i < VPT * 2 / CH; ++i) {
+        const CU x = *(reinterpret_cast<const CU*>(tcol + v) + i);
+#pragma unroll
+        for (int z = 0; z < CH / 2; ++z) an[i * CH / 2 + z] = V2{x[2 * z], x[2 * z + 1]};
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < VPT; ++i) {
+        const V2 x = tcol[min(v + i, n - 1)];
+        an[i] = V2{v + i < n ? x.x : T(0), v + i < n ? x.y : T(0)};
+      }
     }
   };
-  // A-lane position of this thread's values: lane (2 h + p) 16 + ac % 16 of column tile ac / 16 + 4 g
-  const int ah = aq >> 1, as0 = 4 * (aq & 1), act = ac >> 4, a16 = ac & 15;
-  Acc acc[CTW][4];
+  Acc acc[RT];
 #pragma unroll
-  for (int i = 0; i < CTW; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = Acc{};
-  R* yr = reinterpret_cast<R*>(y);
-  const R* xr = reinterpret_cast<const R*>(x_axpy);
+  for (int j = 0; j < RT; ++j) acc[j] = Acc{};
   // stage the k-tile held in an and bn into LDS buffer bf (whose previous
-  // contents every wavefront has used: a barrier lies between)
+  // contents every wavefront has used: a barrier lies between).  A-lane
+  // position of value (h, s): lane (2 h + p) 16 + ac % 16 of column tile ac / 16
   auto stage = [&](int bf) {
+    T* dst = As(bf) + (ac >> 4) * 512;
 #pragma unroll
-    for (int g = 0; g < NAC; ++g)
+    for (int p = 0; p < 2; ++p) {
+      const int vq = VPT * aq, L = (2 * (vq >> 3) + p) * 16 + (ac & 15), s0 = vq & 7;
 #pragma unroll
-      for (int p = 0; p < 2; ++p) {
-        if (ac + 64 * g >= NCOL) break;
-        const int L = (2 * ah + p) * 16 + a16;
-        T* dst = As(bf) + (act + 4 * g) * 512;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int s = as0 + i;
-          dst[(s / CH) * 64 * CH + L * CH + s % CH] = p == 0 ? an[g][i].x : an[g][i].y;
-        }
-      }
+      for (int i = 0; i < VPT; ++i)
+        dst[((s0 + i) / CH) * 64 * CH + L * CH + (s0 + i) % CH] = p == 0 ? an[i].x : an[i].y;
+    }
 #pragma unroll
     for (int j = 0; j < NBC; ++j) *reinterpret_cast<C*>(Bs(bf) + (tid + SA_THREADS * j) * CH) = bn[j];
   };
-  // the products of the k-tile staged in buffer bf
-  auto products = [&](int bf) {
-    C a[CTW][NCH], b[4][NCH];
+  // the products of the k-tile staged in buffer bf, a 16-byte chunk of the
+  // operands at a time with the next on its way; mid() runs half way
+  auto products = [&](int bf, auto mid) {
+    C a[2], b[2][RT];
+    auto fetch = [&](int m) {
+      a[m & 1] = *reinterpret_cast<const C*>(As(bf) + wc * 512 + m * 64 * CH + l * CH);
 #pragma unroll
-    for (int i = 0; i < CTW; ++i)
+      for (int j = 0; j < RT; ++j)
+        b[m & 1][j] = *reinterpret_cast<const C*>(Bs(bf) + (2 * j + wu) * 512 + m * 64 * CH + l * CH);
+    };
+    fetch(0);
 #pragma unroll
-      for (int m = 0; m < NCH; ++m)
-        a[i][m] = *reinterpret_cast<const C*>(As(bf) + (CTW * wc + i) * 512 + m * 64 * CH + l * CH);
+    for (int m = 0; m < NCH; ++m) {
+      if (m + 1 < NCH) fetch(m + 1);
+      if (m == NCH / 2) mid();
+      __builtin_amdgcn_sched_barrier(0);
+      if (ut0 + UT <= nut) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+        for (int s = 0; s < CH; ++s)
 #pragma unroll
-      for (int m = 0; m < NCH; ++m)
-        b[j][m] = *reinterpret_cast<const C*>(Bs(bf) + (4 * wu + j) * 512 + m * 64 * CH + l * CH);
+          for (int j = 0; j < RT; ++j) acc[j] = SM<T>::mfma(a[m & 1][s], b[m & 1][j][s], acc[j]);
+      } else {
+        // the last row block: row tiles past the last are left out
 #pragma unroll
-    for (int s = 0; s < 8; ++s)
+        for (int j = 0; j < RT; ++j) {
+          if (ut0 + 2 * j + wu >= nut) break;
 #pragma unroll
-      for (int i = 0; i < CTW; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = SM<T>::mfma(a[i][s / CH][s % CH], b[j][s / CH][s % CH], acc[i][j]);
+          for (int s = 0; s < CH; ++s) acc[j] = SM<T>::mfma(a[m & 1][s], b[m & 1][j][s], acc[j]);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
   };
+  R* yr = reinterpret_cast<R*>(y);
+  const R* xr = reinterpret_cast<const R*>(x_axpy);
   // Output chunks of 16 bytes (XC complex values of x and y): chunk k of
-  // this thread is column c = k-th chunk / (64 / XC), rows 8 ut0 + XC (chunk
-  // % (64 / XC)) + 0 .. XC - 1.  Whole chunks where n allows 16-byte access
-  // (n even for FP32 vectors); value by value otherwise.
+  // this thread is column c = k-th chunk / CPC, rows 8 ut0 + XC (chunk % CPC)
+  // + 0 .. XC - 1.  Whole chunks where n allows 16-byte access (n even for
+  // FP32 vectors); value by value otherwise.
   using XV = typename std::conditional<sizeof(R) == 4, f4, d2>::type;
+  constexpr int XC = 16 / (2 * (int)sizeof(R)), CPC = ROWS / XC, NXC = NCOL * CPC / SA_THREADS;
   const bool whole = XC == 1 || (n & 1) == 0;
-  // twice the vector offset (in reals) of the column of each chunk, -1 past the block's columns
-  long long colbase[NXC];
-#pragma unroll
-  for (int k = 0; k < NXC; ++k) {
-    const int col = col0 + (tid + SA_THREADS * k) / CPC;
-    colbase[k] = col < ncols ? 2 * (((long long)(col / count) * M + el_x[k]) * n) : -1;
-  }
-  // the vectors of the fused y = x - S t, requested before the last products
+  // the vectors of the fused y = x - S t, on their way while the sums pass through LDS
   XV xv[NXC];
   auto load_x = [&]() {
     if (!xr) return;
 #pragma unroll
     for (int k = 0; k < NXC; ++k) {
       const int ch = tid + SA_THREADS * k, c = ch / CPC, u = 8 * ut0 + XC * (ch - c * CPC);
-      const long long b = colbase[k];
-      xv[k] = XV{};
-      if (b >= 0 && whole && u + XC <= n) {
-        xv[k] = *reinterpret_cast<const XV*>(xr + b + 2 * u);
-      } else if (b >= 0) {
+      const R* xc = xr + 2 * cbase[min(c, ncols - 1 - col0)];
+      if (whole) {
+        xv[k] = *reinterpret_cast<const XV*>(xc + 2 * min(u, n - XC));
+      } else {
 #pragma unroll
-        for (int z = 0; z < 2 * XC; ++z)
-          if (u + z / 2 < n) xv[k][z] = xr[b + 2 * u + z];
+        for (int z = 0; z < 2 * XC; ++z) xv[k][z] = xc[2 * min(u + z / 2, n - 1) + z % 2];
       }
     }
   };
   load_a(0);
-  load_b(0);
   stage(0);
   __syncthreads();
   for (int vt = 0; vt + 1 < nvt; ++vt) {
     load_a(vt + 1);   // the next k-tile is on its way during the products
     load_b(vt + 1);
-    products(vt & 1);
-    if constexpr (NB == 1) __syncthreads();   // (one buffer: every read of it precedes the next fill)
-    stage((vt + 1) & 1);
+    if constexpr (NB == 2) {
+      products(vt & 1, [&] { stage((vt + 1) & 1); });
+    } else {
+      // (one buffer: every read of it precedes the next fill)
+      products(vt & 1, [] {});
+      __syncthreads();
+      stage((vt + 1) & 1);
+    }
     __syncthreads();
   }
+  products((nvt - 1) & 1, [] {});
   load_x();
-  products((nvt - 1) & 1);
   // the output tile through LDS: every wavefront is past its last reads first
   __syncthreads();
   {
     const int jj = l & 15, q = jj >> 3;
 #pragma unroll
-    for (int i = 0; i < CTW; ++i)
+    for (int e = 0; e < 4; ++e) {
+      const int c = 16 * wc + SM<T>::row(l, e);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int c = 16 * (CTW * wc + i) + SM<T>::row(l, e);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) lds[c * YROW + 2 * (8 * (4 * wu + j) + (jj & 7)) + q] = acc[i][j][e];
-      }
+      for (int j = 0; j < RT; ++j) lds[c * YROW + 2 * (8 * (2 * j + wu) + (jj & 7)) + q] = acc[j][e];
+    }
   }
   __syncthreads();
   // (the loads of x all complete here, once: the stores below sit in
@@ -395,13 +404,13 @@ __global__ void __launch_bounds__(SA_THREADS, sizeof(T) == 8 ? 3 : 2) apply_S_mf
 #pragma unroll
   for (int k = 0; k < NXC; ++k) {
     const int ch = tid + SA_THREADS * k, c = ch / CPC, ul = XC * (ch - c * CPC), u = 8 * ut0 + ul;
-    const long long b = colbase[k];
+    const long long b = 2 * cbase[c];
     if (b < 0 || u >= n) continue;
     XV v;
 #pragma unroll
     for (int z = 0; z < 2 * XC; ++z) v[z] = static_cast<R>(lds[c * YROW + 2 * ul + z]);
     if (xr) v = xv[k] - v;
-    if (whole && u + XC <= n) {
+    if (whole) {
       *reinterpret_cast<XV*>(yr + b + 2 * u) = v;
     } else {
 #pragma unroll
@@ -411,18 +420,60 @@ __global__ void __launch_bounds__(SA_THREADS, sizeof(T) == 8 ? 3 : 2) apply_S_mf
   }
 }
 
-template <typename T, typename VX, int CTW = sizeof(T) == 4 ? 2 : 1>
+// column blocks of a group of count elements
+inline int64_t s_col_blocks(int nrhs, int count) { return ((int64_t)nrhs * count + SA_COLS - 1) / SA_COLS; }
+
+// items with columns
+template <int RT> int64_t s_live_items(const TypeTiles& tl, int n, int nrhs) {
+  int64_t cbs = 0;
+  for (int c : tl.group_count) cbs += s_col_blocks(nrhs, c);
+  return cbs * ((n + sa_rows<RT>() - 1) / sa_rows<RT>());
+}
+
+template <typename T, typename VX, int RT>
+void launch_mfma_tile(const void* Sp, const TypeTiles& tl, int n, int M, int nrhs, const void* t, const void* x,
+                      void* y, hipStream_t s) {
+  const int64_t ncb = s_col_blocks(nrhs, tl.group_max), nub = (n + sa_rows<RT>() - 1) / sa_rows<RT>();
+  const int64_t items = tl.n_groups * ncb * nub;
+  EMS_CHECK_ARG(items + 8 <= 0x7fffffffLL, "too many macromodel tiles");
+  const int64_t live = s_live_items<RT>(tl, n, nrhs);
+  int64_t before = 0;
+  XcdItems span;
+  int k = 0, longest = 0;
+  if (live < 2048) {
+    // below 8 items per CU equal shares of all items, whole types together:
+    // 32 x 32 elements, n_eq 192, 4 right-hand sides, FP32 21.5 us against
+    // 25.5 with equal shares of the items with columns
+    for (; k < 8; ++k) span.first[k] = (int)(items * k / 8);
+  } else {
+    // equal shares of the items with columns, which come first in each group: 61 x 61, n_eq 288, 12 right-hand
+    // sides, FP32 302 us against 327
+    for (int g = 0; g < tl.n_groups; ++g) {
+      const int64_t lg = s_col_blocks(nrhs, tl.group_count[g]) * nub;
+      for (; k < 8 && live * k / 8 < before + lg; ++k) span.first[k] = (int)(g * ncb * nub + live * k / 8 - before);
+      before += lg;
+    }
+  }
+  span.first[8] = (int)items;
+  for (k = 0; k < 8; ++k) longest = std::max(longest, span.first[k + 1] - span.first[k]);
+  hipLaunchKernelGGL((apply_S_mfma_kernel<T, VX, RT>), dim3((unsigned)(8 * longest)), dim3(SA_THREADS), 0, s,
+                     static_cast<const T*>(Sp), tl.elem_sorted.as<const int>(),
+                     tl.tiles.as<const int>() + 3 * (size_t)tl.n_tiles, n, M, nrhs, (int)ncb, (int)nub, span,
+                     static_cast<const typename SM<T>::V2*>(t), static_cast<const VX*>(x), static_cast<VX*>(y));
+}
+
+template <typename T, typename VX>
 void launch_mfma_typed(const void* Sp, const TypeTiles& tl, int n, int M, int nrhs, const void* t, const void* x,
                        void* y, hipStream_t s) {
-  const int ncb = (nrhs * TC + sa_cols<CTW>() - 1) / sa_cols<CTW>();
-  const int nub = (s_row_tiles(n) + SA_UT - 1) / SA_UT;
-  const long long items = (long long)tl.n_tiles * ncb * nub;
-  EMS_CHECK_ARG(items + 8 <= 0x7fffffffLL, "too many macromodel tiles");
-  const int per = (int)((items + 7) / 8);
-  hipLaunchKernelGGL((apply_S_mfma_kernel<T, VX, CTW>), dim3((unsigned)(8 * per)), dim3(SA_THREADS), 0, s,
-                     static_cast<const T*>(Sp), tl.elem_sorted.as<const int>(), tl.tiles.as<const int>(), n, M, nrhs,
-                     ncb, nub, (int)items, per,
-                     static_cast<const typename SM<T>::V2*>(t), static_cast<const VX*>(x), static_cast<VX*>(y));
+  // 48 rows in FP64 from 16 items of 32 rows per CU (61 x 61, n_eq 288, 12
+  // right-hand sides: 596 us against 616; 20 x 20: 98 against 79), or where
+  // three workgroups per CU are just too few for the items of 32 rows (32 x 32,
+  // n_eq 192, 4: 41.5 against 45.3)
+  const int64_t two = s_live_items<2>(tl, n, nrhs);
+  if (sizeof(T) == 8 && (two >= 4096 || (two > 768 && s_live_items<3>(tl, n, nrhs) <= 640)))
+    launch_mfma_tile<T, VX, 3>(Sp, tl, n, M, nrhs, t, x, y, s);
+  else
+    launch_mfma_tile<T, VX, 2>(Sp, tl, n, M, nrhs, t, x, y, s);
 }
 
 }  // namespace
