@@ -18,7 +18,14 @@
 // product's column sums are complete within the wavefront (plain stores) and
 // the first product's row sums, kept in registers for all row tiles, are
 // added across the four wavefronts once per workgroup.  LDS float atomics
-// per column tile (the dense kernel's scheme) cost 1.5 ms here at 128 x 128.
+// per column tile cost 1.5 ms here at 128 x 128.
+//
+// Bound by the stream of the records (90 x 100 elements, n_eq 192, 4
+// right-hand sides, FP32: 609 us, 5.1 TB/s with the vectors).  One read of
+// the vectors serves both halves, in batches of independent loads written to
+// LDS in order, and a B operand is one word at a constant offset: 80 -> 73 us
+// at 32 x 32 and 374 -> 345 at 48 x 48 elements, n_eq 288, against a
+// pass per half, one load at a time, and both parts read for each operand.
 #include "internal.h"
 
 namespace emsurf {
@@ -128,49 +135,50 @@ __global__ void __launch_bounds__(LNT, 2) pair_lk_kernel(const T* __restrict__ T
   const V2* x0 = xh + k * (long long)nrhs * n + (long long)r0 * n;
   const V2* x1 = xh + kb * (long long)nrhs * n + (long long)r0 * n;
   auto cmul = [](T ar, T ai, V2 x) { return V2{ar * x.x - ai * x.y, ar * x.y + ai * x.x}; };
-  // columns of [L | K]: L half v' = v < NP, K half v' = NP + v
-  for (int e = threadIdx.x; e < NPC * 4; e += LNT) {
-    const int r = e / NPC, vp = e - r * NPC;
-    const int half = vp >= NP ? 1 : 0, v = vp - half * NP;
-    V2 c0{0, 0}, c1{0, 0};
-    if (r < nr && v < nh) {
-      const V2 xj = x0[(long long)r * n + v], xm = x0[(long long)r * n + nh + v];
-      if (half == 0) {
-        c0 = cmul(cf.ar, cf.ai, xj);
-        c1 = cmul(cf.er, cf.ei, xm);
-      } else {
-        c0 = cmul(cf.br, cf.bi, xm);
-        c1 = cmul(cf.cr, cf.ci, xj);
-      }
+  // columns of [L | K]: L half v' = v < NP, K half v' = NP + v; the
+  // right-hand side fastest, so that the LDS writes are contiguous, and a
+  // batch of loads in flight
+  constexpr int XB = (NP * 4 + LNT - 1) / LNT < 3 ? (NP * 4 + LNT - 1) / LNT : 3;
+  for (int i = 0; i < NP * 4; i += XB * LNT) {
+    V2 xj[XB], xm[XB], yj[XB], ym[XB];
+    T wr[XB];
+#pragma unroll
+    for (int j = 0; j < XB; ++j) {
+      const int e = min(i + j * LNT + (int)threadIdx.x, NP * 4 - 1), r = min(e & 3, nr - 1), v = min(e >> 2, nh - 1);
+      xj[j] = x0[(long long)r * n + v];
+      xm[j] = x0[(long long)r * n + nh + v];
+      yj[j] = x1[(long long)r * n + v];
+      ym[j] = x1[(long long)r * n + nh + v];
+      wr[j] = w[v];
     }
-    xs[(vp * LNV + 2 * r) * 2] = c0.x;
-    xs[(vp * LNV + 2 * r) * 2 + 1] = c0.y;
-    xs[(vp * LNV + 2 * r + 1) * 2] = c1.x;
-    xs[(vp * LNV + 2 * r + 1) * 2 + 1] = c1.y;
-  }
-  for (int e = threadIdx.x; e < NP * 4; e += LNT) {
-    const int r = e / NP, u = e - r * NP;
-    V2 c0{0, 0}, c1{0, 0};
-    if (r < nr && u < nh) {
-      const V2 xj = x1[(long long)r * n + u], xm = x1[(long long)r * n + nh + u];
-      c0 = V2{w[u] * xj.x, w[u] * xj.y};
-      c1 = V2{w[u] * xm.x, w[u] * xm.y};
+#pragma unroll
+    for (int j = 0; j < XB; ++j) {
+      const int e = min(i + j * LNT + (int)threadIdx.x, NP * 4 - 1);
+      const bool ok = (e & 3) < nr && (e >> 2) < nh;
+      auto put = [&](T* at, V2 c0, V2 c1) {
+        V2* d = reinterpret_cast<V2*>(at) + 2 * e;
+        d[0] = V2{ok ? c0.x : T(0), ok ? c0.y : T(0)};
+        d[1] = V2{ok ? c1.x : T(0), ok ? c1.y : T(0)};
+      };
+      put(xs, cmul(cf.ar, cf.ai, xj[j]), cmul(cf.er, cf.ei, xm[j]));
+      put(xs + NP * LNV * 2, cmul(cf.br, cf.bi, xm[j]), cmul(cf.cr, cf.ci, xj[j]));
+      put(xt, V2{wr[j] * yj[j].x, wr[j] * yj[j].y}, V2{wr[j] * ym[j].x, wr[j] * ym[j].y});
     }
-    xt[(u * LNV + 2 * r) * 2] = c0.x;
-    xt[(u * LNV + 2 * r) * 2 + 1] = c0.y;
-    xt[(u * LNV + 2 * r + 1) * 2] = c1.x;
-    xt[(u * LNV + 2 * r + 1) * 2 + 1] = c1.y;
   }
   __syncthreads();
   // lane roles: k-slot kk = l / 16 -> (pair offset off, part); column jj = l % 16:
   // real part of virtual column jj (jj < 8) or imaginary part of jj - 8
   const int kk = l >> 4, jj = l & 15, off = kk >> 1, part_ = kk & 1, a16 = l & 15;
   const bool jre = jj < LNV;
-  const int rj = jj & (LNV - 1);
-  auto bval = [&](const T* x, int idx) {
-    const T xr = x[(idx * LNV + rj) * 2], xi = x[(idx * LNV + rj) * 2 + 1];
-    return part_ == 0 ? (jre ? xr : xi) : (jre ? -xi : xr);
+  // value s of a B operand for source tile v: one part of the lane's column,
+  // with the sign of -xi folded in
+  const bool bneg = part_ == 1 && jre;
+  const int blane = (off * LNV + (jj & (LNV - 1))) * 2 + ((part_ == 0) == jre ? 0 : 1);
+  auto bval = [&](const T* x, int s) {
+    const T val = x[2 * s * LNV * 2];
+    return bneg ? -val : val;
   };
+  auto btile = [&](const T* x, int v) { return x + v * PAIR_TILE * LNV * 2 + blane; };
   Acc acc[NTR];
 #pragma unroll
   for (int t = 0; t < NTR; ++t) acc[t] = Acc{};
@@ -184,7 +192,7 @@ __global__ void __launch_bounds__(LNT, 2) pair_lk_kernel(const T* __restrict__ T
     const int q = wv + 4 * qa;
     T b1[8];
 #pragma unroll
-    for (int s = 0; s < 8; ++s) b1[s] = bval(xs, q * PAIR_TILE + 2 * s + off);
+    for (int s = 0; s < 8; ++s) b1[s] = bval(btile(xs, q), s);
     Acc zq{};
 #pragma unroll
     for (int t = 0; t < NTR; ++t, ++it) {
@@ -213,7 +221,7 @@ __global__ void __launch_bounds__(LNT, 2) pair_lk_kernel(const T* __restrict__ T
 #pragma unroll
       for (int m = 0; m < NCH; ++m)
 #pragma unroll
-        for (int c = 0; c < CH; ++c) zq = M::mfma(cr[m][c], bval(xt, t * PAIR_TILE + 2 * (m * CH + c) + off), zq);
+        for (int c = 0; c < CH; ++c) zq = M::mfma(cr[m][c], bval(btile(xt, t), m * CH + c), zq);
       stage = NSTG == 2 ? stage ^ 1 : 0;
     }
     // the column sums of tile column q are complete: plain stores
