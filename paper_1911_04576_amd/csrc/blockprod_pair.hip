@@ -203,6 +203,7 @@ __global__ void __launch_bounds__(PNT, pair_min_waves<T>(TPW, NRW)) pair_mfma_ke
     const int q = v - tw[ta];
     return (tbase[ta] + (q < 0 ? q + nt : q) * tstep[ta]) * TILE_BYTES;
   };
+  const int last_off = tile_off(vtile(nt - 1), TPW - 1);
   // one tile in flight per u tile of the wavefront: while tile (q, ta) is
   // used, the tiles of the rest of step q and of step q + 1 up to ta - 1 are
   // on their way (every slot is requested, whatever ntw: see the sweep)
@@ -333,7 +334,8 @@ __global__ void __launch_bounds__(PNT, pair_min_waves<T>(TPW, NRW)) pair_mfma_ke
       // the slot's registers are free: request its tile of step q + 1 (every
       // slot requests one, whatever ntw, so that each wait covers exactly
       // the oldest tile; a slot past ntw repeats the request before it)
-      const int noff = tile_off(vn, ta);
+      // (after the last step: one tile, by now in the caches, for every slot)
+      const int noff = q + 1 < nt ? tile_off(vn, ta) : last_off;
 #pragma unroll
       for (int m = 0; m < NCH; ++m) buf[ta][m] = ld_chunk<C>(rs, voff + 1024 * m, noff);
       if (live) {
