@@ -53,14 +53,14 @@
 //
 // What bounds it: up to 8 right-hand sides the stream of the blocks (FP32 at
 // n_eq 288: 5.1 TB/s), beyond that the matrix cores in FP32 (61 x 61 elements,
-// n_eq 288, 13 right-hand sides: 1628 us, of which 1107 us of MFMA at full
+// n_eq 288, 13 right-hand sides: 1612 us, of which 1107 us of MFMA at full
 // rate and a tenth more for 18 tiles on four wavefronts).  What it also spends
 // is latency around the steps, so the vectors are read in batches of
 // independent loads and the B operands without conditions (one wait for many
 // LDS reads, constant address offsets), and the column sums start with a
 // store.  Before that (a wait for every element loaded and for every operand,
 // bank conflicts in the staged vectors, a branch per column sum): 1979 us
-// there; 48 x 40 elements, n_eq 96, 13 right-hand sides: 173 -> 130 us in FP32,
+// there; 48 x 40 elements, n_eq 96, 13 right-hand sides: 173 -> 128 us in FP32,
 // 350 -> 259 us in FP64.
 #include "internal.h"
 
