@@ -208,10 +208,12 @@ struct XcdItems { int first[9]; };
 // column's vector offset is looked up once into LDS (not divided out by every
 // thread), loads carry no conditions, operands leave LDS a chunk ahead of
 // their products, and a small tile fills the chip early: 32 x 32 outputs are
-// as fast as 64 x 64 even where there is work for both.  y = S t, 64 rows x 64
+// as fast as 64 x 64 in most places where there is work for both.  y = S t, 64 rows x 64
 // columns (FP64 32) before: 4 x 4 elements, n_eq 96, 1 right-hand side, FP32
 // 11.9 -> 5.8 us, FP64 12.9 -> 9.0; 48 x 40, n_eq 96, 12: 40 -> 26, 64 -> 50;
-// 61 x 61, n_eq 288, 12: 332 -> 301 (98 TFLOP/s), 650 -> 596.
+// 61 x 61, n_eq 288, 12: 332 -> 301 (98 TFLOP/s), 650 -> 596.  Where 64 rows
+// divide n_eq and work is plentiful it gives a little back (128 x 128, n_eq
+// 192, 12: 555 -> 588, 1129 -> 1171); a second tile for that was not kept.
 template <typename T, typename VX, int RT>
 __global__ void __launch_bounds__(SA_THREADS, 3) apply_S_mfma_kernel(
     const T* __restrict__ Sp, const int* __restrict__ elem_sorted, const int* __restrict__ groups, int n, int M,
