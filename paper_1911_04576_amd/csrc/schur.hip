@@ -121,10 +121,14 @@ template <int CTRL> __device__ __forceinline__ double dpp_d(double v) {
   const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xF, 0xF, false);
   return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
 }
-// Pivot key of a value |a|^2 >= 0: the upper half of the double (sign,
-// exponent, 20 bits of mantissa), ordered like it; -1 for no candidate.
+// Pivot keys of a value |a|^2 >= 0: the upper half of the double (sign,
+// exponent, 20 bits of mantissa), -1 for no candidate, and the lower half;
+// both as integers ordered like the value.
 __device__ __forceinline__ int pivot_key(double v2, bool candidate) {
   return candidate && v2 >= 0.0 ? (int)(__builtin_bit_cast(long long, v2) >> 32) : -1;   // (a NaN is none)
+}
+__device__ __forceinline__ int pivot_low_key(double v2) {
+  return (int)((unsigned)__builtin_bit_cast(long long, v2) ^ 0x80000000u);
 }
 __device__ __forceinline__ int max_i(int a, int b) { return a > b ? a : b; }
 // Largest v within each row of 16 lanes, in every lane: quad exchanges 1 and 2
@@ -144,6 +148,19 @@ __device__ __forceinline__ int wave_max(int v) {
   v = max_i(v, __builtin_amdgcn_update_dpp(v, v, 0x143, 0xC, 0xF, false));
   return __builtin_amdgcn_readlane(v, 63);
 }
+// Of the lanes in `in` (more than one, equal in the upper key): those with the
+// largest lower key, then the one with the lowest position.  MAX reduces over
+// the lanes; every lane takes part.
+template <typename Max>
+__device__ __forceinline__ unsigned long long pivot_tie(unsigned long long in, int low, int pos, Max&& max) {
+  const bool a = (in >> (threadIdx.x & 63)) & 1;
+  const int l = a ? low : INT_MIN, lm = max(l);
+  in &= __ballot(l == lm);
+  if (__popcll(in) == 1) return in;
+  const bool b = (in >> (threadIdx.x & 63)) & 1;
+  const int p = b ? -pos : INT_MIN;
+  return in & __ballot(p == max(p));
+}
 
 // The same panel with the rows in registers, for N - k0 <= NT: one row per
 // thread.  The panel's columns go in sub-blocks of PSB: a sub-block is staged
@@ -153,9 +170,8 @@ __device__ __forceinline__ int wave_max(int v) {
 // columns left of the panel and the rw columns right of it), and the columns
 // to its right (the panel's and the rw beyond) its U rows (L11^-1 A12 by one
 // wavefront) and one rank-PSB update, so that the panel makes one pass
-// through memory per sub-block instead of one per column.  The pivot is the
-// largest |a|^2 among rows [kk, K), to 20 bits (of equal ones the row that
-// stood first when the sub-block began); same singular flags.
+// through memory per sub-block instead of one per column.  Same pivots
+// (largest |a|^2 among rows [kk, K), first position on ties) and singular flags.
 //
 // One CU per matrix walks all the columns, so the panel is a serial chain, and
 // with up to 16 wavefronts on the CU what the chain waits for is the LDS and
@@ -165,7 +181,10 @@ __device__ __forceinline__ int wave_max(int v) {
 //    barriers.  With every wavefront's candidate row published before a single
 //    barrier and read by every lane, the LDS took half of each column.
 //  - The key is the upper half of |a|^2, which a DPP maximum reduces in one
-//    instruction per step: a chosen pivot is within 2^-20 of the largest.
+//    instruction per step.  The ballots tell whether one row alone has it; only
+//    where several are equal in it (20 bits of mantissa) do all wavefronts go
+//    on to the lower half and the position.  Against a choice among those by
+//    the upper half alone: 3.50 -> 3.54 ms for 32 types of 288 + 576 unknowns.
 //  - The pivot row's values sit in one lane each of a row of 16 lanes and
 //    enter the multiply-adds by DPP (row_newbcast): one LDS read per wavefront.
 //  - Rows do not move: a thread keeps its row and tracks its position.
@@ -201,6 +220,7 @@ __global__ void __launch_bounds__(NT) panel_reg_kernel(double2* __restrict__ A, 
   double2* M = A + (long long)b * N * N;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = tid & 15;
   __shared__ int2 rec[NW];                 // each wavefront's largest pivot key and the position of its row
+  __shared__ int2 tie[NW];                 // where several are equal: lower key and position
   __shared__ double2 prow[16];             // the pivot row right of the column, its pivot's inverse in the column's place
   __shared__ double2 U[PSB][2 * PANEL];    // the sub-block's U rows over the columns to its right
   __shared__ int spv[PSB];                 // the sub-block's pivot rows
@@ -255,17 +275,34 @@ __global__ void __launch_bounds__(NT) panel_reg_kernel(double2* __restrict__ A, 
       }
       const int v = pivot_key(v2, pos >= col && pos < K);
       const int wm = wave_max(v);
-      if (lane == __builtin_ctzll(__ballot(v == wm)))   // (some lane holds the maximum)
-        rec[wave] = int2{wm, pos};
+      const unsigned long long own = __ballot(v == wm);   // (some lane holds the maximum)
+      if (lane == __builtin_ctzll(own)) rec[wave] = int2{wm, pos | ((own & (own - 1)) ? INT_MIN : 0)};
       __syncthreads();
       // the wavefronts' records: lane w of every row of 16 lanes takes
       // wavefront w's, the others an empty one that never wins
       const int2 rc = rec[l16 < NW ? l16 : 0];
       const int cv = l16 < NW ? rc.x : -2;
       const int bv = __builtin_amdgcn_readlane(row_max(cv), 0);
-      // (a key of zero, |a| < 1e-157 throughout, has no finite inverse; -1: every value is NaN)
-      const bool singular = bv <= 0;
-      const int p = singular ? col : __builtin_amdgcn_readlane(rc.y, __builtin_ctzll(__ballot(cv == bv)));
+      unsigned long long best = __ballot(cv == bv) & 0xFFFF;
+      int p = __builtin_amdgcn_readlane(rc.y, __builtin_ctzll(best));
+      bool singular = false;
+      if (bv <= 0 || p < 0 || (best & (best - 1)) != 0) {
+        // several are equal in the key (or it is none, or zero); the same
+        // branch in every wavefront
+        unsigned long long in = bv >= 0 ? __ballot(v == bv) : 0;
+        const int low = pivot_low_key(v2);
+        if (__popcll(in) > 1) in = pivot_tie(in, low, pos, [](int x) { return wave_max(x); });
+        if (lane == (in ? __builtin_ctzll(in) : 0)) tie[wave] = in ? int2{low, pos} : int2{INT_MIN, -1};
+        __syncthreads();
+        const int2 tr = tie[l16 < NW ? l16 : 0];
+        best = __ballot(l16 < NW && tr.y >= 0) & 0xFFFF;
+        if (__popcll(best) > 1)
+          best = pivot_tie(best, tr.x, tr.y, [](int x) { return __builtin_amdgcn_readlane(row_max(x), 0); });
+        const int bl = best ? __builtin_ctzll(best) : 0;
+        // (no value above zero: both keys of zero, or every value is NaN)
+        singular = !best || (bv == 0 && __builtin_amdgcn_readlane(tr.x, bl) == INT_MIN);
+        p = singular ? col : __builtin_amdgcn_readlane(tr.y, bl);
+      }
       if (pos == p) {
         if constexpr (NT > 512) rd = 1.0 / v2;
         prow[kk] = singular ? double2{0.0, 0.0} : double2{r[kk].x * rd, -r[kk].y * rd};
