@@ -176,29 +176,49 @@ __global__ void __launch_bounds__((Shape<L, 1>::NT)) pattern_kernel(PatternArgs 
   }
 }
 
-// D[r][h][q][p] holds the radiation intensity U and receives 4 pi U / P_rad[r],
-// P_rad[r] the sum of the Lu partial powers (every workgroup adds them in the
-// same order; the first of a right-hand side reports the sum)
-constexpr int DIR_THREADS = 256;
-__global__ void __launch_bounds__(DIR_THREADS) directivity_kernel(const double* __restrict__ part, int Lu,
+// sum of n values, the same order in every wavefront that forms it
+__device__ __forceinline__ double sum_of(const double* __restrict__ v, int n) {
+  double s = 0.0;
+  for (int i = threadIdx.x & 63; i < n; i += 64) s += v[i];
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
+  return s;
+}
+
+// out[r] = sum of the partial powers of right-hand side r
+__global__ void __launch_bounds__(64) power_kernel(const double* __restrict__ part, int parts,
+                                                   double* __restrict__ out) {
+  const double s = sum_of(part + (long long)blockIdx.x * parts, parts);
+  if (threadIdx.x == 0) out[blockIdx.x] = s;
+}
+
+// D[r][h][q][p] = 4 pi U / P_rad[r], P_rad[r] the sum of the parts partial
+// powers (every workgroup adds those of all right-hand sides, in the same
+// order; the first reports them).  D is left alone where a sum is not positive
+// and finite, which the call refuses.
+constexpr int DIR_THREADS = 256, DIR_RHS = 64;
+__global__ void __launch_bounds__(DIR_THREADS) directivity_kernel(const double* __restrict__ part, int parts,
+                                                                  int nrhs, const double* __restrict__ U,
                                                                   long long per_rhs, double* __restrict__ D,
                                                                   double* __restrict__ prad) {
-  __shared__ double sum;
+  __shared__ double sum[DIR_RHS];
   const int r = blockIdx.y, t = threadIdx.x;
-  if (t < 64) {
-    double s = 0.0;
-    for (int i = t; i < Lu; i += 64) s += part[(long long)r * Lu + i];
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
-    if (t == 0) sum = s;
+  for (int i = t >> 6; i < nrhs; i += DIR_THREADS / 64) {
+    const double s = sum_of(part + (long long)i * parts, parts);
+    if ((t & 63) == 0) sum[i] = s;
   }
   __syncthreads();
-  const double P = sum;
-  if (blockIdx.x == 0 && t == 0) prad[r] = P;
+  if (blockIdx.x == 0 && r == 0 && t < nrhs) prad[t] = sum[t];
+  for (int i = 0; i < nrhs; ++i)
+    if (!(sum[i] > 0.0) || !isfinite(sum[i])) return;
+  const double P = sum[r];
+  const double* u = U + r * per_rhs;
   double* d = D + r * per_rhs;
   for (long long i = blockIdx.x * (long long)DIR_THREADS + t; i < per_rhs; i += (long long)gridDim.x * DIR_THREADS)
-    d[i] = 4.0 * 3.14159265358979323846 * d[i] / P;
+    d[i] = 4.0 * 3.14159265358979323846 * u[i] / P;
 }
+
+int bin_blocks(int Lu, int Lv) { return (int)(((long long)Lu * Lv + BIN_THREADS - 1) / BIN_THREADS); }
 
 // x pass of the lattice DFT of the unknowns (sign +1) into W[iy][p][r][u]
 void lattice_dft_x(int n, int nx, int ny, int nrhs, int Lu, const void* x_dev, void* W, hipStream_t s) {
@@ -306,19 +326,28 @@ extern "C" emsurf_status emsurf_directivity(const emsurf_geom* geom, int32_t nx,
     GreenGeomDev g;
     upload_geom(geom, g, s);
     const int n = 4 * g.n_patch;
-    const size_t b_w = (size_t)ny * Lu * nrhs * n * 16, b_part = (size_t)nrhs * Lu * 8, b_prad = (size_t)nrhs * 8;
-    Scratch ws(Scratch::round(b_w) + Scratch::round(b_part) + b_prad);
+    int parts = Lu;
+    const long long per_rhs = (long long)2 * Lu * Lv;
+    const size_t b_w = Scratch::round((size_t)ny * Lu * nrhs * n * 16), b_U = Scratch::round(nrhs * per_rhs * 8);
+    const size_t b_part = Scratch::round((size_t)nrhs * parts * 8), b_prad = (size_t)nrhs * 8;
+    Scratch ws(b_w + b_U + b_part + 2 * Scratch::round(b_prad));
     void* W = ws.part(b_w);
-    double *part = ws.part<double>(b_part), *prad = ws.part<double>(b_prad);
+    double *U = ws.part<double>(b_U), *part = ws.part<double>(b_part);
+    double *sums = ws.part<double>(b_prad), *prad = ws.part<double>(b_prad);
     lattice_dft_x(n, nx, ny, nrhs, Lu, x_dev, W, s);
     PatternArgs a = pattern_args(g, ny, nrhs, Lu, Lv, W);
-    a.U = static_cast<double*>(D_dev);
+    a.U = U;
     a.part = part;
     launch_pattern(Lv, a, s);
-    const long long per_rhs = (long long)2 * Lu * Lv;
+    if (nrhs > 4) {
+      // (up to four a workgroup's wavefronts add them at once)
+      hipLaunchKernelGGL(power_kernel, dim3((unsigned)nrhs), dim3(64), 0, s, part, parts, sums);
+      part = sums;
+      parts = 1;
+    }
     const long long blocks = (per_rhs + 4 * DIR_THREADS - 1) / (4 * DIR_THREADS);
     hipLaunchKernelGGL(directivity_kernel, dim3((unsigned)(blocks < 4096 ? blocks : 4096), (unsigned)nrhs),
-                       dim3(DIR_THREADS), 0, s, part, Lu, per_rhs, static_cast<double*>(D_dev), prad);
+                       dim3(DIR_THREADS), 0, s, part, parts, nrhs, U, per_rhs, static_cast<double*>(D_dev), prad);
     EMS_LAUNCH_CHECK();
     std::vector<double> pr(nrhs, 0.0);
     EMS_HIP(hipMemcpyAsync(pr.data(), prad, b_prad, hipMemcpyDeviceToHost, s));
