@@ -10,7 +10,9 @@
 // bin), the sum over elements is the zero-padded 2-D DFT with kernel
 // e^{+j 2 pi (p ix / Lu + q iy / Lv)} of the lattice data: a Stockham pass of
 // sign +1 along x (the pass of the coupling apply), then one kernel that runs
-// the pass along y in LDS and projects its points onto the directions.
+// the pass along y in LDS and projects its points onto the directions; where
+// that leaves the chip idle, a pass along y and a projection by single bins.
+#include <algorithm>
 #include <cmath>
 #include <vector>
 
@@ -29,16 +31,17 @@ struct PatternArgs {
   double pitch, k;
   double2* E;            // [r][q][p][2] (E_theta, E_phi), upper half space; or NULL
   double* U;             // [r][half space][q][p] radiation intensity; or NULL
-  double* part;          // [r][p] power of the bins (., p), with U
+  double* part;          // [r][parts] partial powers, with U
 };
 
 // One workgroup per (x bin p, right-hand side r), which owns the bins (q, p)
 // of all q.  It takes BT / 4 patches at a time: their 2 J and 2 M columns are
 // transformed along y in LDS (Lv points), then every thread adds the patches to
-// its bins, both half spaces at once.  A spectrum written by a y pass and read
-// by a projection of each half space is 403 MB at 64 x 57 elements, n_eq 192,
-// 2 RHS and 256 x 256 bins: 330 of 375 us per call, now 97 of 138 us (bound
-// by the FP64 sums of two workgroups per CU, whose spectra fill the LDS).  With a patch's phase split
+// its bins, the upper half space (HS = 1, for E) or both at once (HS = 2, for
+// U).  A spectrum written by a y pass and read by a projection of each half
+// space is 403 MB at 64 x 57 elements, n_eq 192, 2 RHS and 256 x 256 bins: 330
+// of 375 us per call, now 97 of 137 us (bound by the FP64 sums of two
+// workgroups per CU, whose spectra fill the LDS).  With a patch's phase split
 // into e^{jkux} (per workgroup), e^{jkvy} and e^{jkwz} (kept while the next
 // patch has the same y or z) the sums need few sincos:
 //   S = (t . (cp, sp, 0) J, t_z st J, t . phi^ J) summed over the tangents,
@@ -46,7 +49,7 @@ struct PatternArgs {
 //   E_theta += e^{jk..} (+-w S0 - S1 + R2),  E_phi += e^{jk..} (S2 -+ w R0 + R1)
 // with theta^ = (+-w cp, +-w sp, -st) above and below.  Bins outside the
 // visible region u^2 + v^2 < 1 are zero.
-template <int L>
+template <int L, int HS>
 __global__ void __launch_bounds__((Shape<L, 1>::NT)) pattern_kernel(PatternArgs a) {
   using SH = Shape<L, 1>;
   constexpr int BT = SH::BT, NT = SH::NT, NBIN = (L + NT - 1) / NT, PC = BT / 4;
@@ -61,7 +64,7 @@ __global__ void __launch_bounds__((Shape<L, 1>::NT)) pattern_kernel(PatternArgs 
   struct Bin {
     double v, w, cp, sp, st;
     double2 py, pz;               // e^{jkvy}, e^{jkwz}
-    double2 et[2], ep[2];         // above, below
+    double2 et[HS], ep[HS];       // above, below
     bool vis;
   } bin[NBIN];
 #pragma unroll
@@ -76,7 +79,8 @@ __global__ void __launch_bounds__((Shape<L, 1>::NT)) pattern_kernel(PatternArgs 
     B.cp = B.st > 0.0 ? u / B.st : 1.0;
     B.sp = B.st > 0.0 ? B.v / B.st : 0.0;
     B.py = B.pz = double2{1.0, 0.0};
-    B.et[0] = B.et[1] = B.ep[0] = B.ep[1] = double2{0.0, 0.0};
+#pragma unroll
+    for (int h = 0; h < HS; ++h) B.et[h] = B.ep[h] = double2{0.0, 0.0};
   }
   if (u * u < 1.0) {   // (the whole workgroup)
     PassArgs f{};
@@ -130,12 +134,12 @@ __global__ void __launch_bounds__((Shape<L, 1>::NT)) pattern_kernel(PatternArgs 
           // theta: w S0 - S1 + R2 above, -w S0 - S1 + R2 below; phi: S2 - w R0 + R1 above, S2 + w R0 + R1 below
           const double2 ct{S[1][2].x - S[0][1].x, S[1][2].y - S[0][1].y};
           const double2 cf{S[0][2].x + S[1][1].x, S[0][2].y + S[1][1].y};
-          const double2 e[4] = {cmul(up, cadd(ct, S[0][0])), cmul(dn, csub(ct, S[0][0])),
-                                cmul(up, csub(cf, S[1][0])), cmul(dn, cadd(cf, S[1][0]))};
-          B.et[0] = cadd(B.et[0], e[0]);
-          B.et[1] = cadd(B.et[1], e[1]);
-          B.ep[0] = cadd(B.ep[0], e[2]);
-          B.ep[1] = cadd(B.ep[1], e[3]);
+          B.et[0] = cadd(B.et[0], cmul(up, cadd(ct, S[0][0])));
+          B.ep[0] = cadd(B.ep[0], cmul(up, csub(cf, S[1][0])));
+          if constexpr (HS == 2) {
+            B.et[1] = cadd(B.et[1], cmul(dn, csub(ct, S[0][0])));
+            B.ep[1] = cadd(B.ep[1], cmul(dn, cadd(cf, S[1][0])));
+          }
         }
       }
       __syncthreads();   // every column is read before the next ones arrive
@@ -148,14 +152,14 @@ __global__ void __launch_bounds__((Shape<L, 1>::NT)) pattern_kernel(PatternArgs 
     const Bin& B = bin[j];
     const int q = t + NT * j;
     if (q >= L) continue;
-    if (a.E) {
+    if constexpr (HS == 1) {
       double2* out = a.E + (((long long)r * L + q) * a.Lu + p) * 2;
       out[0] = B.vis ? B.et[0] : double2{0.0, 0.0};
       out[1] = B.vis ? B.ep[0] : double2{0.0, 0.0};
     }
-    if (a.U) {
+    if constexpr (HS == 2) {
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
+      for (int h = 0; h < HS; ++h) {
         const double U = B.vis ? B.et[h].x * B.et[h].x + B.et[h].y * B.et[h].y + B.ep[h].x * B.ep[h].x +
                                      B.ep[h].y * B.ep[h].y
                                : 0.0;
@@ -164,7 +168,7 @@ __global__ void __launch_bounds__((Shape<L, 1>::NT)) pattern_kernel(PatternArgs 
       }
     }
   }
-  if (!a.U) return;
+  if constexpr (HS == 1) return;
   red[t] = power;
   __syncthreads();
   if (t < 64) {   // (fixed order: lane t adds its share, then a tree)
@@ -173,6 +177,76 @@ __global__ void __launch_bounds__((Shape<L, 1>::NT)) pattern_kernel(PatternArgs 
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
     if (t == 0) a.part[(long long)r * a.Lu + p] = s;
+  }
+}
+
+// The projection by single bins: one thread per bin (q, p) of the spectrum
+// a.W = X[q][p][r][u]; grid (blocks of BIN_THREADS bins, r).
+constexpr int BIN_THREADS = 256;
+template <int HS> __global__ void __launch_bounds__(BIN_THREADS) bins_kernel(PatternArgs a, int Lv) {
+  __shared__ double red[BIN_THREADS];
+  const int r = blockIdx.y, n = 4 * a.P;
+  const long long bins = (long long)Lv * a.Lu, bin = blockIdx.x * (long long)BIN_THREADS + threadIdx.x;
+  const int p = (int)(bin % a.Lu), q = (int)(bin / a.Lu);
+  const double pi = 3.14159265358979323846;
+  const int ps = p < (a.Lu + 1) / 2 ? p : p - a.Lu, qs = q < (Lv + 1) / 2 ? q : q - Lv;
+  const double u = 2.0 * pi * ps / (a.Lu * a.k * a.pitch), v = 2.0 * pi * qs / (Lv * a.k * a.pitch);
+  const double s2 = u * u + v * v;
+  const bool vis = bin < bins && s2 < 1.0;
+  double power = 0.0;
+#pragma unroll
+  for (int h = 0; h < HS; ++h) {
+    double2 et{0.0, 0.0}, ep{0.0, 0.0};
+    if (vis) {
+      const double w = h == 0 ? sqrt(1.0 - s2) : -sqrt(1.0 - s2), st = sqrt(s2);
+      const double cp = st > 0.0 ? u / st : 1.0, sp = st > 0.0 ? v / st : 0.0;
+      const double2* xb = a.W + (bin * a.nrhs + r) * n;
+      double2 N[3] = {}, M[3] = {};
+      for (int i = 0; i < a.P; ++i) {
+        double sn, cs;
+        sincos(a.k * (u * a.rho[3 * i] + v * a.rho[3 * i + 1] + w * a.rho[3 * i + 2]), &sn, &cs);
+        const double2 ph{a.area[i] * cs, a.area[i] * sn};
+        const double2 j0 = cmul(ph, xb[2 * i]), j1 = cmul(ph, xb[2 * i + 1]);
+        const double2 m0 = cmul(ph, xb[2 * a.P + 2 * i]), m1 = cmul(ph, xb[2 * a.P + 2 * i + 1]);
+        const double *t0 = a.tan + 6 * i, *t1 = t0 + 3;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          N[c].x += j0.x * t0[c] + j1.x * t1[c];
+          N[c].y += j0.y * t0[c] + j1.y * t1[c];
+          M[c].x += m0.x * t0[c] + m1.x * t1[c];
+          M[c].y += m0.y * t0[c] + m1.y * t1[c];
+        }
+      }
+      const double th[3] = {w * cp, w * sp, -st}, ph[3] = {-sp, cp, 0.0};
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        et.x += N[c].x * th[c] + M[c].x * ph[c];
+        et.y += N[c].y * th[c] + M[c].y * ph[c];
+        ep.x += N[c].x * ph[c] - M[c].x * th[c];
+        ep.y += N[c].y * ph[c] - M[c].y * th[c];
+      }
+    }
+    if (bin >= bins) continue;
+    if constexpr (HS == 1) {
+      double2* out = a.E + ((long long)r * bins + bin) * 2;
+      out[0] = et;
+      out[1] = ep;
+    } else {
+      const double U = et.x * et.x + et.y * et.y + ep.x * ep.x + ep.y * ep.y;
+      a.U[((long long)r * 2 + h) * bins + bin] = U;
+      const double du = 2.0 * pi / (a.Lu * a.k * a.pitch), dv = 2.0 * pi / (Lv * a.k * a.pitch);
+      power += vis ? U * du * dv / sqrt(1.0 - s2) : 0.0;
+    }
+  }
+  if constexpr (HS == 1) return;
+  red[threadIdx.x] = power;
+  __syncthreads();
+  if (threadIdx.x < 64) {   // (fixed order)
+    double s = 0.0;
+    for (int i = threadIdx.x; i < BIN_THREADS; i += 64) s += red[i];
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
+    if (threadIdx.x == 0) a.part[(long long)r * gridDim.x + blockIdx.x] = s;
   }
 }
 
@@ -220,6 +294,20 @@ __global__ void __launch_bounds__(DIR_THREADS) directivity_kernel(const double* 
 
 int bin_blocks(int Lu, int Lv) { return (int)(((long long)Lu * Lv + BIN_THREADS - 1) / BIN_THREADS); }
 
+// Whether a y pass and single bins take the place of the fused kernel: with few
+// columns (p, r) of many bins, whose workgroups leave CUs idle, and with many
+// columns of few bins, whose threads outnumber the bins.  HS = 2 (directivity)
+// against HS = 1 (far field) as the fused kernel saves two half spaces'
+// spectrum reads.  Microseconds fused / by bins, 48 patches, 1 right-hand side:
+// HS 2, 64 x 1024 bins 316 / 158, 128 x 1024 321 / 357, 128 x 512 158 / 158, 128 x
+// 256 90 / 131, 64 x 64 56 / 102; HS 1, 64 x 1024 295 / 97, 128 x 192 89 / 76, 256
+// x 192 96 / 97, 128 x 256 74 / 76, 1024 x 16 90 / 76, 512 x 16 51 / 65.
+bool by_bins(int Lu, int Lv, int nrhs, int P, int hs) {
+  const int64_t columns = (int64_t)Lu * nrhs;
+  if (hs == 2) return (Lv >= 384 && columns <= (Lv < 1024 ? 128 : 64)) || (Lv <= 32 && columns >= std::min(40 * P, 2048));
+  return ((Lv >= 192 || Lv == 96) && columns <= 128) || (Lv <= 32 && columns >= std::min(20 * P, 1024));
+}
+
 // x pass of the lattice DFT of the unknowns (sign +1) into W[iy][p][r][u]
 void lattice_dft_x(int n, int nx, int ny, int nrhs, int Lu, const void* x_dev, void* W, hipStream_t s) {
   const int64_t B = (int64_t)nrhs * n, M = (int64_t)nx * ny;
@@ -232,7 +320,7 @@ void lattice_dft_x(int n, int nx, int ny, int nrhs, int Lu, const void* x_dev, v
   launch_fft_pass(fx, Cx::C128, Cx::C128, Cx::C128, x_dev, W, twiddle_table(Lu, Cx::C128), s);
 }
 
-void launch_pattern(int Lv, const PatternArgs& a, hipStream_t s) {
+template <int HS> void launch_pattern(int Lv, const PatternArgs& a, hipStream_t s) {
   // the y transform addresses its input with 32-bit offsets
   const int64_t B = (int64_t)a.nrhs * 4 * a.P;
   EMS_CHECK_ARG(Lv * a.Lu * B + B + 1024 < (1LL << 31), "FFT line span exceeds 32-bit offsets");
@@ -240,7 +328,7 @@ void launch_pattern(int Lv, const PatternArgs& a, hipStream_t s) {
   switch (Lv) {
 #define EMS_PATTERN(LL)                                                                                 \
   case LL:                                                                                              \
-    hipLaunchKernelGGL((pattern_kernel<LL>), grid, dim3((unsigned)Shape<LL, 1>::NT), 0, s, a);          \
+    hipLaunchKernelGGL((pattern_kernel<LL, HS>), grid, dim3((unsigned)Shape<LL, 1>::NT), 0, s, a);      \
     break;
     EMS_PATTERN(2)
     EMS_PATTERN(4)
@@ -261,6 +349,22 @@ void launch_pattern(int Lv, const PatternArgs& a, hipStream_t s) {
 #undef EMS_PATTERN
     default: break;
   }
+  EMS_LAUNCH_CHECK();
+}
+
+// y pass of a.W into X[q][p][r][u], then the projection by single bins
+template <int HS> void launch_bins(int Lv, PatternArgs a, void* X, hipStream_t s) {
+  const int64_t B = (int64_t)a.nrhs * 4 * a.P;
+  FftPass fy;
+  fy.L = Lv; fy.n_in = a.ny; fy.n_out = Lv; fy.batch = (int)B;
+  fy.n_lines = a.Lu; fy.nl0 = a.Lu;
+  fy.in_s0 = B; fy.in_pt = (int64_t)a.Lu * B;
+  fy.out_s0 = B; fy.out_pt = (int64_t)a.Lu * B;
+  fy.sign = +1;
+  launch_fft_pass(fy, Cx::C128, Cx::C128, Cx::C128, a.W, X, a.tw, s);
+  a.W = static_cast<const double2*>(X);
+  hipLaunchKernelGGL((bins_kernel<HS>), dim3((unsigned)bin_blocks(a.Lu, Lv), (unsigned)a.nrhs), dim3(BIN_THREADS), 0, s,
+                     a, Lv);
   EMS_LAUNCH_CHECK();
 }
 
@@ -301,12 +405,17 @@ extern "C" emsurf_status emsurf_far_field(const emsurf_geom* geom, int32_t nx, i
     hipStream_t s = static_cast<hipStream_t>(stream);
     GreenGeomDev g;
     upload_geom(geom, g, s);
-    const int n = 4 * g.n_patch;
-    Scratch ws((size_t)ny * Lu * nrhs * n * 16);
-    lattice_dft_x(n, nx, ny, nrhs, Lu, x_dev, ws.p, s);
-    PatternArgs a = pattern_args(g, ny, nrhs, Lu, Lv, ws.p);
+    const size_t b_row = (size_t)nrhs * 4 * g.n_patch * Lu * 16, b_w = Scratch::round(ny * b_row);
+    const bool bins = by_bins(Lu, Lv, nrhs, g.n_patch, 1);
+    Scratch ws(b_w + (bins ? Lv * b_row : 0));
+    void* W = ws.part(b_w);
+    lattice_dft_x(4 * g.n_patch, nx, ny, nrhs, Lu, x_dev, W, s);
+    PatternArgs a = pattern_args(g, ny, nrhs, Lu, Lv, W);
     a.E = static_cast<double2*>(E_dev);
-    launch_pattern(Lv, a, s);
+    if (bins)
+      launch_bins<1>(Lv, a, ws.part(Lv * b_row), s);
+    else
+      launch_pattern<1>(Lv, a, s);
     EMS_HIP(hipStreamSynchronize(s));
     ws.idle();
     g.idle();
@@ -325,20 +434,24 @@ extern "C" emsurf_status emsurf_directivity(const emsurf_geom* geom, int32_t nx,
     hipStream_t s = static_cast<hipStream_t>(stream);
     GreenGeomDev g;
     upload_geom(geom, g, s);
-    const int n = 4 * g.n_patch;
-    int parts = Lu;
+    const size_t b_row = (size_t)nrhs * 4 * g.n_patch * Lu * 16, b_w = Scratch::round(ny * b_row);
+    const bool bins = by_bins(Lu, Lv, nrhs, g.n_patch, 2);
+    int parts = bins ? bin_blocks(Lu, Lv) : Lu;
     const long long per_rhs = (long long)2 * Lu * Lv;
-    const size_t b_w = Scratch::round((size_t)ny * Lu * nrhs * n * 16), b_U = Scratch::round(nrhs * per_rhs * 8);
+    const size_t b_x = bins ? Scratch::round(Lv * b_row) : 0, b_U = Scratch::round(nrhs * per_rhs * 8);
     const size_t b_part = Scratch::round((size_t)nrhs * parts * 8), b_prad = (size_t)nrhs * 8;
-    Scratch ws(b_w + b_U + b_part + 2 * Scratch::round(b_prad));
-    void* W = ws.part(b_w);
+    Scratch ws(b_w + b_x + b_U + b_part + 2 * Scratch::round(b_prad));
+    void *W = ws.part(b_w), *X = ws.part(b_x);
     double *U = ws.part<double>(b_U), *part = ws.part<double>(b_part);
     double *sums = ws.part<double>(b_prad), *prad = ws.part<double>(b_prad);
-    lattice_dft_x(n, nx, ny, nrhs, Lu, x_dev, W, s);
+    lattice_dft_x(4 * g.n_patch, nx, ny, nrhs, Lu, x_dev, W, s);
     PatternArgs a = pattern_args(g, ny, nrhs, Lu, Lv, W);
     a.U = U;
     a.part = part;
-    launch_pattern(Lv, a, s);
+    if (bins)
+      launch_bins<2>(Lv, a, X, s);
+    else
+      launch_pattern<2>(Lv, a, s);
     if (nrhs > 4) {
       // (up to four a workgroup's wavefronts add them at once)
       hipLaunchKernelGGL(power_kernel, dim3((unsigned)nrhs), dim3(64), 0, s, part, parts, sums);
