@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cstddef>
 #include <cstdint>
 #include <map>
@@ -327,7 +328,10 @@ struct TypeTiles {
   DevBuf tiles;         // int32 [n_tiles][3] = (type, start in elem_sorted, count), then [n_groups][3]
   int n_tiles = 0;
   int n_groups = 0, group_max = 0;   // larger runs of one type, for the matrix-core apply
-  std::vector<int> group_count;
+  std::vector<int> group_count, tile_count;
+  // tile form of the matrix-core apply per precision (FP64: 1) and number of
+  // right-hand sides, 0 until first asked for
+  mutable std::atomic<unsigned char> form[2][65] = {};
 };
 // y[r][m] = (axpy ? x_axpy[r][m] - : ) S_{type(m)} t[r][m]
 // types: S store type; t type; x_axpy and y types (FP64 or FP32 per ty/tx).

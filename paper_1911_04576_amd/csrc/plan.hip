@@ -351,6 +351,7 @@ void build_tiles(emsurf_plan p, const int32_t* elem_type, hipStream_t s) {
     if (top == 32 || (int64_t)p->tiles.n_groups * p->tiles.group_max <= 2 * (int64_t)M) break;
     tiles.resize(at);
   }
+  for (int i = 0; i < p->tiles.n_tiles; ++i) p->tiles.tile_count.push_back(tiles[3 * (size_t)i + 2]);
   for (int g = 0; g < p->tiles.n_groups; ++g) p->tiles.group_count.push_back(tiles[3 * (size_t)(p->tiles.n_tiles + g) + 2]);
   p->tiles.elem_sorted.alloc(order.size() * sizeof(int));
   p->tiles.tiles.alloc(tiles.size() * sizeof(int));

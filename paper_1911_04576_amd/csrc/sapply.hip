@@ -6,6 +6,8 @@
 // (rows u, columns = elements of one type) with an optional fused
 // "y = x - S t" epilogue used by the operator A = I - S T.
 #include <algorithm>
+#include <atomic>
+#include <climits>
 #include <type_traits>
 
 #include "internal.h"
@@ -211,9 +213,8 @@ struct XcdItems { int first[9]; };
 // as fast as 64 x 64 in most places where there is work for both.  y = S t, 64 rows x 64
 // columns (FP64 32) before: 4 x 4 elements, n_eq 96, 1 right-hand side, FP32
 // 11.9 -> 5.8 us, FP64 12.9 -> 9.0; 48 x 40, n_eq 96, 12: 40 -> 26, 64 -> 50;
-// 61 x 61, n_eq 288, 12: 332 -> 301 (98 TFLOP/s), 650 -> 596.  Where 64 rows
-// divide n_eq and work is plentiful it gives a little back (128 x 128, n_eq
-// 192, 12: 555 -> 588, 1129 -> 1171); a second tile for that was not kept.
+// 61 x 61, n_eq 288, 12: 332 -> 301 (98 TFLOP/s), 650 -> 596.  The wide tile
+// below is the better one in other places (s_form).
 template <typename T, typename VX, int RT>
 __global__ void __launch_bounds__(SA_THREADS, 3) apply_S_mfma_kernel(
     const T* __restrict__ Sp, const int* __restrict__ elem_sorted, const int* __restrict__ groups, int n, int M,
@@ -422,6 +423,243 @@ __global__ void __launch_bounds__(SA_THREADS, 3) apply_S_mfma_kernel(
   }
 }
 
+// The wide tile: 64 rows (SW_UT row tiles) x 64 columns in FP32, x 32 in FP64.
+// Work items w = (type tile * nub + row block) * ncb + column block, in type
+// order, XCD x takes the contiguous items [x per, (x + 1) per).  Wavefront
+// (wc, wu) = (w % 2, w / 2) takes column tiles CTW wc .. CTW wc + CTW - 1 and
+// row tiles 4 wu .. 4 wu + 3 of the item.  Twice (FP32 four times) the products
+// of a 32 x 32 item for less traffic into the LDS: better where work is
+// plentiful and 64 rows divide n, and where its items just fill a round of the
+// chip (s_form below).  Every output is the same sequence of products as in
+// the kernel above.
+constexpr int SW_UT = 8;
+// columns per workgroup: two wavefronts across, CTW column tiles of 16 each
+template <int CTW> constexpr int sw_cols() { return 32 * CTW; }
+template <typename T, typename VX, int CTW>
+__global__ void __launch_bounds__(SA_THREADS, sizeof(T) == 8 ? 3 : 2) apply_S_wide_kernel(
+    const T* __restrict__ Sp, const int* __restrict__ elem_sorted, const int* __restrict__ tiles, int n, int M,
+    int nrhs, int ncb, int nub, int items, int per, const typename SM<T>::V2* __restrict__ t,
+    const VX* __restrict__ x_axpy, VX* __restrict__ y) {
+  using V2 = typename SM<T>::V2;
+  using C = typename SM<T>::C;
+  using Acc = typename SM<T>::Acc;
+  using R = typename Real<VX>::T;
+  constexpr int CH = 16 / (int)sizeof(T), NCH = 8 / CH;
+  constexpr int NCOL = sw_cols<CTW>(), NAC = (NCOL + 63) / 64;   // columns staged per thread
+  constexpr int NBC = SW_UT * 512 / CH / SA_THREADS;   // macromodel chunks staged per thread
+  // a k-tile of the vectors in A-lane order and of the packed macromodels;
+  // two buffers: the next k-tile is staged while the current one is used.
+  // At the end the same memory holds the output tile, rows of YROW values
+  // (64 rows u x (re, im) and padding: the rows start 16 banks apart)
+  // (FP64 keeps one macromodel buffer: 48 KB of LDS, three workgroups per CU,
+  // for a second barrier per k-tile)
+  constexpr int NB = sizeof(T) == 8 ? 1 : 2;
+  constexpr int AS = 2 * CTW * 512, BS = SW_UT * 512;
+  constexpr int YROW = sizeof(T) == 4 ? 132 : 144;
+  constexpr int LDS_T = 2 * AS + NB * BS > NCOL * YROW ? 2 * AS + NB * BS : NCOL * YROW;
+  __shared__ __align__(16) T lds[LDS_T];
+  auto As = [&](int bf) { return lds + bf * AS; };
+  auto Bs = [&](int bf) { return lds + 2 * AS + (NB == 2 ? bf : 0) * BS; };
+  const int w = (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
+  if (w >= items) return;   // the whole workgroup: no barrier reached
+  const int cb = w % ncb, tub = w / ncb, tile = tub / nub, ub = tub - tile * nub;
+  const int type = tiles[3 * tile], start = tiles[3 * tile + 1], count = tiles[3 * tile + 2];
+  const int ncols = nrhs * count, col0 = cb * NCOL;
+  if (col0 >= ncols) return;   // the whole workgroup: no barrier reached
+  const int nut = s_row_tiles(n), nvt = s_k_tiles(n);
+  const int ut0 = ub * SW_UT;
+  const T* St = Sp + (long long)type * nut * nvt * 512;
+  const int tid = threadIdx.x, l = tid & 63, wv = tid >> 6, wc = wv & 1, wu = wv >> 1;
+  // A staging: columns ac + 64 g of the block, source indices 4 aq .. 4 aq + 3 of the k-tile
+  const int ac = tid >> 2, aq = tid & 3;
+  // Element indices of the block's columns: the input columns of this
+  // thread's A staging (NAC) and the output chunks' columns (NXC), loaded
+  // at a clamped index without conditions and all before the first is used
+  // (the compiler barrier keeps them from sinking into the conditional
+  // blocks that use them, where each would cost a wait of its own)
+  constexpr int XC = 16 / (2 * (int)sizeof(R)), CPC = 64 / XC, NXC = NCOL * CPC / SA_THREADS;
+  int el_a[NAC], el_x[NXC];
+#pragma unroll
+  for (int g = 0; g < NAC; ++g) {
+    const int acol = col0 + ac + 64 * g;
+    const bool ok = ac + 64 * g < NCOL && acol < ncols;
+    el_a[g] = elem_sorted[start + (ok ? acol % count : 0)];
+  }
+#pragma unroll
+  for (int k = 0; k < NXC; ++k) {
+    const int col = col0 + (tid + SA_THREADS * k) / CPC;
+    el_x[k] = elem_sorted[start + (col < ncols ? col % count : 0)];
+  }
+  asm volatile("" ::: "memory");
+  const V2* tcol[NAC];
+#pragma unroll
+  for (int g = 0; g < NAC; ++g) {
+    const int acol = col0 + ac + 64 * g;
+    const bool ok = ac + 64 * g < NCOL && acol < ncols;
+    tcol[g] = ok ? t + ((long long)(acol / count) * M + el_a[g]) * n : nullptr;
+  }
+  V2 an[NAC][4];
+  auto load_a = [&](int vt) {
+#pragma unroll
+    for (int g = 0; g < NAC; ++g)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int v = vt * 16 + 4 * aq + i;
+        an[g][i] = (tcol[g] != nullptr && v < n) ? tcol[g][v] : V2{0, 0};
+      }
+  };
+  // the workgroup's SW_UT row tiles of the packed macromodels (zero past n)
+  C bn[NBC];
+  auto load_b = [&](int vt) {
+#pragma unroll
+    for (int j = 0; j < NBC; ++j) {
+      const int ci = tid + SA_THREADS * j, bu = ci / (512 / CH), wi = ci - bu * (512 / CH);
+      bn[j] = ut0 + bu < nut ? *reinterpret_cast<const C*>(St + ((long long)(ut0 + bu) * nvt + vt) * 512 + wi * CH)
+                             : C{};
+    }
+  };
+  // A-lane position of this thread's values: lane (2 h + p) 16 + ac % 16 of column tile ac / 16 + 4 g
+  const int ah = aq >> 1, as0 = 4 * (aq & 1), act = ac >> 4, a16 = ac & 15;
+  Acc acc[CTW][4];
+#pragma unroll
+  for (int i = 0; i < CTW; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = Acc{};
+  R* yr = reinterpret_cast<R*>(y);
+  const R* xr = reinterpret_cast<const R*>(x_axpy);
+  // stage the k-tile held in an and bn into LDS buffer bf (whose previous
+  // contents every wavefront has used: a barrier lies between)
+  auto stage = [&](int bf) {
+#pragma unroll
+    for (int g = 0; g < NAC; ++g)
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {
+        if (ac + 64 * g >= NCOL) break;
+        const int L = (2 * ah + p) * 16 + a16;
+        T* dst = As(bf) + (act + 4 * g) * 512;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int s = as0 + i;
+          dst[(s / CH) * 64 * CH + L * CH + s % CH] = p == 0 ? an[g][i].x : an[g][i].y;
+        }
+      }
+#pragma unroll
+    for (int j = 0; j < NBC; ++j) *reinterpret_cast<C*>(Bs(bf) + (tid + SA_THREADS * j) * CH) = bn[j];
+  };
+  // the products of the k-tile staged in buffer bf
+  auto products = [&](int bf) {
+    C a[CTW][NCH], b[4][NCH];
+#pragma unroll
+    for (int i = 0; i < CTW; ++i)
+#pragma unroll
+      for (int m = 0; m < NCH; ++m)
+        a[i][m] = *reinterpret_cast<const C*>(As(bf) + (CTW * wc + i) * 512 + m * 64 * CH + l * CH);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int m = 0; m < NCH; ++m)
+        b[j][m] = *reinterpret_cast<const C*>(Bs(bf) + (4 * wu + j) * 512 + m * 64 * CH + l * CH);
+#pragma unroll
+    for (int s = 0; s < 8; ++s)
+#pragma unroll
+      for (int i = 0; i < CTW; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = SM<T>::mfma(a[i][s / CH][s % CH], b[j][s / CH][s % CH], acc[i][j]);
+  };
+  // Output chunks of 16 bytes (XC complex values of x and y): chunk k of
+  // this thread is column c = k-th chunk / (64 / XC), rows 8 ut0 + XC (chunk
+  // % (64 / XC)) + 0 .. XC - 1.  Whole chunks where n allows 16-byte access
+  // (n even for FP32 vectors); value by value otherwise.
+  using XV = typename std::conditional<sizeof(R) == 4, f4, d2>::type;
+  const bool whole = XC == 1 || (n & 1) == 0;
+  // twice the vector offset (in reals) of the column of each chunk, -1 past the block's columns
+  long long colbase[NXC];
+#pragma unroll
+  for (int k = 0; k < NXC; ++k) {
+    const int col = col0 + (tid + SA_THREADS * k) / CPC;
+    colbase[k] = col < ncols ? 2 * (((long long)(col / count) * M + el_x[k]) * n) : -1;
+  }
+  // the vectors of the fused y = x - S t, requested before the last products
+  XV xv[NXC];
+  auto load_x = [&]() {
+    if (!xr) return;
+#pragma unroll
+    for (int k = 0; k < NXC; ++k) {
+      const int ch = tid + SA_THREADS * k, c = ch / CPC, u = 8 * ut0 + XC * (ch - c * CPC);
+      const long long b = colbase[k];
+      xv[k] = XV{};
+      if (b >= 0 && whole && u + XC <= n) {
+        xv[k] = *reinterpret_cast<const XV*>(xr + b + 2 * u);
+      } else if (b >= 0) {
+#pragma unroll
+        for (int z = 0; z < 2 * XC; ++z)
+          if (u + z / 2 < n) xv[k][z] = xr[b + 2 * u + z];
+      }
+    }
+  };
+  load_a(0);
+  load_b(0);
+  stage(0);
+  __syncthreads();
+  for (int vt = 0; vt + 1 < nvt; ++vt) {
+    load_a(vt + 1);   // the next k-tile is on its way during the products
+    load_b(vt + 1);
+    products(vt & 1);
+    if constexpr (NB == 1) __syncthreads();   // (one buffer: every read of it precedes the next fill)
+    stage((vt + 1) & 1);
+    __syncthreads();
+  }
+  load_x();
+  products((nvt - 1) & 1);
+  // the output tile through LDS: every wavefront is past its last reads first
+  __syncthreads();
+  {
+    const int jj = l & 15, q = jj >> 3;
+#pragma unroll
+    for (int i = 0; i < CTW; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int c = 16 * (CTW * wc + i) + SM<T>::row(l, e);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) lds[c * YROW + 2 * (8 * (4 * wu + j) + (jj & 7)) + q] = acc[i][j][e];
+      }
+  }
+  __syncthreads();
+  // (the loads of x all complete here, once: the stores below sit in
+  // conditional blocks, and a load still counted as pending at each block's
+  // join would cost a wait for every store before it)
+  __builtin_amdgcn_s_waitcnt(0);
+#pragma unroll
+  for (int k = 0; k < NXC; ++k) {
+    const int ch = tid + SA_THREADS * k, c = ch / CPC, ul = XC * (ch - c * CPC), u = 8 * ut0 + ul;
+    const long long b = colbase[k];
+    if (b < 0 || u >= n) continue;
+    XV v;
+#pragma unroll
+    for (int z = 0; z < 2 * XC; ++z) v[z] = static_cast<R>(lds[c * YROW + 2 * ul + z]);
+    if (xr) v = xv[k] - v;
+    if (whole && u + XC <= n) {
+      *reinterpret_cast<XV*>(yr + b + 2 * u) = v;
+    } else {
+#pragma unroll
+      for (int z = 0; z < 2 * XC; ++z)
+        if (u + z / 2 < n) yr[b + 2 * u + z] = v[z];
+    }
+  }
+}
+
+template <typename T, typename VX, int CTW = sizeof(T) == 4 ? 2 : 1>
+void launch_wide(const void* Sp, const TypeTiles& tl, int n, int M, int nrhs, const void* t, const void* x, void* y,
+                 hipStream_t s) {
+  const int64_t ncb = ((int64_t)nrhs * TC + sw_cols<CTW>() - 1) / sw_cols<CTW>(), nub = (s_row_tiles(n) + SW_UT - 1) / SW_UT;
+  const int64_t items = tl.n_tiles * ncb * nub, per = (items + 7) / 8;
+  EMS_CHECK_ARG(items + 8 <= 0x7fffffffLL, "too many macromodel tiles");
+  hipLaunchKernelGGL((apply_S_wide_kernel<T, VX, CTW>), dim3((unsigned)(8 * per)), dim3(SA_THREADS), 0, s,
+                     static_cast<const T*>(Sp), tl.elem_sorted.as<const int>(), tl.tiles.as<const int>(), n, M, nrhs,
+                     (int)ncb, (int)nub, (int)items, (int)per, static_cast<const typename SM<T>::V2*>(t),
+                     static_cast<const VX*>(x), static_cast<VX*>(y));
+}
+
 // column blocks of a group of count elements
 inline int64_t s_col_blocks(int nrhs, int count) { return ((int64_t)nrhs * count + SA_COLS - 1) / SA_COLS; }
 
@@ -432,16 +670,15 @@ template <int RT> int64_t s_live_items(const TypeTiles& tl, int n, int nrhs) {
   return cbs * ((n + sa_rows<RT>() - 1) / sa_rows<RT>());
 }
 
-template <typename T, typename VX, int RT>
-void launch_mfma_tile(const void* Sp, const TypeTiles& tl, int n, int M, int nrhs, const void* t, const void* x,
-                      void* y, hipStream_t s) {
+// shares of the items among the XCDs
+template <int RT> XcdItems xcd_items(const TypeTiles& tl, int n, int nrhs) {
   const int64_t ncb = s_col_blocks(nrhs, tl.group_max), nub = (n + sa_rows<RT>() - 1) / sa_rows<RT>();
   const int64_t items = tl.n_groups * ncb * nub;
   EMS_CHECK_ARG(items + 8 <= 0x7fffffffLL, "too many macromodel tiles");
   const int64_t live = s_live_items<RT>(tl, n, nrhs);
   int64_t before = 0;
   XcdItems span;
-  int k = 0, longest = 0;
+  int k = 0;
   if (live < 2048) {
     // below 8 items per CU equal shares of all items, whole types together:
     // 32 x 32 elements, n_eq 192, 4 right-hand sides, FP32 21.5 us against
@@ -457,25 +694,126 @@ void launch_mfma_tile(const void* Sp, const TypeTiles& tl, int n, int M, int nrh
     }
   }
   span.first[8] = (int)items;
-  for (k = 0; k < 8; ++k) longest = std::max(longest, span.first[k + 1] - span.first[k]);
+  return span;
+}
+
+template <typename T, typename VX, int RT>
+void launch_mfma_tile(const void* Sp, const TypeTiles& tl, int n, int M, int nrhs, const void* t, const void* x,
+                      void* y, hipStream_t s) {
+  const int64_t ncb = s_col_blocks(nrhs, tl.group_max), nub = (n + sa_rows<RT>() - 1) / sa_rows<RT>();
+  const XcdItems span = xcd_items<RT>(tl, n, nrhs);
+  int longest = 0;
+  for (int k = 0; k < 8; ++k) longest = std::max(longest, span.first[k + 1] - span.first[k]);
   hipLaunchKernelGGL((apply_S_mfma_kernel<T, VX, RT>), dim3((unsigned)(8 * longest)), dim3(SA_THREADS), 0, s,
                      static_cast<const T*>(Sp), tl.elem_sorted.as<const int>(),
                      tl.tiles.as<const int>() + 3 * (size_t)tl.n_tiles, n, M, nrhs, (int)ncb, (int)nub, span,
                      static_cast<const typename SM<T>::V2*>(t), static_cast<const VX*>(x), static_cast<VX*>(y));
 }
 
+// Items on the fullest of an XCD's 32 CUs, and that number for the items with
+// columns of the XCD that has most of them
+int rounds(int64_t most) { return (int)((most + 31) / 32); }
+
+template <int RT> int s_rounds(const TypeTiles& tl, int n, int nrhs) {
+  const int64_t ncb = s_col_blocks(nrhs, tl.group_max), nub = (n + sa_rows<RT>() - 1) / sa_rows<RT>();
+  const XcdItems span = xcd_items<RT>(tl, n, nrhs);
+  int64_t most = 0, here = 0;
+  int k = 0;
+  for (int g = 0; g < tl.n_groups; ++g) {
+    // items [lo, hi) have columns
+    int64_t lo = g * ncb * nub;
+    const int64_t hi = lo + s_col_blocks(nrhs, tl.group_count[g]) * nub;
+    while (lo < hi) {
+      while (k < 7 && lo >= span.first[k + 1]) {
+        most = std::max(most, here);
+        here = 0;
+        ++k;
+      }
+      const int64_t to = std::min<int64_t>(hi, k < 7 ? span.first[k + 1] : hi);
+      here += to - lo;
+      lo = to;
+    }
+  }
+  return rounds(std::max(most, here));
+}
+
+// the same of the wide tile (and one item more, as its XCDs' shares end inside
+// a type); INT_MAX where more than a fifth of its items have no columns
+int wide_rounds(const TypeTiles& tl, int n, int nrhs, int cols) {
+  const int64_t ncb = ((int64_t)nrhs * TC + cols - 1) / cols, nub = (s_row_tiles(n) + SW_UT - 1) / SW_UT;
+  const int64_t items = tl.n_tiles * ncb * nub, per = (items + 7) / 8;
+  int64_t most = 0, here = 0, all = 0, end = per;
+  for (int i = 0; i < tl.n_tiles; ++i) {
+    const int64_t live = ((int64_t)nrhs * tl.tile_count[i] + cols - 1) / cols;
+    all += live * nub;
+    for (int64_t ub = 0; ub < nub; ++ub) {
+      int64_t lo = (i * nub + ub) * ncb;
+      const int64_t hi = lo + live;
+      while (lo < hi) {
+        while (lo >= end) {
+          most = std::max(most, here);
+          here = 0;
+          end += per;
+        }
+        const int64_t to = std::min(hi, end);
+        here += to - lo;
+        lo = to;
+      }
+    }
+  }
+  return 5 * all < 4 * items ? INT_MAX : rounds(std::max(most, here) + 1);
+}
+
+enum SForm : unsigned char { S_UNKNOWN, S_ROWS32, S_ROWS48, S_WIDE };
+
+// Tile of an apply: the shortest estimated time, from the items that the
+// fullest CU has (three workgroups at a time in FP64, so that a round begun
+// costs more than its share).  Microseconds per 16 values of n_eq, fitted to
+// 1213 applies a precision (12 x 12 to 128 x 128 elements, n_eq 64 to 384, 4 to 64
+// types, 1 to 24 right-hand sides): FP64 0.69 an item of 32 rows, 1.0 of 48, 1.25
+// wide; FP32 0.33 and 1.2.  Against one tile for all of them: 48 rows for the
+// plentiful cost 1.3 times at n_eq 64 (two blocks of 48 rows), 1.1 at 128 and 256;
+// 128 x 128, n_eq 256, 12 right-hand sides FP64 2216 -> 1950 us wide, FP32 1022 ->
+// 951; 64 x 64, n_eq 192, 1 right-hand side FP64 57 -> 37.
+SForm s_form(const TypeTiles& tl, int n, int nrhs, bool f64) {
+  constexpr double e32[3] = {0.6, 1.2, 1.0}, e48[3] = {0.5, 1.4, 1.2};
+  const int m = s_rounds<2>(tl, n, nrhs), w = wide_rounds(tl, n, nrhs, f64 ? sw_cols<1>() : sw_cols<2>());
+  double best = f64 ? 0.69 * (m + e32[m % 3]) : 0.331 * (m + 0.6);
+  SForm form = S_ROWS32;
+  if (f64) {
+    const int m3 = s_rounds<3>(tl, n, nrhs);
+    const double t = m3 + e48[m3 % 3];
+    if (t < best) {
+      best = t;
+      form = S_ROWS48;
+    }
+  }
+  const double wide = f64 ? 1.25 * (w + 0.7) : 1.2 * (w + 0.5);
+  return wide < 0.97 * best ? S_WIDE : form;
+}
+
 template <typename T, typename VX>
 void launch_mfma_typed(const void* Sp, const TypeTiles& tl, int n, int M, int nrhs, const void* t, const void* x,
                        void* y, hipStream_t s) {
-  // 48 rows in FP64 from 16 items of 32 rows per CU (61 x 61, n_eq 288, 12
-  // right-hand sides: 596 us against 616; 20 x 20: 98 against 79), or where
-  // three workgroups per CU are just too few for the items of 32 rows (32 x 32,
-  // n_eq 192, 4: 41.5 against 45.3)
-  const int64_t two = s_live_items<2>(tl, n, nrhs);
-  if (sizeof(T) == 8 && (two >= 4096 || (two > 768 && s_live_items<3>(tl, n, nrhs) <= 640)))
-    launch_mfma_tile<T, VX, 3>(Sp, tl, n, M, nrhs, t, x, y, s);
-  else
-    launch_mfma_tile<T, VX, 2>(Sp, tl, n, M, nrhs, t, x, y, s);
+  // (the plan keeps the form of each number of right-hand sides)
+  const bool f64 = sizeof(T) == 8;
+  std::atomic<unsigned char>* kept = nrhs >= 1 && nrhs <= 64 ? &tl.form[f64][nrhs] : nullptr;
+  unsigned char form = kept ? kept->load(std::memory_order_relaxed) : S_UNKNOWN;
+  if (form == S_UNKNOWN) {
+    form = s_form(tl, n, nrhs, f64);
+    if (kept) kept->store(form, std::memory_order_relaxed);
+  }
+  if (form == S_WIDE) {
+    launch_wide<T, VX>(Sp, tl, n, M, nrhs, t, x, y, s);
+    return;
+  }
+  if constexpr (sizeof(T) == 8) {
+    if (form == S_ROWS48) {
+      launch_mfma_tile<T, VX, 3>(Sp, tl, n, M, nrhs, t, x, y, s);
+      return;
+    }
+  }
+  launch_mfma_tile<T, VX, 2>(Sp, tl, n, M, nrhs, t, x, y, s);
 }
 
 }  // namespace
