@@ -96,7 +96,7 @@ struct DevBuf {
 
 // Device workspace of one call that waits for its stream before it returns:
 // taken from the blocks that earlier calls left idle (the smallest that
-// holds n bytes), else allocated.  The call says idle() once nothing on the
+// holds n bytes, unless it is more than twice as large), else allocated.  The call says idle() once nothing on the
 // device uses the block any more; it is then kept for later calls of any
 // thread and stream.  At most SCRATCH_KEPT idle bytes are kept per device
 // (least recently used freed first); all are freed when the last plan of the

@@ -40,12 +40,18 @@ void free_blocks(const std::vector<Idle>& blocks) {
 
 Scratch::Scratch(size_t n) {
   EMS_HIP(hipGetDevice(&dev_));
+  const size_t unit = 2u << 20;
+  const size_t want = std::max<size_t>(1, (n + unit - 1) / unit) * unit;
   {
+    // the smallest block that holds n, of at most twice the bytes: a box
+    // geometry of 2 KB would hold a workspace of GB, and the call's own
+    // workspace be allocated anew
     std::lock_guard<std::mutex> lk(g_mu);
     auto& v = idle_blocks();
     auto best = v.end();
     for (auto it = v.begin(); it != v.end(); ++it)
-      if (it->dev == dev_ && it->bytes >= n && (best == v.end() || it->bytes < best->bytes)) best = it;
+      if (it->dev == dev_ && it->bytes >= n && it->bytes <= 2 * want && (best == v.end() || it->bytes < best->bytes))
+        best = it;
     if (best != v.end()) {
       p = best->p;
       bytes = best->bytes;
@@ -53,8 +59,6 @@ Scratch::Scratch(size_t n) {
       return;
     }
   }
-  const size_t unit = 2u << 20;
-  const size_t want = std::max<size_t>(1, (n + unit - 1) / unit) * unit;
   device_malloc(&p, want);
   bytes = want;
 }

@@ -1,0 +1,64 @@
+"""Device memory that the library keeps between calls, by the card's free bytes."""
+import gc
+
+import numpy as np
+import pytest
+
+import workload as W
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+MB = 1 << 20
+
+
+def free():
+    torch.cuda.synchronize()
+    return torch.cuda.mem_get_info()[0]
+
+
+def box(E, P=24):
+    g = W.box_geometry(24)
+    return E.Geometry(g.rho[:P], g.area[:P], g.tan[:P], W.PITCH, W.K0)
+
+
+def nothing_kept(E):
+    """The process's last plan gives everything back."""
+    gc.collect()
+    S, tm = np.zeros((1, 96, 96), complex), np.zeros((1, 1), np.int32)
+    E.emsurf_plan_create_green(1, 1, 1, 1, box(E), S, tm, store=E.EMSURF_STORE_FP64).destroy()
+
+
+class Macromodels:
+    """Calls whose workspace is half a MB per cell type."""
+
+    def __init__(self, E, types, n=64, m=64):
+        self.E, self.args = E, (types, n, m)
+        self.z = torch.eye(n + m, dtype=torch.complex128, device="cuda").repeat(types, 1, 1)
+        self.out = torch.empty((types, n, n), dtype=torch.complex128, device="cuda")
+
+    def __call__(self):
+        self.E.emsurf_macromodels(*self.args, self.z, None, self.out)
+        return free()
+
+
+class Pattern:
+    """Calls whose workspace is nrhs Lu / 64 MB and a little more."""
+
+    def __init__(self, E, nrhs, Lu=64, P=16):
+        self.E, self.args = E, (box(E, P), 4, 16, nrhs, Lu, 64)
+        self.x = torch.ones((nrhs, 16, 4, 4 * P), dtype=torch.complex128, device="cuda")
+        self.D = torch.empty((nrhs, 2, 64, Lu), dtype=torch.float64, device="cuda")
+
+    def __call__(self):
+        self.E.emsurf_directivity(*self.args, self.x, self.D)
+        return free()
+
+
+def test_a_small_request_does_not_take_a_large_block():
+    """The pattern's workspace of 70 MB takes over the macromodels' 100 MB, which its geometry's 2 KB do not hold."""
+    import paper_1911_04576_amd as E
+    nothing_kept(E)
+    macromodels, pattern = Macromodels(E, 200), Pattern(E, 64)
+    before = macromodels()
+    assert abs(before - pattern()) < 16 * MB
+    assert abs(before - pattern()) < 16 * MB
