@@ -72,7 +72,9 @@ Scratch::~Scratch() {
 void Scratch::idle() {
   if (!p) return;
   std::vector<Idle> drop;
-  {
+  if (bytes > SCRATCH_KEPT) {
+    drop.push_back({dev_, p, bytes});   // (no other block would make room for it)
+  } else {
     std::lock_guard<std::mutex> lk(g_mu);
     auto& v = idle_blocks();
     size_t held = bytes;
@@ -84,10 +86,7 @@ void Scratch::idle() {
       drop.push_back(*it);
       it = v.erase(it);
     }
-    if (held <= SCRATCH_KEPT)
-      v.push_back({dev_, p, bytes});
-    else
-      drop.push_back({dev_, p, bytes});
+    v.push_back({dev_, p, bytes});
   }
   p = nullptr;
   bytes = 0;

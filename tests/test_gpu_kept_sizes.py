@@ -42,11 +42,11 @@ class Macromodels:
 
 
 class Pattern:
-    """Calls whose workspace is nrhs Lu / 64 MB and a little more."""
+    """Calls whose workspace is nrhs ny Lu / 1024 MB and a little more."""
 
-    def __init__(self, E, nrhs, Lu=64, P=16):
-        self.E, self.args = E, (box(E, P), 4, 16, nrhs, Lu, 64)
-        self.x = torch.ones((nrhs, 16, 4, 4 * P), dtype=torch.complex128, device="cuda")
+    def __init__(self, E, nrhs, ny=16, Lu=64, P=16):
+        self.E, self.args = E, (box(E, P), 4, ny, nrhs, Lu, 64)
+        self.x = torch.ones((nrhs, ny, 4, 4 * P), dtype=torch.complex128, device="cuda")
         self.D = torch.empty((nrhs, 2, 64, Lu), dtype=torch.float64, device="cuda")
 
     def __call__(self):
@@ -61,4 +61,13 @@ def test_a_small_request_does_not_take_a_large_block():
     macromodels, pattern = Macromodels(E, 200), Pattern(E, 64)
     before = macromodels()
     assert abs(before - pattern()) < 16 * MB
+    assert abs(before - pattern()) < 16 * MB
+
+
+def test_a_block_beyond_the_limit_leaves_the_others():
+    """A workspace of 4.6 GB cannot be kept; the macromodels' 100 MB still are."""
+    import paper_1911_04576_amd as E
+    nothing_kept(E)
+    macromodels, pattern = Macromodels(E, 200), Pattern(E, 64, ny=64, Lu=1024, P=18)
+    before = macromodels()
     assert abs(before - pattern()) < 16 * MB
