@@ -63,9 +63,14 @@ class HostPool {
   HostBlock take(size_t n) {
     HostBlock b;
     b.pool = this;
+    const size_t unit = 1u << 20, want = std::max<size_t>(1, (n + unit - 1) / unit) * unit;
+    // the smallest idle block that holds n, of at most twice the bytes
     auto best = idle_.end();
-    for (auto it = idle_.begin(); it != idle_.end(); ++it)
-      if (it->second >= n && (best == idle_.end() || it->second < best->second)) best = it;
+    size_t idle = 0;
+    for (auto it = idle_.begin(); it != idle_.end(); ++it) {
+      idle += it->second;
+      if (it->second >= n && it->second <= 2 * want && (best == idle_.end() || it->second < best->second)) best = it;
+    }
     if (best != idle_.end()) {
       b.p = best->first;
       b.bytes = best->second;
@@ -73,18 +78,20 @@ class HostPool {
       idle_.erase(best);
       return b;
     }
-    const size_t unit = 1u << 20, want = std::max<size_t>(1, (n + unit - 1) / unit) * unit;
-    // idle blocks that were too small make way
-    while (!idle_.empty() && pinned_ + want > HOST_PINNED) {
-      (void)hipHostFree(idle_.back().first);
-      pinned_ -= idle_.back().second;
-      idle_.pop_back();
-    }
-    if (pinned_ + want <= HOST_PINNED && hipHostMalloc(&b.p, want, hipHostMallocDefault) == hipSuccess) {
-      pinned_ += want;
-      b.bytes = want;
-      b.pinned = true;
-      return b;
+    // beside the blocks in use there is room for it, once idle blocks have
+    // made way, the least recently used first
+    if (pinned_ - idle + want <= HOST_PINNED) {
+      while (pinned_ + want > HOST_PINNED) {
+        (void)hipHostFree(idle_.front().first);
+        pinned_ -= idle_.front().second;
+        idle_.erase(idle_.begin());
+      }
+      if (hipHostMalloc(&b.p, want, hipHostMallocDefault) == hipSuccess) {
+        pinned_ += want;
+        b.bytes = want;
+        b.pinned = true;
+        return b;
+      }
     }
     (void)hipGetLastError();
     b.p = std::malloc(std::max<size_t>(1, n));
