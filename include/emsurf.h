@@ -244,8 +244,8 @@ emsurf_status emsurf_fill_LK_point_green(const emsurf_geom* geom, int32_t nx, in
  *   Zt_dev     c128 [n_types][n_eq][n_eq] output of Z~, or NULL.
  * 1 <= n_types <= 4096, 1 <= n_eq <= 512, 0 <= n_int <= 4096.  Workspaces of
  * n_types ((n_eq + n_int)^2 + 4 n_eq^2) complex values are taken for the
- * call from memory that the library keeps (at most 4 GiB per device, freed with
- * the process's last plan and whenever an allocation fails).  Part of the
+ * call from memory that the library keeps (at most 4 GiB per device; see
+ * emsurf_release_idle_memory).  Part of the
  * elimination runs on a second stream that the library creates once per device
  * (default priority) and joins back into `stream`; the call blocks until
  * `stream` is done.  A singular Z_int,int or Z~ + Z_self (a zero
@@ -580,6 +580,15 @@ size_t emsurf_server_slot_bytes(emsurf_server server, const emsurf_plan_desc* de
 void emsurf_server_destroy(emsurf_server server);
 
 void emsurf_plan_destroy(emsurf_plan plan);
+
+/* Frees the device memory that the library keeps between calls for the
+ * workspaces of plan creation, macromodels and patterns (idle blocks, at most
+ * 4 GiB per device).  It is also freed with the process's last plan and where
+ * an allocation of the library fails; a process without plans, or one whose
+ * other allocators need the memory, calls this.  Waits for the devices that
+ * hold blocks; calls that are running keep theirs. */
+emsurf_status emsurf_release_idle_memory(void);
+
 const char* emsurf_status_str(emsurf_status s);
 const char* emsurf_last_error(void);
 

@@ -184,6 +184,7 @@ _SIGS = {
     "emsurf_server_destroy": (None, [_P]),
     "emsurf_server_entry_bytes": (ctypes.c_size_t, [_P, ctypes.POINTER(emsurf_plan_desc)]),
     "emsurf_server_slot_bytes": (ctypes.c_size_t, [_P, ctypes.POINTER(emsurf_plan_desc)]),
+    "emsurf_release_idle_memory": (ctypes.c_int, []),
     "emsurf_status_str": (ctypes.c_char_p, [ctypes.c_int]),
     "emsurf_last_error": (ctypes.c_char_p, []),
 }
@@ -549,6 +550,11 @@ def emsurf_kernel_times(plan: Plan):
     cnt = (ctypes.c_int64 * 5)()
     _check(lib().emsurf_kernel_times(plan.h, ms, cnt))
     return {p: (ms[i], cnt[i]) for i, p in enumerate(PHASES)}
+
+
+def emsurf_release_idle_memory():
+    """Frees the device memory that the library keeps between calls."""
+    _check(lib().emsurf_release_idle_memory())
 
 
 def emsurf_status_str(st: int) -> str:

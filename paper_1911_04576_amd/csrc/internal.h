@@ -100,7 +100,8 @@ struct DevBuf {
 // device uses the block any more; it is then kept for later calls of any
 // thread and stream.  At most SCRATCH_KEPT idle bytes are kept per device
 // (least recently used freed first); all are freed when the last plan of the
-// process is destroyed and when an allocation of the library fails.
+// process is destroyed, when an allocation of the library fails and by
+// emsurf_release_idle_memory.
 constexpr size_t SCRATCH_KEPT = (size_t)4 << 30;
 class Scratch {
  public:

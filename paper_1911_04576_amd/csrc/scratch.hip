@@ -126,3 +126,8 @@ void plan_closed() {
 }
 
 }  // namespace emsurf
+
+extern "C" emsurf_status emsurf_release_idle_memory(void) {
+  emsurf::scratch_give_back();
+  return EMSURF_OK;
+}

@@ -71,3 +71,18 @@ def test_a_block_beyond_the_limit_leaves_the_others():
     macromodels, pattern = Macromodels(E, 200), Pattern(E, 64, ny=64, Lu=1024, P=18)
     before = macromodels()
     assert abs(before - pattern()) < 16 * MB
+
+
+def test_kept_memory_is_released_on_request():
+    """Without a plan nothing else gives it back."""
+    import paper_1911_04576_amd as E
+    nothing_kept(E)
+    macromodels, pattern = Macromodels(E, 200), Pattern(E, 64)
+    macromodels()
+    E.emsurf_release_idle_memory()
+    before = free()                       # (what the first calls load once is loaded)
+    assert before - macromodels() > 90 * MB
+    pattern()
+    E.emsurf_release_idle_memory()
+    assert abs(before - free()) < 16 * MB
+    assert before - pattern() > 60 * MB   # and the calls work on
