@@ -540,7 +540,8 @@ void emsurf_session_destroy(emsurf_session session);
  * inputs are copied at submit. */
 typedef struct emsurf_server_s* emsurf_server;
 typedef struct {
-  size_t budget_bytes;        /* device bytes plans + sessions may hold */
+  size_t budget_bytes;        /* device bytes plans + sessions may hold; the library's kept call workspaces are
+                               * freed after admissions where they go beyond what these leave of it */
   int32_t max_slots;          /* slots per session = largest nrhs of a request, 1..64 */
   uint32_t store;             /* EMSURF_STORE_* of every plan */
   emsurf_solve_opts opts;     /* solve options of every request */

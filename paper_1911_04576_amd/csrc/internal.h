@@ -124,6 +124,8 @@ class Scratch {
   int dev_ = 0;
   size_t used_ = 0;
 };
+// bytes of the current device's idle blocks
+size_t scratch_idle_bytes();
 // free every idle block; whether there was one
 bool scratch_give_back();
 // plans of the process: the last one closed gives the idle blocks back

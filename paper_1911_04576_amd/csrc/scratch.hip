@@ -93,6 +93,16 @@ void Scratch::idle() {
   free_blocks(drop);
 }
 
+size_t scratch_idle_bytes() {
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return 0;
+  std::lock_guard<std::mutex> lk(g_mu);
+  size_t held = 0;
+  for (const Idle& b : idle_blocks())
+    if (b.dev == dev) held += b.bytes;
+  return held;
+}
+
 bool scratch_give_back() {
   std::vector<Idle> drop;
   {

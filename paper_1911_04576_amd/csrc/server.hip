@@ -321,6 +321,14 @@ void admit(emsurf_server sv) {
     sv->active[id] = std::move(*it);
     return sv->queue.erase(it);
   };
+  // the workspaces that the library keeps between calls (building a plan leaves
+  // up to 1 GiB or more) stay only in what plans and sessions leave of the budget
+  struct FitKept {
+    emsurf_server sv;
+    ~FitKept() {
+      if (sv->used + scratch_idle_bytes() > sv->d.budget_bytes) scratch_give_back();
+    }
+  } fit_kept{sv};
   std::map<uint64_t, int> queued_keys;
   for (auto& q : sv->queue) queued_keys[q->key] += 1;
   for (auto it = sv->queue.begin(); it != sv->queue.end();) {

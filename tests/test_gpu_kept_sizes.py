@@ -86,3 +86,27 @@ def test_kept_memory_is_released_on_request():
     E.emsurf_release_idle_memory()
     assert abs(before - free()) < 16 * MB
     assert before - pattern() > 60 * MB   # and the calls work on
+
+
+def test_a_server_keeps_within_its_budget():
+    """Building the surface's plan takes 470 MB of workspace, which a budget of its own bytes does not leave."""
+    import paper_1911_04576_amd as E
+    nothing_kept(E)
+    S, tm = W.random_types(2, 96, seed=1), W.random_type_map(20, 20, 2, seed=1)
+    b = W.random_vectors(2, 20, 20, 96, seed=2)
+    probe = E.emsurf_server_create(1 << 40, 4, E.solve_opts(E.EMSURF_FP32_IR, tol=1e-6))
+    budget = (E.emsurf_server_entry_bytes(probe, 20, 20, 96, 2) + 4 * E.emsurf_server_slot_bytes(probe, 20, 20, 96, 2)
+              + 32 * MB)
+    probe.destroy()
+    Pattern(E, 1)()
+    E.emsurf_release_idle_memory()
+    before = free()
+    srv = E.emsurf_server_create(budget, 4, E.solve_opts(E.EMSURF_FP32_IR, tol=1e-6))
+    E.emsurf_server_submit(srv, 1, 20, 20, 2, box(E), S, tm, b, recip=0)
+    while (done := E.emsurf_server_next_completed(srv)) is None:
+        E.emsurf_server_step(srv)
+    x, infos, _ = E.emsurf_server_fetch(srv, *done)
+    used = before - free()
+    print(f"budget {budget // MB} MB, {used // MB} MB in use", flush=True)
+    assert all(i["converged"] for i in infos) and used <= budget + 64 * MB
+    srv.destroy()
