@@ -270,10 +270,10 @@ emsurf_status emsurf_macromodels(int32_t n_types, int32_t n_eq, int32_t n_int, c
  *   E_dev   c128 [nrhs][Lv][Lu][2] output (E_theta, E_phi) per bin; bins with
  *           u^2 + v^2 >= 1 (no real direction) are set to zero.
  * Lu >= nx and Lv >= ny must be lengths of the form (2^a <= 1024 or
- * 3 * 2^a <= 768); larger ones sample the pattern more finely.  Workspaces of
- * nrhs * n_eq * Lu * (ny + Lv) complex values are taken as in
- * emsurf_macromodels for the call, which synchronises `stream` before
- * returning. */
+ * 3 * 2^a <= 768); larger ones sample the pattern more finely.  A workspace of
+ * nrhs * n_eq * Lu * ny complex values (Lu * (ny + Lv) for few columns of many
+ * bins and for many columns of few) is taken as in emsurf_macromodels for the
+ * call, which synchronises `stream` before returning. */
 emsurf_status emsurf_far_field(const emsurf_geom* geom, int32_t nx, int32_t ny, int32_t nrhs, int32_t Lu,
                                int32_t Lv, const void* x_dev, void* E_dev, void* stream);
 
@@ -287,8 +287,9 @@ emsurf_status emsurf_far_field(const emsurf_geom* geom, int32_t nx, int32_t ny, 
  *   D_dev      double [nrhs][2][Lv][Lu]: half space 0 (w >= 0) then 1 (w < 0);
  *              zero at bins outside the visible region.
  *   prad_host  double [nrhs] (may be NULL): P_rad in units of U.
- * Other arguments as for emsurf_far_field.  EMSURF_ERR_ARG if a right-hand
- * side radiates no power.  Synchronises `stream`. */
+ * Other arguments and workspace as for emsurf_far_field, with 2 nrhs Lv Lu
+ * more reals.  EMSURF_ERR_ARG, with D_dev left alone, if a right-hand side
+ * radiates no power (or one that is not finite).  Synchronises `stream`. */
 emsurf_status emsurf_directivity(const emsurf_geom* geom, int32_t nx, int32_t ny, int32_t nrhs, int32_t Lu,
                                  int32_t Lv, const void* x_dev, void* D_dev, double* prad_host, void* stream);
 

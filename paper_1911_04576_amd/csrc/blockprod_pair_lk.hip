@@ -24,7 +24,7 @@
 // right-hand sides, FP32: 609 us, 5.1 TB/s with the vectors).  One read of
 // the vectors serves both halves, in batches of independent loads written to
 // LDS in order, and a B operand is one word at a constant offset: 80 -> 73 us
-// at 32 x 32 and 374 -> 345 at 48 x 48 elements, n_eq 288, against a
+// at 32 x 32 elements of 192 unknowns and 374 -> 345 at 48 x 48 of 288, against a
 // pass per half, one load at a time, and both parts read for each operand.
 #include "internal.h"
 

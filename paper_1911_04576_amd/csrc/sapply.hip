@@ -209,12 +209,11 @@ struct XcdItems { int first[9]; };
 // Bound by the matrix cores with many columns, by latency with few.  So a
 // column's vector offset is looked up once into LDS (not divided out by every
 // thread), loads carry no conditions, operands leave LDS a chunk ahead of
-// their products, and a small tile fills the chip early: 32 x 32 outputs are
-// as fast as 64 x 64 in most places where there is work for both.  y = S t, 64 rows x 64
-// columns (FP64 32) before: 4 x 4 elements, n_eq 96, 1 right-hand side, FP32
-// 11.9 -> 5.8 us, FP64 12.9 -> 9.0; 48 x 40, n_eq 96, 12: 40 -> 26, 64 -> 50;
-// 61 x 61, n_eq 288, 12: 332 -> 301 (98 TFLOP/s), 650 -> 596.  The wide tile
-// below is the better one in other places (s_form).
+// their products, and a small tile fills the chip early.  y = S t, wide tile ->
+// this one: 12 x 12 elements, n_eq 96, 1 right-hand side, FP32 11.9 -> 5.2 us,
+// FP64 13.1 -> 8.6; 48 x 40, n_eq 96, 12: 38 -> 24, 63 -> 45; 61 x 61, n_eq 288, 12:
+// 332 -> 302 (97 TFLOP/s), 658 -> 590.  The wide tile below is the better one in
+// other places (s_form).
 template <typename T, typename VX, int RT>
 __global__ void __launch_bounds__(SA_THREADS, 3) apply_S_mfma_kernel(
     const T* __restrict__ Sp, const int* __restrict__ elem_sorted, const int* __restrict__ groups, int n, int M,

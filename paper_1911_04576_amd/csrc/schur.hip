@@ -740,8 +740,8 @@ __global__ void __launch_bounds__(256, 2) update_mfma_kernel(double2* __restrict
 // The same update by a persistent grid for the far columns of the lookahead:
 // workgroups of 512 threads, two halves of 256 with a tile each and LDS of
 // their own (133 KB in all, so that a CU holds at most one workgroup).  With a
-// grid of (CUs - 2 panel workgroups' worth) the update never occupies every
-// CU, and the next block's panels and near-column kernels, whose workgroups
+// grid of the CUs less one per matrix and 16 more the update never occupies
+// every CU, and the next block's panels and near-column kernels, whose workgroups
 // each need a CU to themselves, start on the ones it leaves instead of
 // waiting for it to drain.  A tile's work is a sequence of phases, for each
 // chunk of 32 block columns a load phase (the chunk of L21 and U12 into LDS,

@@ -20,7 +20,7 @@ struct SessionSlot {
 };
 
 // Device bytes of a session: the part held for its lifetime (batch staging,
-// reductions, item lists), the vectors of one slot ([b | x | r | V_0..V_m],
+// reductions, coefficients), the vectors of one slot ([b | x | r | V_0..V_m],
 // allocated when a slot is first used), and the total with every slot
 // allocated plus the apply workspace of its stream.
 size_t session_fixed_bytes(const emsurf_plan_desc& d, int max_slots, int restart);

@@ -9,8 +9,9 @@
 // limit or at the end of the cycle; then x += V y and, for the top-level solve,
 // the true residual ||b - A x|| decides whether to stop or restart.  Every
 // right-hand side runs its own instance; they advance in lockstep so that all
-// share one batched operator apply, and an instance that has stopped carries a
-// zero basis vector until the cycle ends.
+// share one batched operator apply.  An instance that has stopped goes on with
+// basis vectors that its solution takes no part of (y = 0; zero vectors after a
+// breakdown) until the cycle ends.
 //
 // Mixed precision (GMRES-IR): outer r = b - A x with the FP64 operator; inner
 // GMRES on A d = r with the FP32 operator (FP32 FFTs and products, FP64 basis,
