@@ -38,12 +38,18 @@ __device__ constexpr double kS16[16] = {
     0.0, -0.38268343236508978178, -0.70710678118654757274, -0.92387953251128673848,
     -1.0, -0.92387953251128673848, -0.70710678118654757274, -0.38268343236508978178};
 
-// sin of 2*pi*j/120, j = 0..30, and what its rounding to FP64 leaves out: the
-// constants inside the butterflies of radices 3, 5 and those composed of them
-// (6 to 24, which divide 120)
+// sin of 2*pi*j/16 and, for j = 0..30, of 2*pi*j/120, and what their rounding to
+// FP64 leaves out: the constants inside the butterflies of powers of two, and of
+// radices 3, 5 and those composed of them (6 to 24, which divide 120)
 struct HiLo {
   double hi, lo;
 };
+__device__ constexpr HiLo sin16(int j) {   // j >= 0
+  const double lo[4] = {0.0, -1.0050772696461588e-17, -4.833646656726457e-17, 1.7645047084336677e-17};
+  const double v = j % 8 == 4 ? 0.0 : lo[j % 8 < 4 ? j % 8 : 8 - j % 8];
+  return {kS16[j % 16], j % 16 < 8 ? v : -v};
+}
+__device__ constexpr HiLo cos16(int j) { return sin16(j + 4); }
 __device__ constexpr HiLo kSin120[31] = {
     {0.0, 0.0}, {0.052335956242943835, -1.9154745404913664e-18}, {0.10452846326765347, 5.525270925166623e-19},
     {0.15643446504023087, 5.047996510305999e-20}, {0.20791169081775934, -5.47375691962595e-18},
@@ -70,8 +76,9 @@ __device__ constexpr HiLo cos120(int j) { return sin120(j + 30); }
 // inverse, where the roundings of products average out.  FP32 structured
 // applies of 50 x 50 elements (100 points an axis, two radices 10), error
 // against 64 bits: 1.81e-7 with the rounded constants, 1.41e-7 with the rest
-// (1.35e-7 at 128 points); 90 x 100 elements 1.80e-7 -> 1.54e-7.  A multiply-add
-// for each, 1.2% of the latter apply.
+// (1.35e-7 at 128 points); 90 x 100 elements 1.80e-7 -> 1.54e-7.  In FP64, 320
+// points an axis: 2.56e-16, with radix 16's own rest too 2.17e-16 (2.02e-16 at
+// 384 points).  A multiply-add for each, 1.2% of the 90 x 100 apply.
 template <typename T> struct Const {
   T hi, lo;
   __device__ constexpr Const(HiLo c)
@@ -90,13 +97,20 @@ template <typename T> __device__ constexpr Const<T> negated(Const<T> c) {
   return c;
 }
 
+// v (c + sign i s)
+template <typename T, typename V> __device__ __forceinline__ V turn(Const<T> c, Const<T> s, V v, int sign) {
+  const Const<T> m = negated(s);
+  return V{times2(c, v.x, sign < 0 ? s : m, v.y), times2(c, v.y, sign < 0 ? m : s, v.x)};
+}
+
 // factors R = A B of a composite butterfly, 0 for the others
 constexpr int composite_a(int R) {
   return R == 6 ? 3 : R == 10 || R == 15 || R == 20 ? 5 : R == 12 ? 4 : R == 24 ? 8 : 0;
 }
 
 // In-register DFT of length R: a[k] <- sum_n a[n] e^{sign 2 pi i n k / R}.
-// LO: radix 3 with the rest of its constant too, as in the composite radices.
+// LO: constants with their rest in the powers of two and radix 3 too (the mixed
+// lengths), as in the composite radices.
 template <int R, typename V, bool LO = false>
 __device__ __forceinline__ void dft(V (&a)[R], int sign) {
   using T = typename Real<V>::T;
@@ -139,9 +153,7 @@ __device__ __forceinline__ void dft(V (&a)[R], int sign) {
       for (int k1 = 1; k1 < A; ++k1) {
         if (n2 == 0) continue;
         const int j = n2 * k1 % R * (120 / R);
-        const Const<T> wc(cos120(j)), ws(sin120(j)), wn = negated(ws);
-        const V v = c[n2][k1];
-        c[n2][k1] = V{times2(wc, v.x, sign < 0 ? ws : wn, v.y), times2(wc, v.y, sign < 0 ? wn : ws, v.x)};
+        c[n2][k1] = turn(Const<T>(cos120(j)), Const<T>(sin120(j)), c[n2][k1], sign);
       }
     }
 #pragma unroll
@@ -162,8 +174,8 @@ __device__ __forceinline__ void dft(V (&a)[R], int sign) {
     V e[H], o[H];
 #pragma unroll
     for (int i = 0; i < H; ++i) { e[i] = a[2 * i]; o[i] = a[2 * i + 1]; }
-    dft<H, V>(e, sign);
-    dft<H, V>(o, sign);
+    dft<H, V, LO>(e, sign);
+    dft<H, V, LO>(o, sign);
 #pragma unroll
     for (int k = 0; k < H; ++k) {
       constexpr int step = 16 / R;
@@ -174,8 +186,12 @@ __device__ __forceinline__ void dft(V (&a)[R], int sign) {
       } else if (j == 4) {
         t = mul_si(o[k], sign);
       } else {
-        V w{static_cast<T>(kC16[j]), static_cast<T>(sign < 0 ? -kS16[j] : kS16[j])};
-        t = cmul(w, o[k]);
+        if constexpr (LO) {
+          t = turn(Const<T>(cos16(j)), Const<T>(sin16(j)), o[k], sign);
+        } else {
+          V w{static_cast<T>(kC16[j]), static_cast<T>(sign < 0 ? -kS16[j] : kS16[j])};
+          t = cmul(w, o[k]);
+        }
       }
       a[k] = cadd(e[k], t);
       a[k + H] = csub(e[k], t);
@@ -212,6 +228,7 @@ struct PassArgs {
 // Lengths 2^a (2..1024) and 3 * 2^a (24..768) run radix-16 or radix-8 stages
 // while possible, then what is left of the power of two, then radix 3.
 template <int L, int WD = 1> struct Shape {
+  static constexpr bool MIXED = false;
   static constexpr bool R3 = L % 3 == 0;
   static constexpr int VPT = R3 ? 24 : (L >= 16 ? 16 : L);
   static constexpr int NT = (R3 ? 128 : 256) * WD;
@@ -248,6 +265,7 @@ template <int L, int WD = 1> struct Shape {
 // composite radices (one LDS exchange), with 16 or 32 columns and 10 to 24
 // values per thread.
 template <int L_, int WD, int G_, int BT_, int R0, int R1, int R2> struct MixedShape {
+  static constexpr bool MIXED = true;
   static constexpr int G = G_, BT = BT_ * WD, NT = G * BT;
   static constexpr int NST = R2 > 1 ? 3 : R1 > 1 ? 2 : 1;
   static constexpr int radix(int s) { return s == 0 ? R0 : s == 1 ? R1 : R2; }
@@ -350,7 +368,7 @@ __device__ __forceinline__ void run_stage(const PassArgs& a, VC* lds, const VI* 
         v[j][q] = cmul(v[j][q], w);
       }
     }
-    dft<R, VC>(v[j], a.sign);
+    dft<R, VC, SH::MIXED>(v[j], a.sign);
   }
   // ---- store
 #pragma unroll
